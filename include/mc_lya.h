@@ -199,7 +199,7 @@ enum {
                                      once (1..1024, default 512; smaller claims near the end
                                      of the input) */
     MC_LYA_OPT_TILE_REFILL = 14,  /* tiled walk: refill a wave once this many lanes are idle
-                                     (1..64, default 40) */
+                                     (1..64, default 32) */
     MC_LYA_OPT_TAIL = 15,         /* tiled walk: once fewer packets than this many millionths
                                      of a batch are in flight (0..1000000, default 20000 =
                                      2 %; 0 = never), one kernel walks them to the end with
@@ -221,8 +221,8 @@ enum {
  *               emission weight, quantised weight, packet count, first packet
  *               and absorbed tally (36 bytes), plus 48 bytes with evolve = 1;
  *   per packet  its cell (4 bytes) and two generations of tiled-walk
- *               hand-over state (234 bytes) for B = batch_packets packets (N
- *               if 0): 4 N + 234 B bytes; if the hand-over part cannot be
+ *               hand-over state (138 bytes) for B = batch_packets packets (N
+ *               if 0): 4 N + 138 B bytes; if the hand-over part cannot be
  *               allocated, init halves B down to 2^25 packets; the tiled
  *               walk walks emissions larger than B in batches of B;
  *   per tile    its table entry and exit lists (about 140 bytes);
@@ -234,7 +234,7 @@ typedef struct mc_lya_limits {
                                      call returns ESTATE */
     int32_t reserved;             /* 0 */
     uint64_t batch_packets;       /* packets of one tiled-walk batch (0 = max_packets): the
-                                     hand-over state reserved for it is 234 bytes a packet;
+                                     hand-over state reserved for it is 138 bytes a packet;
                                      larger emissions walk in batches (the same integers) */
 } mc_lya_limits;
 

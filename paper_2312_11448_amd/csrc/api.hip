@@ -174,7 +174,7 @@ struct mc_lya_ctx {
     int state = 0;                    // 0 packed, 1 emitted, 2 transported
     // options
     int kernel = 2, block = 256, waves_per_cu = 32, chunk = 256, refill = 16, nqueues = 8;
-    int tile_chunk = 512, tile_refill = 40;  // the tiled walk's own chunk and refill
+    int tile_chunk = 512, tile_refill = 32;  // the tiled walk's own chunk and refill
     int64_t max_cross = 1000000;
     int timing = 0;                          // 0 off, 1 per launch, 2 per transport
     int64_t coarse_launches = 0;
@@ -438,7 +438,7 @@ mc_lya_status classify_boxes(mc_lya_ctx *c)
 // or, if that much memory cannot be had, for as many as fit in halving steps
 // down to 2^25; a larger emission then walks in batches. Every batch repeats
 // the per-generation tile loads and flushes, so fewer batches are faster;
-// the 2^28 packets of the 256^3 workload (63 GB of state) are one batch on a
+// the 2^28 packets of the 256^3 workload (37 GB of state) are one batch on a
 // 288 GB device.
 constexpr uint64_t kMinTiledBatch = 1ull << 25;
 constexpr int kGenRound = 16;                  // generations queued between two checks

@@ -218,19 +218,25 @@ struct TileInfo {
 };
 static_assert(sizeof(TileInfo) == 64, "TileInfo layout");
 
-// A packet standing on the face between two tiles (112 bytes).
-struct alignas(16) PState {
-    double tmx, tmy, tmz, tdx, tdy, tdz, t;
+// A packet handed from one tile generation to the next: 64 bytes, so that a
+// lane's read through the index list is one aligned memory sector. It is
+// stored standing on the face it crosses, before the crossing: tm are the face
+// distances not yet advanced, so the smallest one names the face and is the
+// path length walked; the advance, the reciprocals td = 1/|k| and the binary32
+// direction are formed again on loading, by the expressions that formed them
+// first. kz = 2u - 1 of a 23-bit uniform is exact in binary32. A packet
+// deferred inside its cell is stored the same way, at the face it came in by.
+struct alignas(64) PState {
+    double tm[3];
+    double kx, ky;
+    float kz;
+    float x;                 // gas-frame frequency (of the cell it leaves; deferred: of its cell)
+    float ku;                // k . U of that cell (Doppler units)
     uint32_t w;
-    uint32_t pad;
-    float x, kx, ky, kz;     // pre-jump frequency and direction
-    float ku;                // k . U of the cell it leaves (Doppler units)
-    uint32_t pad2[2];
-    uint32_t cell;           // cell it enters (global)
     uint32_t ncross;
-    int32_t ix, iy, iz;      // coordinates of that cell
+    uint32_t pos;            // its cell in the tile that takes it up: x + 16 y + 256 z
 };
-static_assert(sizeof(PState) == 112, "PState layout");
+static_assert(sizeof(PState) == 64, "PState layout");
 
 // Exit lists of one tile in one generation: states in [base, base + off[7]),
 // and the states that left through face f are idx[base + off[f] .. base + off[f+1]).

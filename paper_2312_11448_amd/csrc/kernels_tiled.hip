@@ -75,6 +75,7 @@ struct TileCtx {
 // tile (found from the record of the slot it steps into, kOutside).
 struct TLane {
     double tmx, tmy, tmz, tdx, tdy, tdz, t;
+    double kxd, kyd;         // (the hand-over state's direction)
     float kx, ky, kz;
     float x, kap, ku;
     uint32_t w, ncross;
@@ -107,9 +108,9 @@ __device__ __forceinline__ Rec rec_at(const char *recs, int32_t q)
     return r;
 }
 
-// A packet standing in cell (L.ix, L.iy, L.iz) of this tile, as a TLane.
+// A packet standing in cell (lx, ly, lz) of this tile, as a TLane.
 template <int RS>
-__device__ __forceinline__ void to_tile(TLane &T, const Lane &L, const TileCtx &C)
+__device__ __forceinline__ void to_tile(TLane &T, const Lane &L, int32_t lx, int32_t ly, int32_t lz)
 {
     T.tmx = L.tmx;
     T.tmy = L.tmy;
@@ -118,6 +119,8 @@ __device__ __forceinline__ void to_tile(TLane &T, const Lane &L, const TileCtx &
     T.tdy = L.tdy;
     T.tdz = L.tdz;
     T.t = L.t;
+    T.kxd = L.kxd;
+    T.kyd = L.kyd;
     T.kx = L.kx;
     T.ky = L.ky;
     T.kz = L.kz;
@@ -126,22 +129,11 @@ __device__ __forceinline__ void to_tile(TLane &T, const Lane &L, const TileCtx &
     T.ku = L.ku;
     T.w = L.w;
     T.ncross = L.ncross;
-    T.q = tile_slot(L.ix - C.ox, L.iy - C.oy, L.iz - C.oz) * RS;
+    T.q = tile_slot(lx, ly, lz) * RS;
     // the walk steps +1 along an axis when the direction's component is > 0, else -1
     T.dqx = L.kx > 0.0f ? RS : -RS;
     T.dqy = L.ky > 0.0f ? kSX * RS : -kSX * RS;
     T.dqz = L.kz > 0.0f ? kSX * kSY * RS : -kSX * kSY * RS;
-}
-
-// Global coordinates of a TLane's cell.
-template <int RS>
-__device__ __forceinline__ void tile_cell(const TLane &T, const TileCtx &C, int32_t &ix, int32_t &iy, int32_t &iz)
-{
-    int32_t lx, ly, lz;
-    slot_cell((int32_t)((uint32_t)T.q / (uint32_t)RS), lx, ly, lz);
-    ix = C.ox + lx;
-    iy = C.oy + ly;
-    iz = C.oz + lz;
 }
 
 // Along an axis the tile spans, one cell past either end of the tile is its
@@ -255,6 +247,8 @@ __device__ __forceinline__ void idle_tlane(TLane &T, int32_t rs)
     T.tmx = T.tmy = T.tmz = 1.0;
     T.tdx = T.tdy = T.tdz = 1.0;
     T.t = 0.0;
+    T.kxd = 1.0;
+    T.kyd = 0.0;
     T.kx = 1.0f;
     T.ky = T.kz = 0.0f;
     T.x = -3.0e38f;
@@ -268,68 +262,68 @@ __device__ __forceinline__ void idle_tlane(TLane &T, int32_t rs)
     T.dqz = kSX * kSY * rs;
 }
 
+// Offsets of a cell inside its tile, packed (tile origins are multiples of
+// the tile edge, so they are the low bits of the box coordinates).
+static_assert((kTileX & (kTileX - 1)) == 0 && (kTileY & (kTileY - 1)) == 0 && (kTileZ & (kTileZ - 1)) == 0 &&
+                  kTileX <= 16 && kTileY <= 16 && kTileZ <= 16,
+              "a cell's offset in its tile takes 4 bits per axis");
+__device__ __forceinline__ uint32_t pack_pos(int32_t ix, int32_t iy, int32_t iz)
+{
+    return (uint32_t)(ix & (kTileX - 1)) | (uint32_t)(iy & (kTileY - 1)) << 4 | (uint32_t)(iz & (kTileZ - 1)) << 8;
+}
+
+// The state with the face distances (tx, ty, tz) and the cell at offsets pos.
+__device__ __forceinline__ void save_state(PState *out, const TLane &L, double tx, double ty, double tz, uint32_t pos)
+{
+    PState o;
+    o.tm[0] = tx;
+    o.tm[1] = ty;
+    o.tm[2] = tz;
+    o.kx = L.kxd;
+    o.ky = L.kyd;
+    o.kz = L.kz;
+    o.x = L.x;
+    o.ku = L.ku;
+    o.w = L.w;
+    o.ncross = L.ncross;
+    o.pos = pos;
+    *out = o;
+}
+
 // A packet standing on the tile's edge, written for the neighbouring tile:
-// the face crossing that tile_step left undone (the same face choice and
-// FP64 advance as walk_step, and the next cell with the box's periodic wrap),
-// with the pre-jump frequency and the velocity of the cell it leaves.
+// the face crossing that tile_step left undone is left to the tile that takes
+// the packet up (load_state); the next cell is the one behind that face, with
+// the box's periodic wrap. Returns the face it leaves through.
 template <int RS>
-__device__ __forceinline__ uint32_t save_exit(PState &o, const TLane &L, const TileCtx &C, const WalkBox &B)
+__device__ __forceinline__ uint32_t save_exit(PState *out, const TLane &L, const TileCtx &C, const WalkBox &B)
 {
     const Face f = next_face(L.tmx, L.tmy, L.tmz);
-    int32_t ix, iy, iz;
-    tile_cell<RS>(L, C, ix, iy, iz);
+    int32_t lx, ly, lz;
+    slot_cell((int32_t)((uint32_t)L.q / (uint32_t)RS), lx, ly, lz);
+    const int32_t ix = C.ox + lx, iy = C.oy + ly, iz = C.oz + lz;
     const int32_t ci = (f.bx ? ix : 0) + (f.by ? iy : 0) + (f.bz ? iz : 0);
     const int32_t ni = (f.bx ? B.nx : 0) + (f.by ? B.ny : 0) + (f.bz ? B.nz : 0);
     const bool up = (f.bx & (L.kx > 0.0f)) | (f.by & (L.ky > 0.0f)) | (f.bz & (L.kz > 0.0f));
     int32_t mi = ci + (up ? 1 : -1);
     mi = mi == ni ? 0 : mi;
     mi = mi < 0 ? ni - 1 : mi;
-    const int32_t jx = f.bx ? mi : ix, jy = f.by ? mi : iy, jz = f.bz ? mi : iz;
-    o.tmx = f.bx ? L.tmx + L.tdx : L.tmx;
-    o.tmy = f.by ? L.tmy + L.tdy : L.tmy;
-    o.tmz = f.bz ? L.tmz + L.tdz : L.tmz;
-    o.tdx = L.tdx;
-    o.tdy = L.tdy;
-    o.tdz = L.tdz;
-    o.t = f.tn;
-    o.w = L.w;
-    o.x = L.x;
-    o.kx = L.kx;
-    o.ky = L.ky;
-    o.kz = L.kz;
-    o.ku = L.ku;
-    o.cell = B.cell_off + (uint32_t)jx + (uint32_t)B.nx * ((uint32_t)jy + (uint32_t)B.ny * (uint32_t)jz);
-    o.ncross = L.ncross;
-    o.ix = jx;
-    o.iy = jy;
-    o.iz = jz;
-    return (f.bx ? 0u : (f.by ? 2u : 4u)) + (up ? 1u : 0u);   // the face it leaves through
+    save_state(out, L, L.tmx, L.tmy, L.tmz, pack_pos(f.bx ? mi : ix, f.by ? mi : iy, f.bz ? mi : iz));
+    return (f.bx ? 0u : (f.by ? 2u : 4u)) + (up ? 1u : 0u);
 }
 
 // A packet deferred to the tile's next generation, standing inside its cell.
+// It has crossed a face in this generation: along the axis of its last
+// crossing the next face is td past the path length walked, and storing that
+// length there puts it back on the face (of two such axes either serves: both
+// were crossed at the same length, and both advance to the same distance).
 template <int RS>
-__device__ __forceinline__ void save_here(PState &o, const TLane &L, const TileCtx &C, const WalkBox &B)
+__device__ __forceinline__ void save_here(PState *out, const TLane &L)
 {
-    int32_t ix, iy, iz;
-    tile_cell<RS>(L, C, ix, iy, iz);
-    o.tmx = L.tmx;
-    o.tmy = L.tmy;
-    o.tmz = L.tmz;
-    o.tdx = L.tdx;
-    o.tdy = L.tdy;
-    o.tdz = L.tdz;
-    o.t = L.t;
-    o.w = L.w;
-    o.x = L.x;
-    o.kx = L.kx;
-    o.ky = L.ky;
-    o.kz = L.kz;
-    o.ku = L.ku;
-    o.cell = B.cell_off + (uint32_t)ix + (uint32_t)B.nx * ((uint32_t)iy + (uint32_t)B.ny * (uint32_t)iz);
-    o.ncross = L.ncross;
-    o.ix = ix;
-    o.iy = iy;
-    o.iz = iz;
+    int32_t lx, ly, lz;
+    slot_cell((int32_t)((uint32_t)L.q / (uint32_t)RS), lx, ly, lz);
+    const bool bx = L.tdx < kFar && L.tmx == L.t + L.tdx;
+    const bool by = !bx && L.tdy < kFar && L.tmy == L.t + L.tdy;
+    save_state(out, L, bx ? L.t : L.tmx, by ? L.t : L.tmy, !bx && !by ? L.t : L.tmz, pack_pos(lx, ly, lz));
 }
 
 __device__ __forceinline__ uint32_t rank_in(uint64_t mask)
@@ -347,26 +341,28 @@ __device__ __forceinline__ T wave_sum(T v)
     return v;
 }
 
+// The packet of a hand-over state, its face crossed (all but its cell's
+// record and global index).
 __device__ __forceinline__ void load_state(Lane &L, const PState &o, const WalkBox &B)
 {
-    L.tmx = o.tmx;
-    L.tmy = o.tmy;
-    L.tmz = o.tmz;
-    L.tdx = o.tdx;
-    L.tdy = o.tdy;
-    L.tdz = o.tdz;
-    L.t = o.t;
+    const double kz = (double)o.kz;
+    L.tdx = o.kx != 0.0 ? 1.0 / fabs(o.kx) : kFar;
+    L.tdy = o.ky != 0.0 ? 1.0 / fabs(o.ky) : kFar;
+    L.tdz = kz != 0.0 ? 1.0 / fabs(kz) : kFar;
+    const Face f = next_face(o.tm[0], o.tm[1], o.tm[2]);
+    L.t = f.tn;
+    L.tmx = f.bx ? o.tm[0] + L.tdx : o.tm[0];
+    L.tmy = f.by ? o.tm[1] + L.tdy : o.tm[1];
+    L.tmz = f.bz ? o.tm[2] + L.tdz : o.tm[2];
+    L.kxd = o.kx;
+    L.kyd = o.ky;
+    L.kx = (float)o.kx;
+    L.ky = (float)o.ky;
+    L.kz = o.kz;
     L.w = o.w;
     L.x = o.x;
-    L.kx = o.kx;
-    L.ky = o.ky;
-    L.kz = o.kz;
     L.ku = o.ku;
-    L.c = o.cell;
     L.ncross = o.ncross;
-    L.ix = o.ix;
-    L.iy = o.iy;
-    L.iz = o.iz;
     L.nx = B.nx;
     L.ny = B.ny;
     L.nz = B.nz;
@@ -412,7 +408,7 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
         if (__ballot(parked)) {
             if (parked) {
                 const uint32_t g = s_base + atomicAdd(s_exit, 1u);
-                const uint32_t f = save_exit<RS>(P.out_state[g], L, C, B);
+                const uint32_t f = save_exit<RS>(&P.out_state[g], L, C, B);
                 P.out_face[g] = (uint8_t)f;
                 atomicAdd(&s_fcnt[f], 1u);
                 L.w = 0u;
@@ -422,7 +418,10 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
     uint32_t cur = 0, end = 0;
     const uint32_t chunk = (uint32_t)P.chunk;
     // refilling stalls the whole wave on the new packets' loads: wait until
-    // this many lanes are idle (1..64; 64 waits for all)
+    // this many lanes are idle (1..64; 64 waits for all). On 256^3 a threshold
+    // of 24 / 32 / 40 / 48 walks in 107.6 / 105.8 / 108.2 / 114.4 ms: fewer
+    // lanes idle against fewer refill passes. With 112-byte states the best
+    // was 40, at 136 ms: a refill then read 2.6 sectors a lane, now 1.
     const uint32_t refill = (uint32_t)min(max(P.refill, 1), 64);
     // a ring slot of this lane's own (the ring's z = -1 plane has 324 slots),
     // whose tally is never read: where a lane with nothing to deposit adds 0
@@ -459,13 +458,16 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
             if (!alive && r < take) {
                 const uint32_t j = cur + r;
                 Lane N;
+                int32_t lx, ly, lz;
                 if (GEN0) {
                     int lo = 0, hi = ncell - 1;             // largest cell with pre <= j
                     while (lo < hi) {
                         const int mid = (lo + hi + 1) >> 1;
                         if (pre[mid] <= j) lo = mid; else hi = mid - 1;
                     }
-                    const int lx = lo % ti.sx, ly = (lo / ti.sx) % ti.sy, lz = lo / (ti.sx * ti.sy);
+                    lx = lo % ti.sx;
+                    ly = (lo / ti.sx) % ti.sy;
+                    lz = lo / (ti.sx * ti.sy);
                     const uint32_t gc = B.cell_off + (uint32_t)(ti.ox + lx) +
                                         (uint32_t)B.nx * ((uint32_t)(ti.oy + ly) + (uint32_t)B.ny * (uint32_t)(ti.oz + lz));
                     const uint64_t pf = P.pfirst[gc];
@@ -481,12 +483,16 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
 #pragma unroll
                     for (int m = 1; m <= 6; ++m) k += (m <= ti.nsrc && pre[m] <= j) ? 1 : 0;
                     const uint32_t g = P.in_idx[lst[k] + (j - pre[k])];
-                    load_state(N, P.in_state[g], B);
-                    const Rec rc = rec_at<VEL>(recs, tile_slot(N.ix - ti.ox, N.iy - ti.oy, N.iz - ti.oz) * RS);
+                    const PState o = P.in_state[g];
+                    load_state(N, o, B);
+                    lx = (int32_t)(o.pos & 15u);
+                    ly = (int32_t)(o.pos >> 4 & 15u);
+                    lz = (int32_t)(o.pos >> 8);
+                    const Rec rc = rec_at<VEL>(recs, tile_slot(lx, ly, lz) * RS);
                     if (k < ti.nsrc) finish_entry<VEL>(N, rc);   // entering through a face
                     else N.kap = rc.kap;                         // deferred inside its cell
                 }
-                to_tile<RS>(L, N, C);
+                to_tile<RS>(L, N, lx, ly, lz);
                 alive = true;
             }
             fresh = true;
@@ -510,7 +516,7 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
                 flush_exits();
                 if (alive) {
                     const uint32_t g = s_base + atomicAdd(s_exit, 1u);
-                    save_here<RS>(P.out_state[g], L, C, B);
+                    save_here<RS>(&P.out_state[g], L);
                     P.out_face[g] = (uint8_t)kDeferred;
                     atomicAdd(&s_fcnt[kDeferred], 1u);
                 }
@@ -852,13 +858,27 @@ __global__ __launch_bounds__(256) void tail_walk_kernel(TailParams P)
         }
         const TileExits e = P.exits[q][lo];
         const uint32_t k = P.idx[q][e.base + ((uint32_t)i - P.prefix[lo])];
-        box = P.tiles[lo].box;
+        const TileInfo &src = P.tiles[lo];
+        box = src.box;
         const WalkBox B = P.boxes[box];
+        // the tile that takes the packet up: its own for a deferred one, else
+        // the neighbour behind the face it left through (the neighbour that
+        // this tile pulls from through the opposite face)
+        const uint32_t face = P.face[q][k];
+        int to = lo;
+        for (int m = 0; m < src.nsrc; ++m)
+            if ((src.src_faces >> (4 * m) & 15u) == (face ^ 1u)) to = src.src_tile[m];
+        const TileInfo &dst = P.tiles[to];
         Lane L;
-        load_state(L, P.state[q][k], B);
+        const PState o = P.state[q][k];
+        load_state(L, o, B);
+        L.ix = dst.ox + (int32_t)(o.pos & 15u);
+        L.iy = dst.oy + (int32_t)(o.pos >> 4 & 15u);
+        L.iz = dst.oz + (int32_t)(o.pos >> 8);
+        L.c = cell_of(L);
         const uint32_t cross0 = L.ncross;          // crossings walked by the tile generations
         const Rec r = load_rec<VEL>(P.rec, L.c);
-        if (P.face[q][k] == kDeferred) L.kap = r.kap;   // deferred inside its cell
+        if (face == kDeferred) L.kap = r.kap;   // deferred inside its cell
         else finish_entry<VEL>(L, r);                   // entering through a face
         const Line ln = line_of(B);
         uint64_t dep = 0;

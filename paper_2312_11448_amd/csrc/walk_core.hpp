@@ -38,6 +38,7 @@ struct Lane {
     double tmx, tmy, tmz;
     double tdx, tdy, tdz;
     double t;
+    double kxd, kyd;     // direction along x and y (hand-over between tiles)
     float kx, ky, kz;    // direction (binary32: velocity terms only)
     float x;             // gas-frame frequency, Doppler widths
     float kap;           // kappa of the current cell
@@ -139,6 +140,8 @@ __device__ __forceinline__ void emit_packet(Lane &L, const WalkBox &B, uint64_t 
     L.tmy = ky != 0.0 ? (ky > 0.0 ? 1.0 - fy : fy) * L.tdy : kFar;
     L.tmz = kz != 0.0 ? (kz > 0.0 ? 1.0 - fz : fz) * L.tdz : kFar;
     L.t = 0.0;
+    L.kxd = kx;
+    L.kyd = ky;
     L.kx = (float)kx;
     L.ky = (float)ky;
     L.kz = (float)kz;
