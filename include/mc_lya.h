@@ -117,7 +117,9 @@ typedef struct mc_lya_box_stats {
     int64_t escaped;              /* weight redshifted out of the line */
     int64_t capped_weight;        /* weight of packets stopped by the crossing cap */
     int64_t capped_packets;
-    int64_t crossings;            /* (packet, cell) segments walked */
+    int64_t crossings;            /* (packet, cell) segments of the packets' walks, those counted
+                                     without a step among them (a packet that no cell can take
+                                     weight from any more) */
     int64_t packets;              /* packets emitted in the box */
     int32_t conserved;            /* 1 iff absorbed + escaped + capped_weight == emitted */
     int32_t tiled;                /* 1 if the last walk of the box's packets was the tile-decomposed
@@ -220,11 +222,12 @@ enum {
  *   per cell    the packed record (4 bytes, 16 with a velocity field), the
  *               emission weight, quantised weight, packet count, first packet
  *               and absorbed tally (36 bytes), plus 48 bytes with evolve = 1;
- *   per packet  its cell (4 bytes) and two generations of tiled-walk
- *               hand-over state (138 bytes) for B = batch_packets packets (N
- *               if 0): 4 N + 138 B bytes; if the hand-over part cannot be
- *               allocated, init halves B down to 2^25 packets; the tiled
- *               walk walks emissions larger than B in batches of B;
+ *   per packet  its cell (4 bytes) and the tiled walk's packet states (two
+ *               generations' hand-over states and the list of packets with no
+ *               deposit left: 202 bytes) for B = batch_packets packets (N if
+ *               0): 4 N + 202 B bytes; if the states cannot be allocated,
+ *               init halves B down to 2^25 packets; the tiled walk walks
+ *               emissions larger than B in batches of B;
  *   per tile    its table entry and exit lists (about 140 bytes);
  *   per box     a few hundred bytes of tables and per-block partial sums. */
 typedef struct mc_lya_limits {
@@ -234,7 +237,7 @@ typedef struct mc_lya_limits {
                                      call returns ESTATE */
     int32_t reserved;             /* 0 */
     uint64_t batch_packets;       /* packets of one tiled-walk batch (0 = max_packets): the
-                                     hand-over state reserved for it is 138 bytes a packet;
+                                     hand-over state reserved for it is 202 bytes a packet;
                                      larger emissions walk in batches (the same integers) */
 } mc_lya_limits;
 

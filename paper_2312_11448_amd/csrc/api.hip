@@ -102,6 +102,7 @@ struct mc_lya_ctx {
     std::vector<PackBox> pack;
     std::vector<WalkBox> walk;
     std::vector<BoxRed> red;
+    std::vector<RedBox> redbox;       // the deposit-free end of a walk, per box (set by refresh)
     std::vector<uint64_t> walked;     // packets walked per box since the last emit
     std::vector<uint8_t> walked_tiled;  // per box: the last walk of its packets was the tiled walk
     uint64_t total_cells = 0;
@@ -115,6 +116,7 @@ struct mc_lya_ctx {
     WalkBox *d_walk = nullptr;
     BoxRed *d_red = nullptr;
     BoxTot *d_tot = nullptr;
+    RedBox *d_redbox = nullptr;
     void *d_rec = nullptr;
     double *d_wgt = nullptr;
     double *d_part = nullptr;
@@ -142,6 +144,7 @@ struct mc_lya_ctx {
     uint8_t *d_face[2] = {nullptr, nullptr};
     uint32_t *d_idx[2] = {nullptr, nullptr};
     unsigned long long *d_gen = nullptr;     // per generation: bump allocator, exits
+    PState *d_redlist = nullptr;             // [state_cap] packets with no deposit left to make
     uint64_t state_cap = 0;
     int64_t generations = 0;                 // generations launched by the last tiled transport
     std::vector<uint8_t> tiled;              // per box: walked by tiles (1) or by the persistent walk (0)
@@ -208,6 +211,8 @@ mc_lya_status hip_fail(mc_lya_ctx *c, hipError_t e, const char *what)
         if (e_ != hipSuccess) return hip_fail((ctx), e_, #expr);     \
     } while (0)
 
+void free_tile_buffers(mc_lya_ctx *c);
+
 void free_all(mc_lya_ctx *c)
 {
     if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
@@ -219,12 +224,13 @@ void free_all(mc_lya_ctx *c)
     if (c->join) (void)hipEventDestroy(c->join);
     c->side = nullptr;
     c->fork = c->join = nullptr;
-    void *ptrs[] = {c->d_pack, c->d_walk, c->d_red, c->d_tot, c->d_rec, c->d_wgt, c->d_part, c->d_q,
+    void *ptrs[] = {c->d_pack, c->d_walk, c->d_red, c->d_tot, c->d_redbox, c->d_rec, c->d_wgt, c->d_part, c->d_q,
                     c->d_bsum, c->d_npk, c->d_A, c->d_queue, c->d_boxabs, c->d_fsum, c->d_feed,
-                    c->d_cop, c->d_pfirst, c->d_seg, c->d_featbox, c->d_tail_prefix, c->d_tiles, c->d_texits[0], c->d_texits[1], c->d_state[0], c->d_sbox, c->d_ev, c->d_ev_coef,
-                    c->d_state[1], c->d_face[0], c->d_face[1], c->d_idx[0], c->d_idx[1], c->d_gen};
+                    c->d_cop, c->d_pfirst, c->d_seg, c->d_featbox, c->d_tail_prefix, c->d_tiles, c->d_texits[0], c->d_texits[1], c->d_sbox, c->d_ev, c->d_ev_coef,
+                    c->d_gen};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
+    free_tile_buffers(c);
     for (auto &ev : c->events) {
         (void)hipEventDestroy(ev.first);
         (void)hipEventDestroy(ev.second);
@@ -258,6 +264,37 @@ std::string check_desc(const mc_lya_box_desc &d, int b)
     if (d.profile != MC_LYA_PROFILE_DOPPLER && d.profile != MC_LYA_PROFILE_VOIGT)
         return bad("profile must be MC_LYA_PROFILE_DOPPLER or MC_LYA_PROFILE_VOIGT");
     return std::string();
+}
+
+// The constants of red_only and red_count for a box with largest kappa kmax,
+// drift delta, threshold x_eff and largest flow deviation udev from the mean
+// flow u. The bounds: a segment is at most 1.75 cells long; the thermal
+// profile at x is exp(-x^2)/sqrt(pi); the Voigt correction -(2a/pi) F'(x) is at
+// most damp 0.85 / x^2 for |x| >= 1; 2 % for the binary32 evaluation. One
+// face rounds x twice (the drift, the jump), by at most half an ulp of x_eff's
+// binade each, and the jump's difference of projections once; a segment's
+// length by 2^-24 of itself.
+// With a flow, red_count's decisions are unsure within the sum of those
+// roundings over the walk that is left, so it pays where that sum is well
+// below a cell's drift: at most a quarter of delta (at delta = 0.019, the
+// paper's cells, it is under 3 % of it, and some 2 % of the packets are
+// unsure; below delta = 0.006 most would be).
+RedBox red_constants(double kmax, double delta, double x_eff, const double u[3], double udev, bool vel, double damp)
+{
+    RedBox r;
+    std::memset(&r, 0, sizeof r);
+    r.cg = (float)(std::max(kmax, 0.0) * delta * 1.75 * 0.5641895835477563 * 1.02);
+    r.cv = (float)(std::max(kmax, 0.0) * delta * 1.75 * damp * 0.85 * 1.02);
+    for (int a = 0; a < 3; ++a) r.ub[a] = (float)u[a];
+    r.udev = (float)(udev * 1.0001 + 1e-4);
+    auto half_ulp = [](double v) { return std::ldexp(1.0, std::ilogb(std::max(v, 1e-30)) - 24); };
+    const double round = 1.02 * (2.0 * half_ulp(x_eff) + half_ulp(2.0 * udev + 1e-6) + delta * 1.75 * 0x1p-24);
+    r.round = (float)round;
+    const bool still = !vel || (udev == 0.0 && u[0] == 0.0 && u[1] == 0.0 && u[2] == 0.0);
+    const double most = 1.7321 * 2.0 * (x_eff + udev) / delta + 4.0;
+    const bool fine = std::isfinite(r.cg) && std::isfinite(r.cv) && std::isfinite(x_eff) && delta > 0.0;
+    r.mode = !fine ? kRedOff : still ? kRedStill : round * most <= 0.25 * delta ? kRedFlow : kRedOff;
+    return r;
 }
 
 // Expected crossings per packet in a homogeneous box with opacity kappa per
@@ -335,6 +372,10 @@ mc_lya_status do_refresh(mc_lya_ctx *c)
             w.kfar = 0.0f;
             w.xblue = std::numeric_limits<float>::infinity();
         }
+        const double nc = (double)w.cells();
+        const double um[3] = {c->red[b].usum[0] / nc, c->red[b].usum[1] / nc, c->red[b].usum[2] / nc};
+        c->redbox[b] = red_constants((double)c->red[b].kappa_max, (double)w.delta, (double)w.x_eff, um, udev, c->vel,
+                                     (double)w.damp);
         c->cpp[b] = crossings_per_packet(c->red[b].kappa_sum / (double)w.cells(), w.delta, w.x_eff, (double)w.w0);
     }
     c->state = 0;
@@ -438,22 +479,21 @@ mc_lya_status classify_boxes(mc_lya_ctx *c)
 // or, if that much memory cannot be had, for as many as fit in halving steps
 // down to 2^25; a larger emission then walks in batches. Every batch repeats
 // the per-generation tile loads and flushes, so fewer batches are faster;
-// the 2^28 packets of the 256^3 workload (37 GB of state) are one batch on a
+// the 2^28 packets of the 256^3 workload (54 GB of state) are one batch on a
 // 288 GB device.
 constexpr uint64_t kMinTiledBatch = 1ull << 25;
 constexpr int kGenRound = 16;                  // generations queued between two checks
-constexpr uint64_t kStateBytes = 2 * (sizeof(PState) + sizeof(uint8_t) + sizeof(uint32_t));
 
+// (one allocation of each kind: two generations' states and the red list, two
+// generations' faces, two generations' indices)
 void free_tile_buffers(mc_lya_ctx *c)
 {
-    for (int i = 0; i < 2; ++i) {
-        if (c->d_state[i]) (void)hipFree(c->d_state[i]);
-        if (c->d_face[i]) (void)hipFree(c->d_face[i]);
-        if (c->d_idx[i]) (void)hipFree(c->d_idx[i]);
-        c->d_state[i] = nullptr;
-        c->d_face[i] = nullptr;
-        c->d_idx[i] = nullptr;
-    }
+    if (c->d_state[0]) (void)hipFree(c->d_state[0]);
+    if (c->d_face[0]) (void)hipFree(c->d_face[0]);
+    if (c->d_idx[0]) (void)hipFree(c->d_idx[0]);
+    c->d_state[0] = c->d_state[1] = c->d_redlist = nullptr;
+    c->d_face[0] = c->d_face[1] = nullptr;
+    c->d_idx[0] = c->d_idx[1] = nullptr;
     c->state_cap = 0;
 }
 
@@ -462,17 +502,19 @@ hipError_t alloc_tile_buffers(mc_lya_ctx *c, uint64_t packets)
 {
     uint64_t cap = std::max<uint64_t>(1, packets);
     for (;;) {
-        hipError_t e = hipSuccess;
-        for (int i = 0; i < 2 && e == hipSuccess; ++i) {
-            if ((e = dalloc(&c->d_state[i], cap)) == hipSuccess && (e = dalloc(&c->d_face[i], cap)) == hipSuccess)
-                e = dalloc(&c->d_idx[i], cap);
-        }
+        hipError_t e = dalloc(&c->d_state[0], 3 * cap);
+        if (e == hipSuccess) e = dalloc(&c->d_face[0], 2 * cap);
+        if (e == hipSuccess) e = dalloc(&c->d_idx[0], 2 * cap);
         if (e == hipSuccess) break;
         free_tile_buffers(c);
         (void)hipGetLastError();
         if (e != hipErrorOutOfMemory || cap <= kMinTiledBatch) return e;
         cap = std::max(kMinTiledBatch, cap / 2);               // smaller batches
     }
+    c->d_state[1] = c->d_state[0] + cap;
+    c->d_redlist = c->d_state[0] + 2 * cap;
+    c->d_face[1] = c->d_face[0] + cap;
+    c->d_idx[1] = c->d_idx[0] + cap;
     c->state_cap = cap;
     return hipSuccess;
 }
@@ -533,6 +575,9 @@ TileParams tile_params(mc_lya_ctx *c, uint64_t first, uint64_t n)
     p.defer_min = 2048;
     p.tail_min = tail_packets(c, n);
     p.tail_gen = c->d_gen + kTailGenSlot;
+    p.red = c->d_redbox;
+    p.red_state = c->d_redlist;
+    p.red_count = c->d_gen + kRedCountSlot;
     p.first = first;
     p.count = n;
     return p;
@@ -593,6 +638,8 @@ mc_lya_status enqueue_tail(mc_lya_ctx *c, uint64_t n, bool timed)
     t.prefix = c->d_tail_prefix;
     t.ntiles = (int)c->tiles.size();
     t.max_cross = (uint32_t)c->max_cross;
+    t.red = c->d_redbox;
+    t.red_state = c->d_redlist;
     hipEvent_t e1 = nullptr;
     if (timed) {
         mc_lya_status st = timed_begin(c, &e1);
@@ -600,6 +647,27 @@ mc_lya_status enqueue_tail(mc_lya_ctx *c, uint64_t n, bool timed)
     }
     HIP_TRY(c, launch_tail_walk(t, capacity, c->vel, c->voigt, c->stream));
     if (timed) return timed_end(c, e1);
+    return MC_LYA_OK;
+}
+
+// The red list of the current batch, after its generations and tail walk. It
+// is not a walk launch of its own: with timing 1 its time goes to the launch
+// before it, whose end is recorded again behind it.
+mc_lya_status enqueue_red_list(mc_lya_ctx *c, uint64_t n, bool timed)
+{
+    RedParams p;
+    std::memset(&p, 0, sizeof p);
+    p.boxes = c->d_walk;
+    p.red = c->d_redbox;
+    p.n_boxes = c->n_boxes;
+    p.max_cross = (uint32_t)c->max_cross;
+    p.rec = c->d_rec;
+    p.tot = c->d_tot;
+    p.state = c->d_redlist;
+    p.counters = c->d_gen;
+    const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((n + 1023) / 1024, (uint64_t)c->num_cu * 8));
+    HIP_TRY(c, launch_red_list(p, grid, c->vel, c->voigt, c->stream));
+    if (timed && c->timing == 1 && c->events_used) return timed_end(c, c->events[c->events_used - 1].second);
     return MC_LYA_OK;
 }
 
@@ -616,6 +684,7 @@ mc_lya_status exits_after(mc_lya_ctx *c, int gen, unsigned long long *exits)
 // the exit count after each round, until no packet is left crossing.
 mc_lya_status drain_generations(mc_lya_ctx *c, TileParams &p, int gen, int *end = nullptr)
 {
+    const int first = gen;
     for (;;) {
         unsigned long long exits = 0;
         mc_lya_status st = exits_after(c, gen, &exits);
@@ -626,6 +695,8 @@ mc_lya_status drain_generations(mc_lya_ctx *c, TileParams &p, int gen, int *end 
         }
         if (gen >= kMaxGenerations) return fail(c, MC_LYA_EDEVICE, "tiled walk did not drain");
         const int g1 = std::min(gen + kGenRound, kMaxGenerations);
+        // (the red list has been counted once: these generations add to it)
+        if (gen == first) HIP_TRY(c, launch_red_mark(c->d_gen, c->stream));
         st = enqueue_generations(c, p, gen, g1, true);
         if (st != MC_LYA_OK) return st;
         gen = g1;
@@ -652,8 +723,10 @@ mc_lya_status walk_tiled(mc_lya_ctx *c, uint64_t first, uint64_t count)
         // generation stopped in it), so it needs no host round trip
         mc_lya_status st = enqueue_generations(c, p, 0, g1, true);
         if (st == MC_LYA_OK) st = enqueue_tail(c, n, true);
+        if (st == MC_LYA_OK) st = enqueue_red_list(c, n, true);
         if (st == MC_LYA_OK) st = drain_generations(c, p, g1, &end);
         if (st == MC_LYA_OK && end > g1) st = enqueue_tail(c, n, true);
+        if (st == MC_LYA_OK && end > g1) st = enqueue_red_list(c, n, true);
         if (st != MC_LYA_OK) return st;
         // the last generation that still handed packets on
         std::vector<unsigned long long> cnt(2 * (size_t)end);
@@ -733,6 +806,7 @@ mc_lya_status plan_walk(mc_lya_ctx *c, uint64_t first, uint64_t count, WalkPlan 
     p.rec = c->d_rec;
     p.A = c->d_A;
     p.tot = c->d_tot;
+    p.red = c->d_redbox;
     p.queue = c->d_queue;
     p.first = first;
     p.count = count;
@@ -855,6 +929,7 @@ mc_lya_status transport_graph(mc_lya_ctx *c, WalkPlan &w)
             e = launch_zero_counters(c->d_gen, kGenCounters, c->stream);
             if (e == hipSuccess && enqueue_generations(c, tp, 0, budget, false) != MC_LYA_OK) e = hipErrorUnknown;
             if (e == hipSuccess && enqueue_tail(c, c->total_packets, false) != MC_LYA_OK) e = hipErrorUnknown;
+            if (e == hipSuccess && enqueue_red_list(c, c->total_packets, false) != MC_LYA_OK) e = hipErrorUnknown;
         }
         c->generations = gens;
         if (forked && join_beside(c) != MC_LYA_OK) e = hipErrorUnknown;
@@ -889,6 +964,7 @@ mc_lya_status transport_graph(mc_lya_ctx *c, WalkPlan &w)
         st = drain_generations(c, tp, budget, &end);
         // generations beyond the budget ran eagerly: their tail walk too
         if (st == MC_LYA_OK && end > budget) st = enqueue_tail(c, c->total_packets, true);
+        if (st == MC_LYA_OK && end > budget) st = enqueue_red_list(c, c->total_packets, true);
         if (st != MC_LYA_OK) return st;
         // ran out of captured generations: the next capture takes what this
         // emission needed plus one round of slack (empty generations return
@@ -1014,6 +1090,7 @@ mc_lya_status mc_lya_init(mc_lya_ctx **out, const mc_lya_box_desc *boxes, int32_
     c->walked.assign(n_boxes, 0);
     c->walked_tiled.assign(n_boxes, 0);
     c->ph.resize(n_boxes);
+    c->redbox.resize(n_boxes);
     uint64_t off = 0;
     int max_blk = 1;
     for (int b = 0; b < n_boxes; ++b) {
@@ -1061,6 +1138,7 @@ mc_lya_status mc_lya_init(mc_lya_ctx **out, const mc_lya_box_desc *boxes, int32_
     hipError_t e = hipSuccess;
     if ((e = dalloc(&c->d_pack, n_boxes)) != hipSuccess || (e = dalloc(&c->d_walk, n_boxes)) != hipSuccess ||
         (e = dalloc(&c->d_red, n_boxes)) != hipSuccess || (e = dalloc(&c->d_tot, n_boxes)) != hipSuccess ||
+        (e = dalloc(&c->d_redbox, n_boxes)) != hipSuccess ||
         (e = hipMalloc(&c->d_rec, cells * (c->vel ? sizeof(float4) : sizeof(float)))) != hipSuccess ||
         (e = dalloc(&c->d_wgt, cells)) != hipSuccess || (e = dalloc(&c->d_part, nbk * kPartStride)) != hipSuccess ||
         (e = dalloc(&c->d_q, cells)) != hipSuccess || (e = dalloc(&c->d_bsum, nbk)) != hipSuccess ||
@@ -1139,6 +1217,7 @@ mc_lya_status mc_lya_emit(mc_lya_ctx *c, const uint64_t *seeds, const uint64_t *
     c->total_packets = ntot;
     const int nb = c->n_boxes;
     HIP_TRY(c, hipMemcpyAsync(c->d_walk, c->walk.data(), sizeof(WalkBox) * nb, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(c->d_redbox, c->redbox.data(), sizeof(RedBox) * nb, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, launch_quantize(c->d_pack, nb, c->max_blk, c->d_wgt, c->d_red, c->d_q, c->d_bsum, c->stream));
     HIP_TRY(c, launch_scan_blocks(c->d_pack, nb, c->max_blk, c->d_bsum, c->d_red, c->stream));
     HIP_TRY(c, launch_allocate(c->d_pack, c->d_walk, nb, c->max_blk, c->d_q, c->d_bsum, c->d_red, c->d_npk,

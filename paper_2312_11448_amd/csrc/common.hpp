@@ -51,9 +51,22 @@ struct BoxRed {
     unsigned long long wmax_bits;   // max emission weight (bit pattern of a double >= 0)
     unsigned long long udev_bits;   // max |U_c - <U>| (bit pattern of a double >= 0)
     uint32_t flags;       // validation failures (bit mask)
-    uint32_t pad;
+    float kappa_max;      // largest kappa_c
     uint64_t qtot;        // sum of the quantised weights
 };
+
+// Per-box constants of the deposit-free end of an escaping packet's walk
+// (red_core.hpp): a later deposit is at most w (cg exp(-xup^2) + cv / xup^2),
+// xup the largest frequency still to come.
+enum : int32_t { kRedOff = 0, kRedStill = 1, kRedFlow = 2 };   // not used, no flow, flow
+struct alignas(32) RedBox {
+    float cg, cv;
+    float ub[3];          // <U>
+    float udev;           // max |U_c - <U>|, rounded up
+    float round;          // bound on the binary32 roundings of x at one face
+    int32_t mode;
+};
+static_assert(sizeof(RedBox) == 32, "RedBox layout");
 
 // Per-box running totals of the walk (device, int64).
 struct BoxTot {
@@ -111,7 +124,7 @@ constexpr int kSetupBlock = 256;
 // sum (uint64 bits), [7] sum of Delta and [8] of Delta^2 (pack). Reduced per
 // box by one-block kernels; no same-address atomics, which serialise at the
 // cache.
-constexpr int kPartStride = 10;
+constexpr int kPartStride = 10;   // ([9]: the block's largest kappa)
 
 hipError_t launch_pack(const PackBox *pb_dev, int n_boxes, int max_blk, bool vel_rec, void *rec,
                        double *wgt, double *partials, BoxRed *red, hipStream_t s);
@@ -140,6 +153,7 @@ struct WalkParams {
     const uint32_t *cell_of_packet;
     unsigned long long *A;   // per-cell absorbed weight
     BoxTot *tot;
+    const RedBox *red;
     unsigned long long *queue;   // work counters, one per part of the range (persistent kernel)
     uint64_t first, count;   // global packet range
     int64_t max_cross;
@@ -235,6 +249,7 @@ struct alignas(64) PState {
     uint32_t w;
     uint32_t ncross;
     uint32_t pos;            // its cell in the tile that takes it up: x + 16 y + 256 z
+                             // (in the red list: its global cell)
 };
 static_assert(sizeof(PState) == 64, "PState layout");
 
@@ -251,9 +266,11 @@ struct TileExits {
 constexpr int kMaxGenerations = 4096;  // per transport batch (packets cross at most one tile per generation)
 // Counters of a batch: per generation (bump allocator, exits), then the tail
 // hand-off: the generation that found fewer than tail_min packets in flight
-// (0 = none) and the number of packets handed to the tail walk.
-constexpr int kGenCounters = 2 * kMaxGenerations + 2;
+// (0 = none) and the number of packets handed to the tail walk; then the red
+// list: the packets written to it and those already counted to their end.
+constexpr int kGenCounters = 2 * kMaxGenerations + 4;
 constexpr int kTailGenSlot = 2 * kMaxGenerations, kTailCountSlot = 2 * kMaxGenerations + 1;
+constexpr int kRedCountSlot = 2 * kMaxGenerations + 2, kRedDoneSlot = 2 * kMaxGenerations + 3;
 
 struct TileParams {
     const WalkBox *boxes;
@@ -283,6 +300,9 @@ struct TileParams {
     int32_t gen;             // index of this generation in the batch
     uint64_t tail_min;       // fewer packets in flight than this: stop and leave them to the tail walk
     unsigned long long *tail_gen;   // where the first generation that stops records its index
+    const RedBox *red;
+    PState *red_state;       // packets with no deposit left to make (one slot per packet of the batch)
+    unsigned long long *red_count;
 };
 
 // The tail walk: the packets the last full generation handed on, walked to
@@ -301,12 +321,30 @@ struct TailParams {
     uint32_t *prefix;        // [ntiles] first tail packet of each tile
     int32_t ntiles;
     uint32_t max_cross;
+    const RedBox *red;
+    PState *red_state;
+};
+
+// The red list: packets with no deposit left to make, counted to their end.
+struct RedParams {
+    const WalkBox *boxes;
+    const RedBox *red;
+    int32_t n_boxes;
+    uint32_t max_cross;
+    const void *rec;
+    BoxTot *tot;
+    const PState *state;
+    unsigned long long *counters;   // the batch counters (kRedCountSlot, kRedDoneSlot)
 };
 
 hipError_t launch_tile_generation(const TileParams &p, bool gen0, bool vel, bool voigt, hipStream_t s);
 // The tail walk of a batch (no-op when no generation stopped); `capacity`
 // bounds the packets it can take (tail_min).
 hipError_t launch_tail_walk(const TailParams &p, uint64_t capacity, bool vel, bool voigt, hipStream_t s);
+// Counts the packets of the red list that are not yet done; launch_red_mark
+// makes the list as it stands done (before more packets are added to it).
+hipError_t launch_red_list(const RedParams &p, int grid, bool vel, bool voigt, hipStream_t s);
+hipError_t launch_red_mark(unsigned long long *counters, hipStream_t s);
 hipError_t launch_zero_counters(unsigned long long *c, int n, hipStream_t s);
 
 hipError_t launch_walk_simple(const WalkParams &p, int block, hipStream_t s);

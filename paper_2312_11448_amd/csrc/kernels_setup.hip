@@ -156,6 +156,7 @@ __global__ __launch_bounds__(B) void pack_kernel(const PackBox *__restrict__ pbs
     const double sd1 = block_sum(d1, lds);
     const double sd2 = block_sum(d2, lds);
     const double wm = block_max(w, lds);
+    const double km = block_max(ks, lds);
     // validation failures are rare: an atomic only where one is found
     const uint32_t fl = wave_or(flags);
     if ((threadIdx.x & 63) == 0 && fl) atomicOr(&red[b].flags, fl);
@@ -168,6 +169,7 @@ __global__ __launch_bounds__(B) void pack_kernel(const PackBox *__restrict__ pbs
         p[4] = wm;
         p[7] = sd1;
         p[8] = sd2;
+        p[9] = km;
     }
 }
 
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(B) void box_reduce_kernel(const PackBox *__restrict
     const int b = blockIdx.x;
     const int nblk = pbs[b].nblk;
     double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    double wm = 0.0;
+    double wm = 0.0, km = 0.0;
     for (int k = threadIdx.x; k < nblk; k += B) {
         const double *p = partials + ((size_t)b * max_blk + k) * kPartStride;
 #pragma unroll
@@ -188,11 +190,13 @@ __global__ __launch_bounds__(B) void box_reduce_kernel(const PackBox *__restrict
         acc[4] += p[7];
         acc[5] += p[8];
         wm = fmax(wm, p[4]);
+        km = fmax(km, p[9]);
     }
     double tot[6];
 #pragma unroll
     for (int j = 0; j < 6; ++j) tot[j] = block_sum(acc[j], lds);
     wm = block_max(wm, lds);
+    km = block_max(km, lds);
     if (threadIdx.x == 0) {
         red[b].usum[0] = tot[0];
         red[b].usum[1] = tot[1];
@@ -200,6 +204,7 @@ __global__ __launch_bounds__(B) void box_reduce_kernel(const PackBox *__restrict
         red[b].kappa_sum = tot[3];
         red[b].od_sum = tot[4];
         red[b].od2_sum = tot[5];
+        red[b].kappa_max = (float)km;
         red[b].wmax_bits = (unsigned long long)__double_as_longlong(wm);
     }
 }

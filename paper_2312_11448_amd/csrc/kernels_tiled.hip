@@ -12,6 +12,10 @@
 // indexed by face; in the next generation each tile pulls exactly the face
 // lists that point at it and applies the face jump.
 //
+// A packet that has no deposit left to make when it leaves a tile goes to the
+// red list instead, and is counted to its escape without further tiles
+// (red_core.hpp).
+//
 // Once a tile's input is used up, its waves thin out as packets finish; a
 // wave left with only a few live lanes writes them to the tile's own
 // deferred list instead, and the next generation takes them up again with
@@ -20,7 +24,7 @@
 //
 // The per-packet arithmetic is walk_core's, so the integer tallies are the
 // same bits as those of the other drivers.
-#include "walk_core.hpp"
+#include "red_core.hpp"
 
 namespace mclya {
 namespace {
@@ -65,6 +69,7 @@ struct TileCtx {
     Line ln;
     int32_t ox, oy, oz, sx, sy, sz;
     uint32_t span;
+    RedBox red;
 };
 
 // A packet inside a tile. Ray geometry and line state are a Lane's; the cell
@@ -273,7 +278,8 @@ __device__ __forceinline__ uint32_t pack_pos(int32_t ix, int32_t iy, int32_t iz)
 }
 
 // The state with the face distances (tx, ty, tz) and the cell at offsets pos.
-__device__ __forceinline__ void save_state(PState *out, const TLane &L, double tx, double ty, double tz, uint32_t pos)
+template <class L_>
+__device__ __forceinline__ void save_state(PState *out, const L_ &L, double tx, double ty, double tz, uint32_t pos)
 {
     PState o;
     o.tm[0] = tx;
@@ -290,12 +296,14 @@ __device__ __forceinline__ void save_state(PState *out, const TLane &L, double t
     *out = o;
 }
 
-// A packet standing on the tile's edge, written for the neighbouring tile:
-// the face crossing that tile_step left undone is left to the tile that takes
-// the packet up (load_state); the next cell is the one behind that face, with
-// the box's periodic wrap. Returns the face it leaves through.
+// A packet standing on the tile's edge, written out: the face crossing that
+// tile_step left undone is left to whoever takes the packet up (load_state);
+// the next cell is the one behind that face, with the box's periodic wrap,
+// named by its offsets in the neighbouring tile, or (red list) globally.
+// Returns the face it leaves through.
 template <int RS>
-__device__ __forceinline__ uint32_t save_exit(PState *out, const TLane &L, const TileCtx &C, const WalkBox &B)
+__device__ __forceinline__ uint32_t save_exit(PState *out, const TLane &L, const TileCtx &C, const WalkBox &B,
+                                              bool red)
 {
     const Face f = next_face(L.tmx, L.tmy, L.tmz);
     int32_t lx, ly, lz;
@@ -307,7 +315,9 @@ __device__ __forceinline__ uint32_t save_exit(PState *out, const TLane &L, const
     int32_t mi = ci + (up ? 1 : -1);
     mi = mi == ni ? 0 : mi;
     mi = mi < 0 ? ni - 1 : mi;
-    save_state(out, L, L.tmx, L.tmy, L.tmz, pack_pos(f.bx ? mi : ix, f.by ? mi : iy, f.bz ? mi : iz));
+    const int32_t jx = f.bx ? mi : ix, jy = f.by ? mi : iy, jz = f.bz ? mi : iz;
+    const uint32_t cell = B.cell_off + (uint32_t)jx + (uint32_t)B.nx * ((uint32_t)jy + (uint32_t)B.ny * (uint32_t)jz);
+    save_state(out, L, L.tmx, L.tmy, L.tmz, red ? cell : pack_pos(jx, jy, jz));
     return (f.bx ? 0u : (f.by ? 2u : 4u)) + (up ? 1u : 0u);
 }
 
@@ -316,14 +326,12 @@ __device__ __forceinline__ uint32_t save_exit(PState *out, const TLane &L, const
 // crossing the next face is td past the path length walked, and storing that
 // length there puts it back on the face (of two such axes either serves: both
 // were crossed at the same length, and both advance to the same distance).
-template <int RS>
-__device__ __forceinline__ void save_here(PState *out, const TLane &L)
+template <class L_>
+__device__ __forceinline__ void save_here(PState *out, const L_ &L, uint32_t pos)
 {
-    int32_t lx, ly, lz;
-    slot_cell((int32_t)((uint32_t)L.q / (uint32_t)RS), lx, ly, lz);
     const bool bx = L.tdx < kFar && L.tmx == L.t + L.tdx;
     const bool by = !bx && L.tdy < kFar && L.tmy == L.t + L.tdy;
-    save_state(out, L, bx ? L.t : L.tmx, by ? L.t : L.tmy, !bx && !by ? L.t : L.tmz, pack_pos(lx, ly, lz));
+    save_state(out, L, bx ? L.t : L.tmx, by ? L.t : L.tmy, !bx && !by ? L.t : L.tmz, pos);
 }
 
 __device__ __forceinline__ uint32_t rank_in(uint64_t mask)
@@ -339,36 +347,6 @@ __device__ __forceinline__ T wave_sum(T v)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     return v;
-}
-
-// The packet of a hand-over state, its face crossed (all but its cell's
-// record and global index).
-__device__ __forceinline__ void load_state(Lane &L, const PState &o, const WalkBox &B)
-{
-    const double kz = (double)o.kz;
-    L.tdx = o.kx != 0.0 ? 1.0 / fabs(o.kx) : kFar;
-    L.tdy = o.ky != 0.0 ? 1.0 / fabs(o.ky) : kFar;
-    L.tdz = kz != 0.0 ? 1.0 / fabs(kz) : kFar;
-    const Face f = next_face(o.tm[0], o.tm[1], o.tm[2]);
-    L.t = f.tn;
-    L.tmx = f.bx ? o.tm[0] + L.tdx : o.tm[0];
-    L.tmy = f.by ? o.tm[1] + L.tdy : o.tm[1];
-    L.tmz = f.bz ? o.tm[2] + L.tdz : o.tm[2];
-    L.kxd = o.kx;
-    L.kyd = o.ky;
-    L.kx = (float)o.kx;
-    L.ky = (float)o.ky;
-    L.kz = o.kz;
-    L.w = o.w;
-    L.x = o.x;
-    L.ku = o.ku;
-    L.ncross = o.ncross;
-    L.nx = B.nx;
-    L.ny = B.ny;
-    L.nz = B.nz;
-    L.coff = B.cell_off;
-    L.delta = B.delta;
-    L.xeff = B.x_eff;
 }
 
 // The tile's totals in LDS, in the order of the box totals they add to.
@@ -388,7 +366,7 @@ template <bool VEL, bool GEN0, bool VOIGT, bool WRAP>
 __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &ti, const WalkBox &B,
                                           const TileCtx &C, uint32_t n_in, const uint32_t *pre, const uint32_t *lst,
                                           const char *recs, unsigned long long *tally, uint32_t *s_next,
-                                          uint32_t *s_exit, uint32_t s_base, uint32_t *s_fcnt,
+                                          uint32_t *s_exit, uint32_t *s_red_n, uint32_t s_base, uint32_t *s_fcnt,
                                           unsigned long long *s_tot, TileAcc &acc)
 {
     constexpr int RS = VEL ? 16 : 4;
@@ -407,10 +385,17 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
         const bool parked = !alive && L.w != 0u;
         if (__ballot(parked)) {
             if (parked) {
-                const uint32_t g = s_base + atomicAdd(s_exit, 1u);
-                const uint32_t f = save_exit<RS>(&P.out_state[g], L, C, B);
-                P.out_face[g] = (uint8_t)f;
-                atomicAdd(&s_fcnt[f], 1u);
+                // the tile's n_in slots: exits fill them from the front,
+                // packets for the red list from the back
+                const bool red = red_only(C.red, L.x, L.ku, L.kx, L.ky, L.kz, L.w);
+                uint32_t g;
+                if (red) g = s_base + n_in - 1u - atomicAdd(s_red_n, 1u);
+                else g = s_base + atomicAdd(s_exit, 1u);
+                const uint32_t f = save_exit<RS>(&P.out_state[g], L, C, B, red);
+                if (!red) {
+                    P.out_face[g] = (uint8_t)f;
+                    atomicAdd(&s_fcnt[f], 1u);
+                }
                 L.w = 0u;
             }
         }
@@ -516,7 +501,9 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
                 flush_exits();
                 if (alive) {
                     const uint32_t g = s_base + atomicAdd(s_exit, 1u);
-                    save_here<RS>(&P.out_state[g], L);
+                    int32_t lx, ly, lz;
+                    slot_cell((int32_t)((uint32_t)L.q / (uint32_t)RS), lx, ly, lz);
+                    save_here(&P.out_state[g], L, pack_pos(lx, ly, lz));
                     P.out_face[g] = (uint8_t)kDeferred;
                     atomicAdd(&s_fcnt[kDeferred], 1u);
                 }
@@ -585,7 +572,8 @@ __global__ __launch_bounds__(BLK) void tile_walk_kernel(TileParams P)
     __shared__ uint32_t pre[GEN0 ? TC + 1 : 8];   // GEN0: cell prefix of packet counts; else list prefix
     __shared__ uint32_t lst[8];                    // pull: first index of each source list
     __shared__ uint32_t s_tsum[kWaves];
-    __shared__ uint32_t s_next, s_exit, s_total, s_base;
+    __shared__ uint32_t s_next, s_exit, s_red_n, s_total, s_base;
+    __shared__ unsigned long long s_red_at;        // the tile's place in the red list
     __shared__ uint32_t s_fcnt[8], s_fcur[8];
     __shared__ unsigned long long s_red[kWaves];   // crossings of each wave
     __shared__ unsigned long long s_tot[5];        // escaped weight, -, capped packets and weight, wing
@@ -698,6 +686,7 @@ __global__ __launch_bounds__(BLK) void tile_walk_kernel(TileParams P)
     if (tid == 0) {
         s_next = 0;
         s_exit = 0;
+        s_red_n = 0;
         s_base = (uint32_t)atomicAdd(P.bump, (unsigned long long)n_in);
     }
     if (tid < 8) s_fcnt[tid] = 0;
@@ -717,14 +706,15 @@ __global__ __launch_bounds__(BLK) void tile_walk_kernel(TileParams P)
     C.sy = ti.sy;
     C.sz = ti.sz;
     C.span = ti.span;
+    C.red = P.red[ti.box];
     const char *recs = VEL ? reinterpret_cast<const char *>(srec4) : reinterpret_cast<const char *>(sreck);
     TileAcc acc{0};
     // a tile that spans the box along some axis wraps round inside itself
     if (ti.span)
-        walk_tile<VEL, GEN0, VOIGT, true>(P, ti, B, C, n_in, pre, lst, recs, tally, &s_next, &s_exit, s_base, s_fcnt,
+        walk_tile<VEL, GEN0, VOIGT, true>(P, ti, B, C, n_in, pre, lst, recs, tally, &s_next, &s_exit, &s_red_n, s_base, s_fcnt,
                                           s_tot, acc);
     else
-        walk_tile<VEL, GEN0, VOIGT, false>(P, ti, B, C, n_in, pre, lst, recs, tally, &s_next, &s_exit, s_base, s_fcnt,
+        walk_tile<VEL, GEN0, VOIGT, false>(P, ti, B, C, n_in, pre, lst, recs, tally, &s_next, &s_exit, &s_red_n, s_base, s_fcnt,
                                            s_tot, acc);
 
     // ---- finish: tally, totals, face lists of the exits ----------------------
@@ -767,8 +757,9 @@ __global__ __launch_bounds__(BLK) void tile_walk_kernel(TileParams P)
             atomicAdd(dst, t);
         }
     }
-    const uint32_t n_exit = s_exit;
+    const uint32_t n_exit = s_exit, n_red = s_red_n;
     if (tid == 0) {
+        if (n_red) s_red_at = atomicAdd(P.red_count, (unsigned long long)n_red);
         TileExits e;
         e.base = s_base;
         uint32_t run = 0;
@@ -782,6 +773,14 @@ __global__ __launch_bounds__(BLK) void tile_walk_kernel(TileParams P)
         if (n_exit) atomicAdd(P.exits, (unsigned long long)n_exit);
     }
     __syncthreads();
+    // packets without deposits left: the back of the tile's slots, copied to
+    // the red list (their slots are taken up again two generations on)
+    {
+        const float4 *from = reinterpret_cast<const float4 *>(P.out_state + (s_base + n_in - n_red));
+        float4 *to = reinterpret_cast<float4 *>(P.red_state + s_red_at);
+        constexpr uint32_t kQuads = sizeof(PState) / sizeof(float4);
+        for (uint32_t k = tid; k < kQuads * n_red; k += BLK) to[k] = from[k];
+    }
     // the face lists: four exits per thread at a time, their faces read first
     constexpr int kIdxBatch = 4;
     for (uint32_t k0 = tid; k0 < n_exit; k0 += kIdxBatch * BLK) {
@@ -883,9 +882,15 @@ __global__ __launch_bounds__(256) void tail_walk_kernel(TailParams P)
         const Line ln = line_of(B);
         uint64_t dep = 0;
         uint32_t wing = 0;
+        const RedBox R = P.red[box];
         int fate;
         do {
             fate = walk_step<VEL, VOIGT>(L, P.rec, GlobalSink{P.A}, P.max_cross, dep, ln, wing);
+            if (fate == kAlive && red_only(R, L.x, L.ku, L.kx, L.ky, L.kz, L.w)) {
+                // no deposit left: to the red list (it has room for every packet of the batch)
+                save_here(&P.red_state[atomicAdd(&P.counters[kRedCountSlot], 1ull)], L, L.c);
+                break;
+            }
         } while (fate == kAlive);
         cross = L.ncross - cross0;                 // the generations counted theirs
         esc = fate == kEscaped ? L.w : 0;

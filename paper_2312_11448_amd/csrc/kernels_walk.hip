@@ -27,13 +27,6 @@ __device__ __forceinline__ uint32_t rank_in(uint64_t mask)
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 __device__ __forceinline__ uint64_t bcast_u64(uint64_t v, int src)
 {
     return __shfl(v, src, 64);
@@ -45,47 +38,6 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v)
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
     return ((uint64_t)hi << 32) | lo;
-}
-
-// Per-lane per-box totals, flushed with one atomic per box per wave.
-struct Acc {
-    int32_t box;
-    uint64_t esc, cross, capn, capw, wing;
-};
-
-// Convergent: every lane of the wave must call it. Lanes with `give` add
-// their totals to their box; the wave issues one atomic per distinct box.
-__device__ __forceinline__ void flush(Acc &a, bool give, BoxTot *__restrict__ tot)
-{
-    uint64_t pending = __ballot(give && a.box >= 0);
-    while (pending) {
-        const int leader = __ffsll((unsigned long long)pending) - 1;
-        const int b = __shfl(a.box, leader, 64);
-        const bool mine = give && a.box == b;
-        const uint64_t e = wave_sum_u64(mine ? a.esc : 0);
-        const uint64_t c = wave_sum_u64(mine ? a.cross : 0);
-        const uint64_t n = wave_sum_u64(mine ? a.capn : 0);
-        const uint64_t w = wave_sum_u64(mine ? a.capw : 0);
-        const uint64_t g = wave_sum_u64(mine ? a.wing : 0);
-        if ((int)lane_id() == leader) {
-            if (e) atomicAdd(&tot[b].escaped, (unsigned long long)e);
-            if (c) atomicAdd(&tot[b].crossings, (unsigned long long)c);
-            if (n) atomicAdd(&tot[b].capped_packets, (unsigned long long)n);
-            if (w) atomicAdd(&tot[b].capped_weight, (unsigned long long)w);
-            if (g) atomicAdd(&tot[b].wing, (unsigned long long)g);
-        }
-        pending &= ~__ballot(mine);
-    }
-    if (give) a.esc = a.cross = a.capn = a.capw = a.wing = 0;
-}
-
-__device__ __forceinline__ void account(Acc &a, const Lane &L, int fate, uint32_t wing)
-{
-    a.cross += L.ncross;
-    a.esc += fate == kEscaped ? L.w : 0;
-    a.capn += fate == kCapped ? 1 : 0;
-    a.capw += fate == kCapped ? L.w : 0;
-    a.wing += wing;
 }
 
 // Box of a global packet id (boxes sorted by packet offset).

@@ -482,4 +482,82 @@ __device__ __forceinline__ int walk_step(Lane &L, const void *__restrict__ rec, 
     return fate;
 }
 
+// The packet of a hand-over state, its face crossed (all but its cell's
+// record and global index).
+__device__ __forceinline__ void load_state(Lane &L, const PState &o, const WalkBox &B)
+{
+    const double kz = (double)o.kz;
+    L.tdx = o.kx != 0.0 ? 1.0 / fabs(o.kx) : kFar;
+    L.tdy = o.ky != 0.0 ? 1.0 / fabs(o.ky) : kFar;
+    L.tdz = kz != 0.0 ? 1.0 / fabs(kz) : kFar;
+    const Face f = next_face(o.tm[0], o.tm[1], o.tm[2]);
+    L.t = f.tn;
+    L.tmx = f.bx ? o.tm[0] + L.tdx : o.tm[0];
+    L.tmy = f.by ? o.tm[1] + L.tdy : o.tm[1];
+    L.tmz = f.bz ? o.tm[2] + L.tdz : o.tm[2];
+    L.kxd = o.kx;
+    L.kyd = o.ky;
+    L.kx = (float)o.kx;
+    L.ky = (float)o.ky;
+    L.kz = o.kz;
+    L.w = o.w;
+    L.x = o.x;
+    L.ku = o.ku;
+    L.ncross = o.ncross;
+    L.nx = B.nx;
+    L.ny = B.ny;
+    L.nz = B.nz;
+    L.coff = B.cell_off;
+    L.delta = B.delta;
+    L.xeff = B.x_eff;
+}
+
+__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// Per-lane per-box totals, flushed with one atomic per box per wave.
+struct Acc {
+    int32_t box;
+    uint64_t esc, cross, capn, capw, wing;
+};
+
+// Convergent: every lane of the wave must call it. Lanes with `give` add
+// their totals to their box; the wave issues one atomic per distinct box.
+__device__ __forceinline__ void flush(Acc &a, bool give, BoxTot *__restrict__ tot)
+{
+    uint64_t pending = __ballot(give && a.box >= 0);
+    while (pending) {
+        const int leader = __ffsll((unsigned long long)pending) - 1;
+        const int b = __shfl(a.box, leader, 64);
+        const bool mine = give && a.box == b;
+        const uint64_t e = wave_sum_u64(mine ? a.esc : 0);
+        const uint64_t c = wave_sum_u64(mine ? a.cross : 0);
+        const uint64_t n = wave_sum_u64(mine ? a.capn : 0);
+        const uint64_t w = wave_sum_u64(mine ? a.capw : 0);
+        const uint64_t g = wave_sum_u64(mine ? a.wing : 0);
+        if ((int)__lane_id() == leader) {
+            if (e) atomicAdd(&tot[b].escaped, (unsigned long long)e);
+            if (c) atomicAdd(&tot[b].crossings, (unsigned long long)c);
+            if (n) atomicAdd(&tot[b].capped_packets, (unsigned long long)n);
+            if (w) atomicAdd(&tot[b].capped_weight, (unsigned long long)w);
+            if (g) atomicAdd(&tot[b].wing, (unsigned long long)g);
+        }
+        pending &= ~__ballot(mine);
+    }
+    if (give) a.esc = a.cross = a.capn = a.capw = a.wing = 0;
+}
+
+__device__ __forceinline__ void account(Acc &a, const Lane &L, int fate, uint32_t wing)
+{
+    a.cross += L.ncross;
+    a.esc += fate == kEscaped ? L.w : 0;
+    a.capn += fate == kCapped ? 1 : 0;
+    a.capw += fate == kCapped ? L.w : 0;
+    a.wing += wing;
+}
+
 }  // namespace mclya

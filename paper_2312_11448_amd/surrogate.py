@@ -20,7 +20,7 @@ import numpy as np
 import torch
 
 # packets per tiled-walk batch that a context reserves hand-over state for
-# (138 bytes a packet): larger emissions walk in batches
+# (202 bytes a packet): larger emissions walk in batches
 BATCH = 1 << 28
 
 from .sim import Simulation
