@@ -147,6 +147,12 @@ struct mc_lya_ctx {
     PState *d_redlist = nullptr;             // [state_cap] packets with no deposit left to make
     uint64_t state_cap = 0;
     int64_t generations = 0;                 // generations launched by the last tiled transport
+    // a box alone in its context with fewer tiles than compute units: `share`
+    // workgroups walk each tile, each a share of its packets into a tally of its own
+    int share = 1;
+    unsigned long long *d_share = nullptr;   // their tallies, zero between walks
+    size_t share_cells = 0;
+    bool share_dirty = false;                // a walk that used them did not get to their sum
     std::vector<uint8_t> tiled;              // per box: walked by tiles (1) or by the persistent walk (0)
     std::vector<double> cpp;                 // per box: estimated crossings per packet (set by refresh)
     std::vector<uint64_t> seg_host;          // packet segments of the persistent part: starts, then ids
@@ -224,7 +230,7 @@ void free_all(mc_lya_ctx *c)
     if (c->join) (void)hipEventDestroy(c->join);
     c->side = nullptr;
     c->fork = c->join = nullptr;
-    void *ptrs[] = {c->d_pack, c->d_walk, c->d_red, c->d_tot, c->d_redbox, c->d_rec, c->d_wgt, c->d_part, c->d_q,
+    void *ptrs[] = {c->d_pack, c->d_walk, c->d_red, c->d_tot, c->d_redbox, c->d_share, c->d_rec, c->d_wgt, c->d_part, c->d_q,
                     c->d_bsum, c->d_npk, c->d_A, c->d_queue, c->d_boxabs, c->d_fsum, c->d_feed,
                     c->d_cop, c->d_pfirst, c->d_seg, c->d_featbox, c->d_tail_prefix, c->d_tiles, c->d_texits[0], c->d_texits[1], c->d_sbox, c->d_ev, c->d_ev_coef,
                     c->d_gen};
@@ -290,6 +296,7 @@ RedBox red_constants(double kmax, double delta, double x_eff, const double u[3],
     auto half_ulp = [](double v) { return std::ldexp(1.0, std::ilogb(std::max(v, 1e-30)) - 24); };
     const double round = 1.02 * (2.0 * half_ulp(x_eff) + half_ulp(2.0 * udev + 1e-6) + delta * 1.75 * 0x1p-24);
     r.round = (float)round;
+    r.binade = (float)std::ldexp(1.0, std::ilogb(std::max(x_eff, 1e-30)));
     const bool still = !vel || (udev == 0.0 && u[0] == 0.0 && u[1] == 0.0 && u[2] == 0.0);
     const double most = 1.7321 * 2.0 * (x_eff + udev) / delta + 4.0;
     const bool fine = std::isfinite(r.cg) && std::isfinite(r.cv) && std::isfinite(x_eff) && delta > 0.0;
@@ -429,9 +436,20 @@ void build_tiles(mc_lya_ctx *c)
                             ++t.nsrc;
                         }
                     }
+                    t.span |= (uint32_t)c->share << 8;
                     c->tiles.push_back(t);
                 }
     }
+    // the sharing workgroups' entries: the same tiles again, each handing its
+    // packets on among the entries of its own number
+    const int n = (int)c->tiles.size();
+    for (int r = 1; r < c->share; ++r)
+        for (int i = 0; i < n; ++i) {
+            TileInfo t = c->tiles[i];
+            t.span |= (uint32_t)r << 20;
+            for (int k = 0; k < t.nsrc; ++k) t.src_tile[k] += r * n;
+            c->tiles.push_back(t);
+        }
 }
 
 int tiles_of_box(const mc_lya_box_desc &d)
@@ -441,6 +459,27 @@ int tiles_of_box(const mc_lya_box_desc &d)
 
 constexpr int kMinTiles = 8;              // fewer tiles than this never pays
 constexpr int kAllTiled = 1000000;        // tile_share at or above this: every box is tiled
+
+// How many workgroups walk each of a lone box's nt tiles (1 with as many tiles
+// as compute units): as many as the chip holds at once, one per compute unit,
+// while each has kSharePackets packets to walk (128 to 1024 time alike).
+constexpr uint64_t kSharePackets = 512;
+// A lone box with fewer tiles than compute units is walked by (shared) tiles
+// from this many crossings as classify_boxes estimates them (42 a packet on
+// the 128^3 workload's fields, where they walk 87). The tiles take about 20 generations of
+// 35 us however few packets there are; the persistent walk takes as long as
+// its longest packet (0.3 to 0.5 ms) and then is bound by the device's 2.4e10
+// deposits/s. Transports, us (tiles, persistent): 48^3 with 1.1e5 packets 850,
+// 560 and with 4.4e5 960, 1200; 64^3 with 2.6e5 910, 930; 32^3 with 5.2e5
+// 1060, 1180 and with 2.1e6 1420, 4050; 64^3 with 1.7e7 4900, 31500.
+constexpr double kSharedWork = 1.2e7;
+int sharing(const mc_lya_ctx *c, int nt, uint64_t packets)
+{
+    const uint64_t per = packets / ((uint64_t)nt * kSharePackets);
+    const int most = std::min(c->num_cu / std::max(1, nt), 0xfff);
+    const int fits = (int)(c->share_cells / ((size_t)nt * kTileCells)) + 1;     // tallies reserved at init
+    return std::max(1, (int)std::min<uint64_t>(per, (uint64_t)std::min(most, fits)));
+}
 
 // Which boxes the tiled walk takes: those whose estimated work per tile is at
 // most tile_share % of one compute unit's fair share of the whole emission
@@ -464,9 +503,17 @@ mc_lya_status classify_boxes(mc_lya_ctx *c)
         else if (c->tile_share > 0)
             m[b] = nt >= kMinTiles && cost[b] / nt <= 0.01 * c->tile_share * fair ? 1 : 0;
     }
-    if (m == c->tiled) return MC_LYA_OK;
+    int share = 1;
+    if (nb == 1 && c->tile_share > 0) {
+        const int nt = tiles_of_box(c->desc[0]);
+        share = sharing(c, nt, c->walk[0].npkt);
+        if (cost[0] >= kSharedWork) m[0] = 1;
+        if (!m[0]) share = 1;
+    }
+    if (m == c->tiled && share == c->share) return MC_LYA_OK;
     HIP_TRY(c, hipStreamSynchronize(c->stream));      // the previous table may still be in flight
     c->tiled = m;
+    c->share = share;
     build_tiles(c);
     if (!c->tiles.empty())
         HIP_TRY(c, hipMemcpyAsync(c->d_tiles, c->tiles.data(), sizeof(TileInfo) * c->tiles.size(),
@@ -578,6 +625,7 @@ TileParams tile_params(mc_lya_ctx *c, uint64_t first, uint64_t n)
     p.red = c->d_redbox;
     p.red_state = c->d_redlist;
     p.red_count = c->d_gen + kRedCountSlot;
+    p.share_A = c->d_share;
     p.first = first;
     p.count = n;
     return p;
@@ -588,6 +636,7 @@ TileParams tile_params(mc_lya_ctx *c, uint64_t first, uint64_t n)
 // per launch (not while a graph is being captured).
 mc_lya_status enqueue_generations(mc_lya_ctx *c, TileParams &p, int g0, int g1, bool timed)
 {
+    if (c->share > 1) c->share_dirty = true;
     for (int gen = g0; gen < g1; ++gen) {
         const int cur = gen & 1, prev = cur ^ 1;
         p.in_state = c->d_state[prev];
@@ -650,10 +699,12 @@ mc_lya_status enqueue_tail(mc_lya_ctx *c, uint64_t n, bool timed)
     return MC_LYA_OK;
 }
 
-// The red list of the current batch, after its generations and tail walk. It
-// is not a walk launch of its own: with timing 1 its time goes to the launch
-// before it, whose end is recorded again behind it.
-mc_lya_status enqueue_red_list(mc_lya_ctx *c, uint64_t n, bool timed)
+// The red list of the current batch, after its tail walk and before
+// generation `gen` (if it comes to that), and the sum of the tallies of
+// workgroups that shared a tile. It is not a walk launch of its own: with
+// timing 1 its time goes to the launch before it, whose end is recorded again
+// behind it.
+mc_lya_status enqueue_red_list(mc_lya_ctx *c, uint64_t n, int gen, bool timed)
 {
     RedParams p;
     std::memset(&p, 0, sizeof p);
@@ -664,9 +715,17 @@ mc_lya_status enqueue_red_list(mc_lya_ctx *c, uint64_t n, bool timed)
     p.rec = c->d_rec;
     p.tot = c->d_tot;
     p.state = c->d_redlist;
+    // (generation `gen`, if there is one, writes this index buffer; until
+    // then it is free)
+    p.unsure = c->d_idx[gen & 1];
     p.counters = c->d_gen;
-    const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((n + 1023) / 1024, (uint64_t)c->num_cu * 8));
+    const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((n + 255) / 256, (uint64_t)c->num_cu * 8));
     HIP_TRY(c, launch_red_list(p, grid, c->vel, c->voigt, c->stream));
+    if (c->share > 1) {
+        HIP_TRY(c, launch_share_sum(c->d_tiles, c->d_walk, (int)c->tiles.size() / c->share, c->share, c->d_A,
+                                    c->d_share, c->stream));
+        c->share_dirty = false;
+    }
     if (timed && c->timing == 1 && c->events_used) return timed_end(c, c->events[c->events_used - 1].second);
     return MC_LYA_OK;
 }
@@ -723,10 +782,10 @@ mc_lya_status walk_tiled(mc_lya_ctx *c, uint64_t first, uint64_t count)
         // generation stopped in it), so it needs no host round trip
         mc_lya_status st = enqueue_generations(c, p, 0, g1, true);
         if (st == MC_LYA_OK) st = enqueue_tail(c, n, true);
-        if (st == MC_LYA_OK) st = enqueue_red_list(c, n, true);
+        if (st == MC_LYA_OK) st = enqueue_red_list(c, n, g1, true);
         if (st == MC_LYA_OK) st = drain_generations(c, p, g1, &end);
         if (st == MC_LYA_OK && end > g1) st = enqueue_tail(c, n, true);
-        if (st == MC_LYA_OK && end > g1) st = enqueue_red_list(c, n, true);
+        if (st == MC_LYA_OK && end > g1) st = enqueue_red_list(c, n, end, true);
         if (st != MC_LYA_OK) return st;
         // the last generation that still handed packets on
         std::vector<unsigned long long> cnt(2 * (size_t)end);
@@ -929,7 +988,7 @@ mc_lya_status transport_graph(mc_lya_ctx *c, WalkPlan &w)
             e = launch_zero_counters(c->d_gen, kGenCounters, c->stream);
             if (e == hipSuccess && enqueue_generations(c, tp, 0, budget, false) != MC_LYA_OK) e = hipErrorUnknown;
             if (e == hipSuccess && enqueue_tail(c, c->total_packets, false) != MC_LYA_OK) e = hipErrorUnknown;
-            if (e == hipSuccess && enqueue_red_list(c, c->total_packets, false) != MC_LYA_OK) e = hipErrorUnknown;
+            if (e == hipSuccess && enqueue_red_list(c, c->total_packets, budget, false) != MC_LYA_OK) e = hipErrorUnknown;
         }
         c->generations = gens;
         if (forked && join_beside(c) != MC_LYA_OK) e = hipErrorUnknown;
@@ -955,7 +1014,9 @@ mc_lya_status transport_graph(mc_lya_ctx *c, WalkPlan &w)
         st = timed_begin(c, &e1);
         if (st != MC_LYA_OK) return st;
     }
+    c->share_dirty = w.tiled && c->share > 1;
     HIP_TRY(c, hipGraphLaunch(c->graph_exec, c->stream));
+    c->share_dirty = false;                  // the graph ends with their sum
     st = timed_end(c, e1);
     if (st != MC_LYA_OK) return st;
     c->generations = budget;
@@ -964,7 +1025,7 @@ mc_lya_status transport_graph(mc_lya_ctx *c, WalkPlan &w)
         st = drain_generations(c, tp, budget, &end);
         // generations beyond the budget ran eagerly: their tail walk too
         if (st == MC_LYA_OK && end > budget) st = enqueue_tail(c, c->total_packets, true);
-        if (st == MC_LYA_OK && end > budget) st = enqueue_red_list(c, c->total_packets, true);
+        if (st == MC_LYA_OK && end > budget) st = enqueue_red_list(c, c->total_packets, end, true);
         if (st != MC_LYA_OK) return st;
         // ran out of captured generations: the next capture takes what this
         // emission needed plus one round of slack (empty generations return
@@ -980,6 +1041,10 @@ mc_lya_status launch_walk(mc_lya_ctx *c, uint64_t first, uint64_t count)
     WalkPlan w;
     mc_lya_status st = plan_walk(c, first, count, &w);
     if (st != MC_LYA_OK) return st;
+    if (c->share_dirty) {                    // left by a walk that failed
+        HIP_TRY(c, hipMemsetAsync(c->d_share, 0, sizeof(unsigned long long) * c->share_cells, c->stream));
+        c->share_dirty = false;
+    }
     c->generations = 0;
     hipEvent_t coarse_end = nullptr;
     if (c->timing == 2) {
@@ -1018,6 +1083,14 @@ mc_lya_status launch_global_walk(mc_lya_ctx *c, const WalkParams &p, bool timed,
     }
     if (c->kernel == 1) {
         HIP_TRY(c, launch_walk_simple(p, c->block, c->stream));
+    } else if (c->kernel == 2 && c->n_boxes == 1 && box_fits_lds(c->total_cells, c->vel)) {
+        WalkParams q = p;
+        const uint64_t waves = (count + 63) / 64;
+        const int per = (int)std::min<uint64_t>(16, (waves + c->num_cu - 1) / c->num_cu);
+        const int grid = (int)std::min<uint64_t>((uint64_t)c->num_cu, (waves + per - 1) / per);
+        q.chunk = 64;
+        q.nqueues = 1;
+        HIP_TRY(c, launch_walk_box(q, c->total_cells, 64 * per, grid, c->stream));
     } else {
         const int waves_per_block = c->block / 64;
         // never more workgroups than can be resident at once
@@ -1027,7 +1100,12 @@ mc_lya_status launch_global_walk(mc_lya_ctx *c, const WalkParams &p, bool timed,
         int grid = c->num_cu * per_cu;
         const uint64_t need = (count + 63) / 64;     // no more waves than packets
         if ((uint64_t)grid * waves_per_block > need) grid = (int)std::max<uint64_t>(1, (need + waves_per_block - 1) / waves_per_block);
-        HIP_TRY(c, launch_walk_persistent(p, c->block, grid, c->stream));
+        // few packets: every wave gets some (a whole chunk each would leave
+        // most waves without)
+        WalkParams q = p;
+        const uint64_t each = count / ((uint64_t)grid * waves_per_block);
+        q.chunk = (int32_t)std::min<uint64_t>((uint64_t)p.chunk, std::max<uint64_t>(64, each));
+        HIP_TRY(c, launch_walk_persistent(q, c->block, grid, c->stream));
     }
     if (timed) return timed_end(c, e1);
     return MC_LYA_OK;
@@ -1156,7 +1234,16 @@ mc_lya_status mc_lya_init(mc_lya_ctx **out, const mc_lya_box_desc *boxes, int32_
     c->cpp.assign(n_boxes, 1.0);
     c->tiled.assign(n_boxes, 1);         // the tile table starts with every box; emit narrows it
     build_tiles(c);
-    const size_t nt = c->tiles.size();
+    const size_t nt0 = c->tiles.size();
+    // (a lone box with few tiles: room for its tiles shared among the chip's workgroups)
+    const size_t nt = n_boxes == 1 ? std::max<size_t>(nt0, (size_t)c->num_cu) : nt0;
+    c->share_cells = (nt - nt0) * (size_t)kTileCells;
+    if (c->share_cells) {
+        if ((e = dalloc(&c->d_share, c->share_cells)) != hipSuccess)
+            return cleanup(e == hipErrorOutOfMemory ? MC_LYA_ENOMEM : MC_LYA_EDEVICE);
+        if (hipMemsetAsync(c->d_share, 0, sizeof(unsigned long long) * c->share_cells, c->stream) != hipSuccess)
+            return cleanup(MC_LYA_EDEVICE);
+    }
     if ((e = dalloc(&c->d_tiles, nt)) != hipSuccess || (e = dalloc(&c->d_texits[0], nt)) != hipSuccess ||
         (e = dalloc(&c->d_texits[1], nt)) != hipSuccess || (e = dalloc(&c->d_gen, kGenCounters)) != hipSuccess ||
         (e = dalloc(&c->d_tail_prefix, nt)) != hipSuccess)
@@ -1166,7 +1253,7 @@ mc_lya_status mc_lya_init(mc_lya_ctx **out, const mc_lya_box_desc *boxes, int32_
         hipEventCreateWithFlags(&c->fork, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->join, hipEventDisableTiming) != hipSuccess)
         return cleanup(MC_LYA_EDEVICE);
-    if (hipMemcpyAsync(c->d_tiles, c->tiles.data(), sizeof(TileInfo) * nt, hipMemcpyHostToDevice, c->stream) !=
+    if (hipMemcpyAsync(c->d_tiles, c->tiles.data(), sizeof(TileInfo) * nt0, hipMemcpyHostToDevice, c->stream) !=
             hipSuccess ||
         hipMemcpyAsync(c->d_pack, c->pack.data(), sizeof(PackBox) * n_boxes, hipMemcpyHostToDevice, c->stream) !=
             hipSuccess)

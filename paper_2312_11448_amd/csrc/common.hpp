@@ -59,14 +59,16 @@ struct BoxRed {
 // (red_core.hpp): a later deposit is at most w (cg exp(-xup^2) + cv / xup^2),
 // xup the largest frequency still to come.
 enum : int32_t { kRedOff = 0, kRedStill = 1, kRedFlow = 2 };   // not used, no flow, flow
-struct alignas(32) RedBox {
+struct alignas(64) RedBox {
     float cg, cv;
     float ub[3];          // <U>
     float udev;           // max |U_c - <U>|, rounded up
     float round;          // bound on the binary32 roundings of x at one face
+    float binade;         // largest power of two <= x_eff
     int32_t mode;
+    int32_t pad;
 };
-static_assert(sizeof(RedBox) == 32, "RedBox layout");
+static_assert(sizeof(RedBox) == 64, "RedBox layout");
 
 // Per-box running totals of the walk (device, int64).
 struct BoxTot {
@@ -227,8 +229,11 @@ struct TileInfo {
     int32_t nsrc;            // exit lists this tile pulls from (0..6)
     int32_t src_tile[6];     // tile whose exits through face src_face[k] enter this tile
     uint32_t src_faces;      // 4 bits per source: the face (0 -x, 1 +x, 2 -y, 3 +y, 4 -z, 5 +z)
-    uint32_t span;           // bit a: the tile spans the box along axis a (a packet wraps
-                             // round inside the tile instead of leaving it)
+    uint32_t span;           // bits 0-2: the tile spans the box along axis a (a packet wraps
+                             // round inside the tile instead of leaving it); bits 8-19 and
+                             // 20-31: how many workgroups share the tile's cells, and which
+                             // of them this entry is (its share of the emitted packets, its
+                             // own tally)
 };
 static_assert(sizeof(TileInfo) == 64, "TileInfo layout");
 
@@ -267,10 +272,12 @@ constexpr int kMaxGenerations = 4096;  // per transport batch (packets cross at 
 // Counters of a batch: per generation (bump allocator, exits), then the tail
 // hand-off: the generation that found fewer than tail_min packets in flight
 // (0 = none) and the number of packets handed to the tail walk; then the red
-// list: the packets written to it and those already counted to their end.
-constexpr int kGenCounters = 2 * kMaxGenerations + 4;
+// list: the packets written to it, those already counted to their end, and
+// those given back to be stepped.
+constexpr int kGenCounters = 2 * kMaxGenerations + 5;
 constexpr int kTailGenSlot = 2 * kMaxGenerations, kTailCountSlot = 2 * kMaxGenerations + 1;
 constexpr int kRedCountSlot = 2 * kMaxGenerations + 2, kRedDoneSlot = 2 * kMaxGenerations + 3;
+constexpr int kRedUnsureSlot = 2 * kMaxGenerations + 4;
 
 struct TileParams {
     const WalkBox *boxes;
@@ -303,6 +310,8 @@ struct TileParams {
     const RedBox *red;
     PState *red_state;       // packets with no deposit left to make (one slot per packet of the batch)
     unsigned long long *red_count;
+    unsigned long long *share_A;    // tallies of the sharing workgroups after a tile's first
+                                    // (kTileCells each; entry T of n tiles at T - n)
 };
 
 // The tail walk: the packets the last full generation handed on, walked to
@@ -334,13 +343,17 @@ struct RedParams {
     const void *rec;
     BoxTot *tot;
     const PState *state;
-    unsigned long long *counters;   // the batch counters (kRedCountSlot, kRedDoneSlot)
+    uint32_t *unsure;               // list entries to be stepped
+    unsigned long long *counters;   // the batch counters (kRedCountSlot, kRedDoneSlot, kRedUnsureSlot)
 };
 
 hipError_t launch_tile_generation(const TileParams &p, bool gen0, bool vel, bool voigt, hipStream_t s);
 // The tail walk of a batch (no-op when no generation stopped); `capacity`
 // bounds the packets it can take (tail_min).
 hipError_t launch_tail_walk(const TailParams &p, uint64_t capacity, bool vel, bool voigt, hipStream_t s);
+// Adds the sharing workgroups' tallies to the cells' and zeroes them.
+hipError_t launch_share_sum(const TileInfo *tiles, const WalkBox *boxes, int n_tiles, int share, unsigned long long *A,
+                            unsigned long long *share_A, hipStream_t s);
 // Counts the packets of the red list that are not yet done; launch_red_mark
 // makes the list as it stands done (before more packets are added to it).
 hipError_t launch_red_list(const RedParams &p, int grid, bool vel, bool voigt, hipStream_t s);
@@ -349,6 +362,10 @@ hipError_t launch_zero_counters(unsigned long long *c, int n, hipStream_t s);
 
 hipError_t launch_walk_simple(const WalkParams &p, int block, hipStream_t s);
 hipError_t launch_walk_persistent(const WalkParams &p, int block, int grid, hipStream_t s);
+// The persistent walk of a lone box with its records in LDS (box_fits_lds),
+// one workgroup of up to 1024 threads per compute unit.
+bool box_fits_lds(uint64_t cells, bool vel);
+hipError_t launch_walk_box(const WalkParams &p, uint64_t cells, int block, int grid, hipStream_t s);
 int persistent_blocks_per_cu(bool vel, bool voigt, int block);   // resident workgroups per CU
 hipError_t launch_trace(const WalkParams &p, mc_lya_packet_trace *out, hipStream_t s);
 hipError_t launch_philox(const uint32_t *ctr, const uint32_t *key, uint32_t *out, uint64_t n,

@@ -12,7 +12,6 @@ namespace mclya {
 namespace {
 
 constexpr int kRedBlock = 256;
-constexpr uint32_t kRedChunk = 1024;     // packets of a workgroup's turn
 
 // Box of a global cell (boxes sorted by cell offset).
 __device__ __forceinline__ int box_of_cell(const WalkBox *boxes, int n_boxes, uint32_t c)
@@ -36,65 +35,66 @@ __device__ __forceinline__ void load_red(Lane &L, const PState &o, const WalkBox
     L.c = o.pos;
 }
 
-// Each workgroup takes chunks of the list. The packets that red_count gives
-// back (a few per cent) are collected and stepped together afterwards, so that
-// one of them does not hold a wave of others.
-template <bool VEL, bool VOIGT>
+// The packets that red_count gives back (a few per cent) go to a list of
+// their own and are stepped by a second launch (STEP), so that one of them
+// does not hold a wave of others.
+template <bool VEL, bool VOIGT, bool STEP>
 __global__ __launch_bounds__(kRedBlock) void red_list_kernel(RedParams P)
 {
-    __shared__ uint32_t s_unsure[kRedChunk];
-    __shared__ uint32_t s_n;
-    const uint64_t n = P.counters[kRedCountSlot], done = P.counters[kRedDoneSlot];
+    const uint64_t done = STEP ? 0 : P.counters[kRedDoneSlot];
+    const uint64_t n = STEP ? P.counters[kRedUnsureSlot] : P.counters[kRedCountSlot];
     Acc acc{-1, 0, 0, 0, 0, 0};
-    // one packet of the list (or none: i >= n); second = stepped
-    auto take = [&](bool have, uint64_t i, bool second) {
+    const uint64_t stride = (uint64_t)gridDim.x * kRedBlock;
+    for (uint64_t base = done + (uint64_t)blockIdx.x * kRedBlock; base < n; base += stride) {
+        uint64_t i = base + threadIdx.x;
+        const bool have = i < n;
         PState o;
         int box = acc.box;
         if (have) {
+            if (STEP) i = P.unsure[i];
             o = P.state[i];
             box = P.n_boxes == 1 ? 0 : box_of_cell(P.boxes, P.n_boxes, o.pos);
         }
         const bool change = have && box != acc.box;
         if (__ballot(change && acc.box >= 0)) flush(acc, change, P.tot);
-        if (!have) return;
-        acc.box = box;
-        const WalkBox B = P.boxes[box];
-        const RedBox R = P.red[box];
-        const Line ln = line_of(B);
-        Lane L;
-        load_red(L, o, B);
-        RedEnd e;
-        if (!VEL || R.mode == kRedStill) {
-            e = red_exact<false, VOIGT>(L, P.rec, P.max_cross, ln);
-        } else if (!second) {
-            e = red_count<VOIGT>(L, R, P.rec, P.max_cross, ln);
-            if (e.fate == kUnsure) {
-                s_unsure[atomicAdd(&s_n, 1u)] = (uint32_t)(i - done);
-                return;
+        bool unsure = false;
+        if (have) {
+            acc.box = box;
+            const WalkBox B = P.boxes[box];
+            const RedBox R = P.red[box];
+            const Line ln = line_of(B);
+            Lane L;
+            load_red(L, o, B);
+            RedEnd e;
+            if (STEP) {
+                finish_entry<true>(L, load_rec<true>(P.rec, L.c));
+                e = red_exact<true, VOIGT>(L, P.rec, P.max_cross, ln);
+            } else if (!VEL || R.mode == kRedStill) {
+                e = red_exact<false, VOIGT>(L, P.rec, P.max_cross, ln);
+            } else {
+                e = red_count<VOIGT>(L, R, P.rec, P.max_cross, ln);
+                unsure = e.fate == kUnsure;
             }
-        } else {
-            finish_entry<true>(L, load_rec<true>(P.rec, L.c));
-            e = red_exact<true, VOIGT>(L, P.rec, P.max_cross, ln);
-        }
-        acc.cross += e.n;
-        acc.esc += e.fate == kEscaped ? L.w : 0u;
-        acc.capn += e.fate == kCapped ? 1u : 0u;
-        acc.capw += e.fate == kCapped ? L.w : 0u;
-        acc.wing += e.wing;
-    };
-    for (uint64_t base = done + (uint64_t)blockIdx.x * kRedChunk; base < n; base += (uint64_t)gridDim.x * kRedChunk) {
-        if (threadIdx.x == 0) s_n = 0;
-        __syncthreads();
-        for (uint32_t k = threadIdx.x; k < kRedChunk; k += kRedBlock) take(base + k < n, base + k, false);
-        if (VEL) {
-            __syncthreads();
-            const uint32_t m = s_n;
-            for (uint32_t k0 = 0; k0 < m; k0 += kRedBlock) {
-                const uint32_t k = k0 + threadIdx.x;
-                take(k < m, k < m ? done + s_unsure[k] : 0, true);
+            if (!unsure) {
+                acc.cross += e.n;
+                acc.esc += e.fate == kEscaped ? L.w : 0u;
+                acc.capn += e.fate == kCapped ? 1u : 0u;
+                acc.capw += e.fate == kCapped ? L.w : 0u;
+                acc.wing += e.wing;
             }
         }
-        __syncthreads();
+        if (VEL && !STEP) {
+            const uint64_t m = __ballot(unsure);
+            if (m) {
+                unsigned long long at = 0;
+                if (__lane_id() == (uint32_t)(__ffsll((unsigned long long)m) - 1))
+                    at = atomicAdd(&P.counters[kRedUnsureSlot], (unsigned long long)__popcll(m));
+                at = __shfl(at, __ffsll((unsigned long long)m) - 1, 64);
+                if (unsure)
+                    P.unsure[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = (uint32_t)i;
+            }
+        }
     }
     flush(acc, true, P.tot);
 }
@@ -102,20 +102,27 @@ __global__ __launch_bounds__(kRedBlock) void red_list_kernel(RedParams P)
 __global__ void red_mark_kernel(unsigned long long *counters)
 {
     counters[kRedDoneSlot] = counters[kRedCountSlot];
+    counters[kRedUnsureSlot] = 0;
+}
+
+template <bool VOIGT>
+void launch(const RedParams &p, dim3 g, bool vel, hipStream_t s)
+{
+    const dim3 b(kRedBlock);
+    if (vel) {
+        hipLaunchKernelGGL((red_list_kernel<true, VOIGT, false>), g, b, 0, s, p);
+        hipLaunchKernelGGL((red_list_kernel<true, VOIGT, true>), g, b, 0, s, p);
+    } else {
+        hipLaunchKernelGGL((red_list_kernel<false, VOIGT, false>), g, b, 0, s, p);
+    }
 }
 
 }  // namespace
 
 hipError_t launch_red_list(const RedParams &p, int grid, bool vel, bool voigt, hipStream_t s)
 {
-    const dim3 g((unsigned)grid), b(kRedBlock);
-    if (voigt) {
-        if (vel) hipLaunchKernelGGL((red_list_kernel<true, true>), g, b, 0, s, p);
-        else hipLaunchKernelGGL((red_list_kernel<false, true>), g, b, 0, s, p);
-    } else {
-        if (vel) hipLaunchKernelGGL((red_list_kernel<true, false>), g, b, 0, s, p);
-        else hipLaunchKernelGGL((red_list_kernel<false, false>), g, b, 0, s, p);
-    }
+    if (voigt) launch<true>(p, dim3((unsigned)grid), vel, s);
+    else launch<false>(p, dim3((unsigned)grid), vel, s);
     return hipGetLastError();
 }
 

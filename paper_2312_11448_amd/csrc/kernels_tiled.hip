@@ -364,7 +364,8 @@ struct TileAcc {
 // the tile's edge and write them out at the next refill, defer thin waves.
 template <bool VEL, bool GEN0, bool VOIGT, bool WRAP>
 __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &ti, const WalkBox &B,
-                                          const TileCtx &C, uint32_t n_in, const uint32_t *pre, const uint32_t *lst,
+                                          const TileCtx &C, uint32_t n_in, uint32_t j0, const uint32_t *pre,
+                                          const uint32_t *lst,
                                           const char *recs, unsigned long long *tally, uint32_t *s_next,
                                           uint32_t *s_exit, uint32_t *s_red_n, uint32_t s_base, uint32_t *s_fcnt,
                                           unsigned long long *s_tot, TileAcc &acc)
@@ -375,7 +376,9 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
     const uint64_t r_lo = P.first;
     TLane L;
     idle_tlane(L, RS);          // every lane steps, so none starts undefined
-    bool alive = false, more = true;
+    // (little input: waves enough for it, each filled, instead of all waves
+    // with a few lanes each sharing the issue slots)
+    bool alive = false, more = uniform_u32(threadIdx.x >> 6) * 64u < n_in;
     bool fresh = false;          // wave-uniform: packets loaded since the wave's last step
     // A packet that reaches the tile's edge parks in its lane and is written
     // out when the wave next refills or stops: one exit-writing pass for many
@@ -426,7 +429,7 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
                 if (lane == 0) {
                     const uint32_t seen = __hip_atomic_load(s_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                     const uint32_t left = seen < n_in ? n_in - seen : 0u;
-                    want = left < chunk * kWaves ? max(left / kWaves, min(chunk, kMinClaim)) : chunk;
+                    want = left < chunk * kWaves ? max(left / kWaves, min(chunk, n_in < 64u * kWaves ? 64u : kMinClaim)) : chunk;
                     base = atomicAdd(s_next, want);
                 }
                 base = uniform_u32(__shfl(base, 0, 64));
@@ -441,7 +444,7 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
             const uint32_t take = min((uint32_t)__popcll(idle), end - cur);
             const uint32_t r = rank_in(idle);
             if (!alive && r < take) {
-                const uint32_t j = cur + r;
+                const uint32_t j = (GEN0 ? j0 : 0u) + cur + r;
                 Lane N;
                 int32_t lx, ly, lz;
                 if (GEN0) {
@@ -673,6 +676,13 @@ __global__ __launch_bounds__(BLK) void tile_walk_kernel(TileParams P)
         __syncthreads();
     }
     n_in = uniform_u32(s_total);   // (uniform, so the walk loop's exits are too)
+    const uint32_t share = ti.span >> 8 & 0xfffu, part = ti.span >> 20;
+    uint32_t j0 = 0;
+    if (GEN0 && share > 1) {
+        // this workgroup's share of the tile's emitted packets
+        j0 = (uint32_t)((uint64_t)n_in * part / share);
+        n_in = (uint32_t)((uint64_t)n_in * (part + 1) / share) - j0;
+    }
     if (n_in == 0) {
         if (tid == 0) {
             TileExits e;
@@ -705,16 +715,16 @@ __global__ __launch_bounds__(BLK) void tile_walk_kernel(TileParams P)
     C.sx = ti.sx;
     C.sy = ti.sy;
     C.sz = ti.sz;
-    C.span = ti.span;
+    C.span = ti.span & 7u;
     C.red = P.red[ti.box];
     const char *recs = VEL ? reinterpret_cast<const char *>(srec4) : reinterpret_cast<const char *>(sreck);
     TileAcc acc{0};
     // a tile that spans the box along some axis wraps round inside itself
-    if (ti.span)
-        walk_tile<VEL, GEN0, VOIGT, true>(P, ti, B, C, n_in, pre, lst, recs, tally, &s_next, &s_exit, &s_red_n, s_base, s_fcnt,
+    if (C.span)
+        walk_tile<VEL, GEN0, VOIGT, true>(P, ti, B, C, n_in, j0, pre, lst, recs, tally, &s_next, &s_exit, &s_red_n, s_base, s_fcnt,
                                           s_tot, acc);
     else
-        walk_tile<VEL, GEN0, VOIGT, false>(P, ti, B, C, n_in, pre, lst, recs, tally, &s_next, &s_exit, &s_red_n, s_base, s_fcnt,
+        walk_tile<VEL, GEN0, VOIGT, false>(P, ti, B, C, n_in, j0, pre, lst, recs, tally, &s_next, &s_exit, &s_red_n, s_base, s_fcnt,
                                            s_tot, acc);
 
     // ---- finish: tally, totals, face lists of the exits ----------------------
@@ -722,26 +732,30 @@ __global__ __launch_bounds__(BLK) void tile_walk_kernel(TileParams P)
     __threadfence_block();
     __syncthreads();
     {
-        // this workgroup alone owns these cells in this generation: plain
+        // this workgroup alone owns these cells in this generation (or its own
+        // tally of them, where several share the tile): plain
         // read-modify-write, every read issued before the first is used
         constexpr int PER = TC / BLK;
         unsigned long long v[PER], old[PER];
         uint32_t gc[PER];
+        unsigned long long *const A =
+            part ? P.share_A + (size_t)(T - P.ntiles / (int)share) * TC : P.A;
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int q = tid + k * BLK;
             const int lx = q & 15, ly = (q >> 4) & 15, lz = q >> 8;
             v[k] = (lx < ti.sx && ly < ti.sy && lz < ti.sz) ? tally[tile_slot(lx, ly, lz)] : 0ull;
-            gc[k] = B.cell_off + (uint32_t)(ti.ox + lx) +
-                    (uint32_t)B.nx * ((uint32_t)(ti.oy + ly) + (uint32_t)B.ny * (uint32_t)(ti.oz + lz));
+            gc[k] = part ? (uint32_t)q
+                         : B.cell_off + (uint32_t)(ti.ox + lx) +
+                               (uint32_t)B.nx * ((uint32_t)(ti.oy + ly) + (uint32_t)B.ny * (uint32_t)(ti.oz + lz));
             old[k] = 0ull;
         }
 #pragma unroll
         for (int k = 0; k < PER; ++k)
-            if (v[k]) old[k] = P.A[gc[k]];
+            if (v[k]) old[k] = A[gc[k]];
 #pragma unroll
         for (int k = 0; k < PER; ++k)
-            if (v[k]) P.A[gc[k]] = old[k] + v[k];
+            if (v[k]) A[gc[k]] = old[k] + v[k];
     }
     if (tid < (VOIGT ? 5 : 4)) {
         // (after the barrier: every wave's walk has ended, so s_tot is final)
@@ -918,6 +932,29 @@ __global__ __launch_bounds__(256) void tail_walk_kernel(TailParams P)
     }
 }
 
+// The cells of tile t: the tallies of the workgroups that shared it, added to
+// the cells' own and zeroed for the next walk.
+__global__ __launch_bounds__(256) void share_sum_kernel(const TileInfo *__restrict__ tiles,
+                                                        const WalkBox *__restrict__ boxes, int n_tiles, int share,
+                                                        unsigned long long *__restrict__ A,
+                                                        unsigned long long *__restrict__ share_A)
+{
+    const int t = blockIdx.y, q = blockIdx.x * 256 + threadIdx.x;
+    const TileInfo ti = tiles[t];
+    const WalkBox B = boxes[ti.box];
+    const int lx = q & 15, ly = (q >> 4) & 15, lz = q >> 8;
+    if (lx >= ti.sx || ly >= ti.sy || lz >= ti.sz) return;
+    unsigned long long s = 0;
+    for (int r = 0; r < share - 1; ++r) {
+        unsigned long long *p = &share_A[((size_t)r * n_tiles + t) * TC + q];
+        s += *p;
+        *p = 0ull;
+    }
+    const uint32_t gc = B.cell_off + (uint32_t)(ti.ox + lx) +
+                        (uint32_t)B.nx * ((uint32_t)(ti.oy + ly) + (uint32_t)B.ny * (uint32_t)(ti.oz + lz));
+    A[gc] += s;
+}
+
 __global__ void zero_counters_kernel(unsigned long long *c, int n)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -960,6 +997,14 @@ hipError_t launch_tail_walk(const TailParams &p, uint64_t capacity, bool vel, bo
         if (vel) hipLaunchKernelGGL((tail_walk_kernel<true, false>), grid, dim3(256), 0, s, p);
         else hipLaunchKernelGGL((tail_walk_kernel<false, false>), grid, dim3(256), 0, s, p);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_share_sum(const TileInfo *tiles, const WalkBox *boxes, int n_tiles, int share, unsigned long long *A,
+                            unsigned long long *share_A, hipStream_t s)
+{
+    hipLaunchKernelGGL(share_sum_kernel, dim3((unsigned)(TC / 256), (unsigned)n_tiles), dim3(256), 0, s, tiles, boxes,
+                       n_tiles, share, A, share_A);
     return hipGetLastError();
 }
 

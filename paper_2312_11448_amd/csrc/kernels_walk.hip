@@ -10,13 +10,18 @@
 //                    so the 10-20% of packets emitted on the red side, which
 //                    walk hundreds of cells, do not leave the rest of the wave
 //                    idle;
+//   walk_box         the same for a lone box whose records fit a compute
+//                    unit's LDS;
 //   walk_simple      one thread per packet (reference driver, same results).
-// Both produce bit-identical integer tallies: each packet's arithmetic does
+// All produce bit-identical integer tallies: each packet's arithmetic does
 // not depend on the driver, and integer additions commute.
-#include "walk_core.hpp"
+#include "red_core.hpp"
 
 namespace mclya {
 namespace {
+
+constexpr int kBoxLds = 156 * 1024;   // LDS for a lone box's records (walk_box_kernel)
+
 
 // ---- wave helpers --------------------------------------------------------
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
@@ -64,13 +69,34 @@ __device__ __forceinline__ uint64_t packet_id(const WalkParams &P, uint64_t i)
 }
 
 // ---- persistent driver ---------------------------------------------------
-template <bool VEL, bool VOIGT>
-__global__ __launch_bounds__(256) void walk_persistent_kernel(WalkParams P)
-{
-    extern __shared__ WalkBox sbox[];
-    for (int i = threadIdx.x; i < P.n_boxes; i += blockDim.x) sbox[i] = P.boxes[i];
-    __syncthreads();
+// How often a lane looks whether its packet has a deposit left to make, and
+// how many such packets a wave gathers before it counts them to their end
+// together (or until it refills, or has nothing else to do).
+constexpr uint32_t kRedEvery = 4, kRedGather = 32;
 
+// The records of a lone box in LDS (walk_box_kernel), its tallies there too
+// (a small box) or in device memory. No global load is then in a step, so a
+// step never waits for an earlier step's deposit (loads and atomics return in
+// order).
+struct BoxSink {
+    static constexpr bool kCell = true;
+    unsigned long long *A;        // in LDS or device memory
+    const char *lds;
+    __device__ __forceinline__ void deposit(const Lane &L, uint32_t d) const
+    {
+        atomicAdd(&A[L.c], (unsigned long long)d);
+    }
+    __device__ __forceinline__ bool inside(int32_t, int32_t, int32_t) const { return true; }
+    template <bool VEL>
+    __device__ __forceinline__ Rec fetch(const void *__restrict__, uint32_t cn, int32_t, int32_t, int32_t, bool) const
+    {
+        return load_rec<VEL>(lds, cn);       // (a lone box starts at cell 0)
+    }
+};
+
+template <bool VEL, bool VOIGT, class Sink>
+__device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkBox *sbox, const Sink &sink)
+{
     const uint32_t lane = lane_id();
     const uint32_t max_cross = (uint32_t)P.max_cross;
     Lane L;
@@ -78,6 +104,9 @@ __global__ __launch_bounds__(256) void walk_persistent_kernel(WalkParams P)
     Line ln{0.0f, 0.0f, 0.0f};
     Acc acc{-1, 0, 0, 0, 0, 0};
     bool alive = false;
+    bool red = false;                 // holds a packet with no deposit left, to be counted to its end
+    bool sure = true;                 // (that count can still be tried)
+    uint32_t tick = 0;                // wave-uniform: steps taken
     bool more = true;                 // wave-uniform: queue not drained
     uint64_t cur = 0, end = 0;        // wave-uniform: current block of packet ids
     const uint32_t refill = (uint32_t)P.refill;
@@ -92,7 +121,29 @@ __global__ __launch_bounds__(256) void walk_persistent_kernel(WalkParams P)
 
     for (;;) {
         uint64_t idle = __ballot(!alive);
-        if (more && (uint32_t)__popcll(idle) >= refill) {
+        const bool fill = more && (uint32_t)__popcll(idle) >= refill;
+        const uint64_t reds = __ballot(red);
+        if (reds && (fill || (uint32_t)__popcll(reds) >= kRedGather || !__ballot(alive))) {
+            if (red) {
+                const RedBox R = P.red[acc.box];
+                RedEnd e;
+                if (!VEL || R.mode == kRedStill) e = red_exact<false, VOIGT>(L, P.rec, max_cross, ln);
+                else e = red_count<VOIGT>(L, R, P.rec, max_cross, ln);
+                if (e.fate == kUnsure) {
+                    sure = false;     // stepped on
+                    alive = true;
+                } else {
+                    acc.cross += L.ncross + e.n;
+                    acc.esc += e.fate == kEscaped ? L.w : 0u;
+                    acc.capn += e.fate == kCapped ? 1u : 0u;
+                    acc.capw += e.fate == kCapped ? L.w : 0u;
+                    acc.wing += e.wing;
+                }
+                red = false;
+            }
+            idle = __ballot(!alive);
+        }
+        if (fill) {
             while (idle && more) {
                 if (cur >= end) {
                     const uint64_t lo = P.count * part / nq, hi = P.count * (part + 1) / nq;
@@ -108,7 +159,7 @@ __global__ __launch_bounds__(256) void walk_persistent_kernel(WalkParams P)
                     cur = base;
                     end = base + chunk < hi ? base + chunk : hi;
                 }
-        const uint64_t n_idle = (uint64_t)__popcll(idle);
+                const uint64_t n_idle = (uint64_t)__popcll(idle);
                 const uint64_t take = n_idle < end - cur ? n_idle : end - cur;
                 const uint32_t r = rank_in(idle);
                 const bool fresh = !alive && (uint64_t)r < take;
@@ -126,6 +177,7 @@ __global__ __launch_bounds__(256) void walk_persistent_kernel(WalkParams P)
                     init_packet<VEL, VOIGT>(L, B, gp - B.pkt_off, P.cell_of_packet[gp], P.rec);
                     if (VOIGT) ln = line_of(B);
                     alive = true;
+                    sure = P.red[nb].mode != kRedOff;
                 }
                 cur += take;
                 idle = __ballot(!alive);
@@ -141,7 +193,7 @@ __global__ __launch_bounds__(256) void walk_persistent_kernel(WalkParams P)
             uint64_t dep = 0;
             uint32_t wing = 0;
             Lane Ln = L;
-            const int fate = walk_step<VEL, VOIGT>(Ln, P.rec, GlobalSink{P.A}, max_cross, dep, ln, wing, alive);
+            const int fate = walk_step<VEL, VOIGT>(Ln, P.rec, sink, max_cross, dep, ln, wing, alive);
             keep_or_take(L, Ln, alive);
             const bool fin = alive && fate != kAlive;
             acc.cross += fin ? L.ncross : 0u;
@@ -150,9 +202,55 @@ __global__ __launch_bounds__(256) void walk_persistent_kernel(WalkParams P)
             acc.capw += fin && fate == kCapped ? L.w : 0u;
             acc.wing += fin ? wing : 0u;
             alive = alive && fate == kAlive;
+            if (++tick % kRedEvery == 0 && __ballot(alive && sure)) {
+                if (alive && sure) red = red_only(P.red[acc.box], L.x, L.ku, L.kx, L.ky, L.kz, L.w);
+                alive = alive && !red;
+            }
         }
     }
     flush(acc, true, P.tot);
+}
+
+template <bool VEL, bool VOIGT>
+__global__ __launch_bounds__(256) void walk_persistent_kernel(WalkParams P)
+{
+    extern __shared__ WalkBox sbox[];
+    for (int i = threadIdx.x; i < P.n_boxes; i += blockDim.x) sbox[i] = P.boxes[i];
+    __syncthreads();
+    persistent_walk<VEL, VOIGT>(P, sbox, GlobalSink{P.A});
+}
+
+// A lone box whose records fit the LDS: each workgroup reads them all once.
+// A few packets in such a box are one chain of cells each, and its time is
+// the longest chain's: the latency of a step. With the records in L2 a step
+// waited for its read and, as they return in order, for the last deposit.
+// TALLY: the tallies fit too, and are added to the device's at the end. A box
+// of a few cells needs that: its deposits all go to the same few cache lines
+// (8^3 cells: 6.4e9 deposits/s instead of the device's 2.4e10).
+template <bool VEL, bool VOIGT, bool TALLY>
+__global__ __launch_bounds__(1024) void walk_box_kernel(WalkParams P)
+{
+    __shared__ float4 recs[kBoxLds / 16];
+    __shared__ WalkBox sbox[1];
+    if (threadIdx.x == 0) sbox[0] = P.boxes[0];
+    const WalkBox B = P.boxes[0];
+    const uint32_t cells = B.cells();
+    unsigned long long *tally = reinterpret_cast<unsigned long long *>(recs) + (kBoxLds / 8 - cells);   // (TALLY)
+    if (VEL) {
+        for (uint32_t i = threadIdx.x; i < cells; i += blockDim.x) recs[i] = static_cast<const float4 *>(P.rec)[i];
+    } else {
+        float *k = reinterpret_cast<float *>(recs);
+        for (uint32_t i = threadIdx.x; i < cells; i += blockDim.x) k[i] = static_cast<const float *>(P.rec)[i];
+    }
+    if (TALLY)
+        for (uint32_t i = threadIdx.x; i < cells; i += blockDim.x) tally[i] = 0ull;
+    __syncthreads();
+    persistent_walk<VEL, VOIGT>(P, sbox, BoxSink{TALLY ? tally : P.A, reinterpret_cast<const char *>(recs)});
+    if (TALLY) {
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < cells; i += blockDim.x)
+            if (tally[i]) atomicAdd(&P.A[i], tally[i]);
+    }
 }
 
 // ---- one thread per packet -------------------------------------------------
@@ -262,6 +360,31 @@ hipError_t launch_walk_persistent(const WalkParams &p, int block, int grid, hipS
         if (p.vel) hipLaunchKernelGGL((walk_persistent_kernel<true, false>), g, b, lds, s, p);
         else hipLaunchKernelGGL((walk_persistent_kernel<false, false>), g, b, lds, s, p);
     }
+    return hipGetLastError();
+}
+
+bool box_fits_lds(uint64_t cells, bool vel) { return cells * (vel ? 16 : 4) <= (uint64_t)kBoxLds; }
+
+template <bool TALLY>
+static void launch_box(const WalkParams &p, dim3 g, dim3 b, hipStream_t s)
+{
+    if (p.voigt) {
+        if (p.vel) hipLaunchKernelGGL((walk_box_kernel<true, true, TALLY>), g, b, 0, s, p);
+        else hipLaunchKernelGGL((walk_box_kernel<false, true, TALLY>), g, b, 0, s, p);
+    } else {
+        if (p.vel) hipLaunchKernelGGL((walk_box_kernel<true, false, TALLY>), g, b, 0, s, p);
+        else hipLaunchKernelGGL((walk_box_kernel<false, false, TALLY>), g, b, 0, s, p);
+    }
+}
+
+hipError_t launch_walk_box(const WalkParams &p, uint64_t cells, int block, int grid, hipStream_t s)
+{
+    hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(64), 0, s, p.queue, (int)p.nqueues);
+    // tallies in LDS where they fit and adding every workgroup's to the
+    // device's costs less than the deposits (some 40 a packet)
+    const bool tally = cells * (p.vel ? 24 : 12) <= (uint64_t)kBoxLds && cells * (uint64_t)grid <= 10 * p.count;
+    if (tally) launch_box<true>(p, dim3((unsigned)grid), dim3((unsigned)block), s);
+    else launch_box<false>(p, dim3((unsigned)grid), dim3((unsigned)block), s);
     return hipGetLastError();
 }
 

@@ -46,55 +46,73 @@ struct RedEnd {
 };
 enum : int { kUnsure = 5 };
 
+// Coordinate i moved by one cell, or by n (periodic).
+__device__ __forceinline__ int32_t moved(int32_t i, int32_t cells, bool up)
+{
+    const int32_t j = i + (up ? 1 : -1);
+    return j == cells ? 0 : (j < 0 ? cells - 1 : j);
+}
+
+__device__ __forceinline__ int32_t moved_by(int32_t i, uint32_t n, int32_t cells, bool up)
+{
+    const int32_t m = (int32_t)(n % (uint32_t)cells);
+    const int32_t j = up ? i + m : i - m;
+    return j >= cells ? j - cells : (j < 0 ? j + cells : j);
+}
+
 // The rest of the walk of a packet standing inside its cell, face by face,
-// with the roundings of the walk (segment, finish_entry) but no deposits.
+// with the roundings of the walk (segment, finish_entry) but no deposits. The
+// ray's faces do not depend on the cells, so with a flow they are taken
+// kAhead at a time and their cells' records read together.
 template <bool FLOW, bool VOIGT>
 __device__ __forceinline__ RedEnd red_exact(Lane &L, const void *__restrict__ rec, uint32_t max_cross, const Line &ln)
 {
+    constexpr int kAhead = FLOW ? 8 : 1;
     RedEnd e{0u, kEscaped, 0u};
     float stop = -L.xeff;
-    for (;;) {
-        if (L.x <= -L.xeff) {
-            stop = L.x;
-            break;
+    bool done = false;
+    while (!done) {
+        float s[kAhead];
+        Rec r[kAhead];
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            const Face f = next_face(L.tmx, L.tmy, L.tmz);
+            s[j] = (float)(f.tn - L.t);
+            L.t = f.tn;
+            L.tmx = f.bx ? L.tmx + L.tdx : L.tmx;
+            L.tmy = f.by ? L.tmy + L.tdy : L.tmy;
+            L.tmz = f.bz ? L.tmz + L.tdz : L.tmz;
+            if (FLOW) {
+                L.ix = f.bx ? moved(L.ix, L.nx, L.kx > 0.0f) : L.ix;
+                L.iy = f.by ? moved(L.iy, L.ny, L.ky > 0.0f) : L.iy;
+                L.iz = f.bz ? moved(L.iz, L.nz, L.kz > 0.0f) : L.iz;
+                r[j] = load_rec<true>(rec, cell_of(L));
+            }
         }
-        if (L.ncross + e.n >= max_cross) {
-            e.fate = kCapped;
-            return e;
-        }
-        const Face f = next_face(L.tmx, L.tmy, L.tmz);
-        const float xo = fmaf(-L.delta, (float)(f.tn - L.t), L.x);
-        ++e.n;
-        if (xo <= -L.xeff) break;
-        L.t = f.tn;
-        L.tmx = f.bx ? L.tmx + L.tdx : L.tmx;
-        L.tmy = f.by ? L.tmy + L.tdy : L.tmy;
-        L.tmz = f.bz ? L.tmz + L.tdz : L.tmz;
-        L.x = xo;
-        if (FLOW) {
-            const int32_t ci = (f.bx ? L.ix : 0) + (f.by ? L.iy : 0) + (f.bz ? L.iz : 0);
-            const int32_t ni = (f.bx ? L.nx : 0) + (f.by ? L.ny : 0) + (f.bz ? L.nz : 0);
-            const bool up = (f.bx & (L.kx > 0.0f)) | (f.by & (L.ky > 0.0f)) | (f.bz & (L.kz > 0.0f));
-            int32_t mi = ci + (up ? 1 : -1);
-            mi = mi == ni ? 0 : mi;
-            mi = mi < 0 ? ni - 1 : mi;
-            L.ix = f.bx ? mi : L.ix;
-            L.iy = f.by ? mi : L.iy;
-            L.iz = f.bz ? mi : L.iz;
-            finish_entry<true>(L, load_rec<true>(rec, cell_of(L)));
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            if (done) break;
+            if (L.x <= -L.xeff) {
+                stop = L.x;
+                done = true;
+                break;
+            }
+            if (L.ncross + e.n >= max_cross) {
+                e.fate = kCapped;
+                return e;
+            }
+            const float xo = fmaf(-L.delta, s[j], L.x);
+            ++e.n;
+            L.x = xo;
+            if (xo <= -L.xeff) {
+                done = true;
+                break;
+            }
+            if (FLOW) finish_entry<true>(L, r[j]);
         }
     }
     if (VOIGT) e.wing = wing_share(L.w, stop, ln);
     return e;
-}
-
-// Coordinate i moved by n cells (periodic).
-__device__ __forceinline__ int32_t moved(int32_t i, uint32_t n, int32_t cells, bool up)
-{
-    const int32_t m = (int32_t)(n % (uint32_t)cells);
-    int32_t j = up ? i + m : i - m;
-    j = j >= cells ? j - cells : j;
-    return j < 0 ? j + cells : j;
 }
 
 // The same with a flow, without the steps in between: L as red_exact takes it
@@ -112,11 +130,14 @@ __device__ __forceinline__ RedEnd red_count(const Lane &L, const RedBox &R, cons
     const double rd = 1.0 / (double)L.delta;
     const double t0 = L.t;
     // crossings left at most (every ray crosses at most sqrt 3 faces per unit
-    // length), and with them the sum of the walk's roundings
-    const float far = (float)((X - (double)kub + (double)R.udev + (double)L.xeff) * rd);
-    const float most = fmaf(1.7321f, fmaxf(far, 0.0f), 4.0f);
-    const float eps = fmaf(R.round, most, 2e-6f);
-    const double safe = t0 + (X - (double)kub - (double)R.udev + (double)L.xeff - 2.0 * (double)eps) * rd;
+    // length), and with them the sum of the walk's roundings: R.round a face,
+    // half that while |x| is below the binade of x_eff in every cell
+    const double xc = X - (double)kub;
+    const float far = fmaxf((float)((xc + (double)R.udev + (double)L.xeff) * rd), 0.0f);
+    const float near = fmaxf((float)((xc - (double)R.udev + (double)R.binade) * rd), 0.0f);
+    const float most = fmaf(1.7321f, far, 4.0f);
+    const float eps = fmaf(R.round, fmaf(1.7321f, far - 0.5f * fminf(near, far), 4.0f), 2e-6f);
+    const double safe = t0 + (xc - (double)R.udev + (double)L.xeff - 2.0 * (double)eps) * rd;
     double tmx = L.tmx, tmy = L.tmy, tmz = L.tmz, t = t0;
     int32_t ix = L.ix, iy = L.iy, iz = L.iz;
     bool unsure = false;
@@ -130,7 +151,7 @@ __device__ __forceinline__ RedEnd red_count(const Lane &L, const RedBox &R, cons
             t = fmax(t, last);
             const uint32_t n = (uint32_t)j + 1u;
             e.n += n;
-            i = moved(i, n, cells, up);
+            i = moved_by(i, n, cells, up);
         }
     };
     skip(tmx, L.tdx, ix, L.nx, L.kx > 0.0f);
@@ -138,42 +159,62 @@ __device__ __forceinline__ RedEnd red_count(const Lane &L, const RedBox &R, cons
     skip(tmz, L.tdz, iz, L.nz, L.kz > 0.0f);
     if (unsure) return e;
     const uint32_t limit = e.n + (uint32_t)most + 4u;
-    Rec r = load_rec<true>(rec, L.coff + (uint32_t)ix + (uint32_t)L.nx * ((uint32_t)iy + (uint32_t)L.ny * (uint32_t)iz));
-    for (;;) {
-        const Face f = next_face(tmx, tmy, tmz);
-        const double gap = fmin(f.bx ? tmy : tmx, f.bz ? tmy : tmz) - f.tn;      // to the face after it
-        tmx = f.bx ? tmx + L.tdx : tmx;
-        tmy = f.by ? tmy + L.tdy : tmy;
-        tmz = f.bz ? tmz + L.tdz : tmz;
-        ix = f.bx ? moved(ix, 1u, L.nx, L.kx > 0.0f) : ix;
-        iy = f.by ? moved(iy, 1u, L.ny, L.ky > 0.0f) : iy;
-        iz = f.bz ? moved(iz, 1u, L.nz, L.kz > 0.0f) : iz;
-        // the next cell's record, in flight during this cell's tests
-        const Rec nr = load_rec<true>(rec, L.coff + (uint32_t)ix +
-                                               (uint32_t)L.nx * ((uint32_t)iy + (uint32_t)L.ny * (uint32_t)iz));
-        const float ku = ray_velocity(L.kx, L.ky, L.kz, r);
-        const float in = (float)fma(-(double)L.delta, t - t0, X) - ku + L.xeff;       // x + x_eff on entering
-        const float out = (float)fma(-(double)L.delta, f.tn - t0, X) - ku + L.xeff;   // and on leaving
-        if (fabsf(in) <= eps || gap < kTie || e.n > limit) return e;
-        if (in < 0.0f) {                 // redshifted out by the jump into this cell
-            if (VOIGT) {
-                // the stopping frequency is known to eps: the wing's share
-                // has to be the same over that range
-                const float xs = in - L.xeff;
-                e.wing = wing_share(L.w, xs, ln);
-                if (wing_share(L.w, xs - eps - 1e-4f, ln) != e.wing || wing_share(L.w, xs + eps + 1e-4f, ln) != e.wing)
-                    return e;
+    auto read = [&]() {
+        return load_rec<true>(rec, L.coff + (uint32_t)ix + (uint32_t)L.nx * ((uint32_t)iy + (uint32_t)L.ny * (uint32_t)iz));
+    };
+    // then cell by cell, kAhead cells' records read together
+    constexpr int kAhead = 4;
+    bool done = false, jumped = false;
+    float stop = -L.xeff;
+    Rec r = read();
+    while (!done) {
+        Rec nr[kAhead];
+        float in[kAhead], out[kAhead];       // X + x_eff on entering and leaving the cell
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            const Face f = next_face(tmx, tmy, tmz);
+            unsure |= fmin(f.bx ? tmy : tmx, f.bz ? tmy : tmz) - f.tn < kTie;
+            in[j] = (float)fma(-(double)L.delta, t - t0, X);
+            out[j] = (float)fma(-(double)L.delta, f.tn - t0, X);
+            t = f.tn;
+            tmx = f.bx ? tmx + L.tdx : tmx;
+            tmy = f.by ? tmy + L.tdy : tmy;
+            tmz = f.bz ? tmz + L.tdz : tmz;
+            ix = f.bx ? moved(ix, L.nx, L.kx > 0.0f) : ix;
+            iy = f.by ? moved(iy, L.ny, L.ky > 0.0f) : iy;
+            iz = f.bz ? moved(iz, L.nz, L.kz > 0.0f) : iz;
+            nr[j] = read();
+        }
+        if (unsure || e.n > limit) return e;
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            if (done) break;
+            const float ku = ray_velocity(L.kx, L.ky, L.kz, r);
+            r = nr[j];
+            const float xi = in[j] - ku + L.xeff, xo = out[j] - ku + L.xeff;
+            if (fabsf(xi) <= eps) return e;
+            if (xi < 0.0f) {                 // redshifted out by the jump into this cell
+                stop = xi - L.xeff;
+                jumped = true;
+                done = true;
+                break;
             }
-            break;
+            ++e.n;
+            if (fabsf(xo) <= eps) return e;
+            if (xo < 0.0f) {                 // escapes inside this cell
+                done = true;
+                break;
+            }
         }
-        ++e.n;
-        if (fabsf(out) <= eps) return e;
-        if (out < 0.0f) {                // escapes inside this cell
-            if (VOIGT) e.wing = wing_share(L.w, -L.xeff, ln);
-            break;
+    }
+    if (VOIGT) {
+        e.wing = wing_share(L.w, stop, ln);
+        if (jumped) {
+            // the stopping frequency is known to eps: the wing's share has to
+            // be the same over that range
+            const float d = eps + 1e-4f;
+            if (wing_share(L.w, stop - d, ln) != e.wing || wing_share(L.w, stop + d, ln) != e.wing) return e;
         }
-        t = f.tn;
-        r = nr;
     }
     // (the cap is the stepping walk's to decide)
     if (e.n <= max_cross && L.ncross <= max_cross - e.n) e.fate = kEscaped;
