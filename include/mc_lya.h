@@ -507,7 +507,7 @@ typedef struct mc_lya_adam {
 
 /* Creates a network with the given parameters (host [MC_LYA_MLP_PARAMS],
  * copied) and zero Adam moments, on the current device; all its work goes on
- * `stream` (a hipStream_t, or NULL). Allocates about 20 MB (parameters, Adam
+ * `stream` (a hipStream_t, or NULL). Allocates about 10 MB (parameters, Adam
  * moments, the gradient workspace). On failure *out = NULL and
  * mc_lya_mlp_last_error(NULL) tells why. Errors: EINVAL (NULL or non-finite
  * parameters), ENOMEM, EDEVICE. */
@@ -585,8 +585,7 @@ mc_lya_status mc_lya_mlp_train_step(mc_lya_mlp *mlp, const float *features, cons
  *   lr        host [n_steps] learning rates (> 0); beta1, beta2, eps as in
  *             mc_lya_adam
  *   losses    host [n_steps] (each step's loss before its update), or NULL
- * The object allocates a gather buffer of batch cells (kept, grown when a
- * larger batch comes). Synchronises once, at the end; an index outside
+ * Synchronises once, at the end; an index outside
  * [0, n_cells) is then reported as EINVAL (the steps have been taken with
  * such cells read as cell 0). Errors: EINVAL, ENOMEM, EDEVICE. */
 mc_lya_status mc_lya_mlp_train_steps(mc_lya_mlp *mlp, const float *features, const float *targets,

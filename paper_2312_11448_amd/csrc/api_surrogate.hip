@@ -16,28 +16,19 @@ struct mc_lya_mlp {
     hipStream_t stream = nullptr;
     float *d_params = nullptr, *d_m = nullptr, *d_v = nullptr;
     float *d_grad = nullptr;                 // [kMlpParams + 2]: gradient, sum w r^2, sum w
-    float *d_part = nullptr;                 // [kMlpGradBlocks + kMlpGradBlocks / 32][kMlpPartStride]
+    float *d_part = nullptr;                 // [kMlpGradBlocks][kMlpPartStride]
     float *d_env = nullptr;                  // [16]: lower then upper feature bounds
     unsigned long long *d_count = nullptr;
     bool envelope = false;
     int64_t step = 0;
     int forward_grid = 0;
-    // mc_lya_mlp_train_steps: the gathered batch ([cap][8] + [cap] + [cap]),
-    // the index-range flag, and two floats of loss tail per step
-    float *d_batch = nullptr;
-    uint64_t batch_cap = 0;
+    // mc_lya_mlp_train_steps: the index-range flag, and two floats of loss
+    // tail per step
     unsigned int *d_bad = nullptr;
     float *d_tails = nullptr;
     int tails_cap = 0;
     std::string err;
 };
-
-namespace mclya {
-// (kernels_surrogate.hip) rows idx[0..batch) of (X [.][8], t, w) into
-// (Xb, tb, wb); an index outside [0, n_cells) reads row 0 and sets *bad
-hipError_t launch_mlp_gather(const float *X, const float *t, const float *w, uint64_t n_cells, const int64_t *idx,
-                             uint64_t batch, float *Xb, float *tb, float *wb, unsigned int *bad, hipStream_t s);
-}  // namespace mclya
 
 namespace {
 
@@ -63,7 +54,7 @@ mc_lya_status mlp_hip(mc_lya_mlp *m, hipError_t e, const char *what)
 
 void mlp_free(mc_lya_mlp *m)
 {
-    void *ptrs[] = {m->d_params, m->d_m, m->d_v, m->d_grad, m->d_part, m->d_env, m->d_count, m->d_batch, m->d_bad,
+    void *ptrs[] = {m->d_params, m->d_m, m->d_v, m->d_grad, m->d_part, m->d_env, m->d_count, m->d_bad,
                     m->d_tails};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -111,8 +102,7 @@ mc_lya_status mc_lya_mlp_create(mc_lya_mlp **out, const float *params, void *str
     if ((e = hipMalloc(reinterpret_cast<void **>(&m->d_grad), sizeof(float) * (kMlpParams + 2))) != hipSuccess)
         return bail(e, "allocation");
     if ((e = hipMalloc(reinterpret_cast<void **>(&m->d_part),
-                       sizeof(float) * (size_t)(kMlpGradBlocks + (kMlpGradBlocks + 31) / 32) * kMlpPartStride)) !=
-        hipSuccess)
+                       sizeof(float) * (size_t)kMlpGradBlocks * kMlpPartStride)) != hipSuccess)
         return bail(e, "allocation");
     if ((e = hipMalloc(reinterpret_cast<void **>(&m->d_env), sizeof(float) * 16)) != hipSuccess)
         return bail(e, "allocation");
@@ -208,9 +198,9 @@ mc_lya_status mc_lya_mlp_gradient(mc_lya_mlp *m, const float *features, const fl
     mc_lya_status st = check_batch(m, features, n);
     if (st != MC_LYA_OK) return st;
     if (n == 0 || !targets || !weights) return mlp_fail(m, MC_LYA_EINVAL, "need cells, targets and weights");
-    MLP_TRY(m, launch_mlp_gradient(m->d_params, features, targets, weights, n, m->d_part, kMlpGradBlocks,
-                                   m->d_grad, m->stream));
-    MLP_TRY(m, launch_mlp_normalise(m->d_grad, m->stream));
+    const int blocks = launch_mlp_gradient(m->d_params, features, targets, weights, n, nullptr, 0, nullptr, m->d_part,
+                                           m->stream);
+    MLP_TRY(m, launch_mlp_mean_gradient(m->d_part, blocks, m->d_grad, m->stream));
     float tail[2];
     MLP_TRY(m, hipMemcpyAsync(tail, m->d_grad + kMlpParams, sizeof tail, hipMemcpyDeviceToHost, m->stream));
     if (grad) MLP_TRY(m, hipMemcpyAsync(grad, m->d_grad, sizeof(float) * kMlpParams, hipMemcpyDeviceToHost, m->stream));
@@ -230,8 +220,8 @@ mc_lya_status mc_lya_mlp_train_step(mc_lya_mlp *m, const float *features, const 
     if (!hp || !(hp->lr > 0.0f) || !(hp->beta1 >= 0.0f && hp->beta1 < 1.0f) ||
         !(hp->beta2 >= 0.0f && hp->beta2 < 1.0f) || !(hp->eps > 0.0f))
         return mlp_fail(m, MC_LYA_EINVAL, "Adam needs lr > 0, beta1 and beta2 in [0, 1), eps > 0");
-    MLP_TRY(m, launch_mlp_gradient(m->d_params, features, targets, weights, n, m->d_part, kMlpGradBlocks,
-                                   m->d_grad, m->stream));
+    const int blocks = launch_mlp_gradient(m->d_params, features, targets, weights, n, nullptr, 0, nullptr, m->d_part,
+                                           m->stream);
     const int64_t t = m->step + 1;
     MlpAdam a;
     a.lr = hp->lr;
@@ -240,7 +230,7 @@ mc_lya_status mc_lya_mlp_train_step(mc_lya_mlp *m, const float *features, const 
     a.eps = hp->eps;
     a.bc1 = (float)(1.0 - std::pow((double)hp->beta1, (double)t));
     a.bc2 = (float)(1.0 - std::pow((double)hp->beta2, (double)t));
-    MLP_TRY(m, launch_mlp_adam(m->d_params, m->d_m, m->d_v, m->d_grad, a, m->stream));
+    MLP_TRY(m, launch_mlp_adam(m->d_part, blocks, m->d_params, m->d_m, m->d_v, m->d_grad + kMlpParams, a, m->stream));
     m->step = t;
     if (loss) {
         float tail[2];
@@ -268,14 +258,6 @@ mc_lya_status mc_lya_mlp_train_steps(mc_lya_mlp *m, const float *features, const
     for (int s = 0; s < n_steps; ++s)
         if (!(lr[s] > 0.0f)) return mlp_fail(m, MC_LYA_EINVAL, "every learning rate must be > 0");
     if (n_steps == 0) return MC_LYA_OK;
-    if (batch > m->batch_cap) {
-        if (m->d_batch) MLP_TRY(m, hipFree(m->d_batch));
-        m->d_batch = nullptr;
-        m->batch_cap = 0;
-        if (hipMalloc(reinterpret_cast<void **>(&m->d_batch), sizeof(float) * batch * (8 + 2)) != hipSuccess)
-            return mlp_fail(m, MC_LYA_ENOMEM, "device allocation of the gathered batch failed");
-        m->batch_cap = batch;
-    }
     if (!m->d_bad && hipMalloc(reinterpret_cast<void **>(&m->d_bad), sizeof(unsigned int)) != hipSuccess)
         return mlp_fail(m, MC_LYA_ENOMEM, "device allocation failed");
     if (losses && n_steps > m->tails_cap) {
@@ -286,13 +268,10 @@ mc_lya_status mc_lya_mlp_train_steps(mc_lya_mlp *m, const float *features, const
             return mlp_fail(m, MC_LYA_ENOMEM, "device allocation of the losses failed");
         m->tails_cap = n_steps;
     }
-    float *Xb = m->d_batch, *tb = Xb + batch * 8, *wb = tb + batch;    // [batch][8] features, then t, w
     MLP_TRY(m, hipMemsetAsync(m->d_bad, 0, sizeof(unsigned int), m->stream));
     for (int s = 0; s < n_steps; ++s) {
-        MLP_TRY(m, launch_mlp_gather(features, targets, weights, n_cells, idx + (size_t)s * batch, batch, Xb, tb, wb,
-                                     m->d_bad, m->stream));
-        MLP_TRY(m, launch_mlp_gradient(m->d_params, Xb, tb, wb, batch, m->d_part, kMlpGradBlocks, m->d_grad,
-                                       m->stream));
+        const int blocks = launch_mlp_gradient(m->d_params, features, targets, weights, batch, idx + (size_t)s * batch,
+                                               n_cells, m->d_bad, m->d_part, m->stream);
         const int64_t t = m->step + 1;
         MlpAdam a;
         a.lr = lr[s];
@@ -301,11 +280,9 @@ mc_lya_status mc_lya_mlp_train_steps(mc_lya_mlp *m, const float *features, const
         a.eps = eps;
         a.bc1 = (float)(1.0 - std::pow((double)beta1, (double)t));
         a.bc2 = (float)(1.0 - std::pow((double)beta2, (double)t));
-        MLP_TRY(m, launch_mlp_adam(m->d_params, m->d_m, m->d_v, m->d_grad, a, m->stream));
+        MLP_TRY(m, launch_mlp_adam(m->d_part, blocks, m->d_params, m->d_m, m->d_v,
+                                   losses ? m->d_tails + 2 * (size_t)s : m->d_grad + kMlpParams, a, m->stream));
         m->step = t;
-        if (losses)
-            MLP_TRY(m, hipMemcpyAsync(m->d_tails + 2 * (size_t)s, m->d_grad + kMlpParams, 2 * sizeof(float),
-                                      hipMemcpyDeviceToDevice, m->stream));
     }
     unsigned int bad = 0;
     std::vector<float> tails(losses ? 2 * (size_t)n_steps : 0);
@@ -325,15 +302,13 @@ mc_lya_status mc_lya_mlp_train_steps(mc_lya_mlp *m, const float *features, const
 
 // ---- gradient without allocation ---------------------------------------------
 // The workspace of mc_lya_mlp_gradient_static: the gradient kernel's per-block
-// partial sums and the group sums of its fixed-order reduction, in one
-// file-scope device array per GPU (held until the process ends). Host code
+// partial sums, in one file-scope device array per GPU (held until the process ends). Host code
 // never uses the array's name as an address: its device address is looked up
 // once per device with hipGetSymbolAddress and kept below.
 namespace {
 
-constexpr size_t kStaticGradFloats =
-    (size_t)(kMlpGradBlocks + (kMlpGradBlocks + 31) / 32) * kMlpPartStride;
-static_assert(kStaticGradFloats * sizeof(float) == MC_LYA_STATIC_SCRATCH_BYTES, "static workspace size");
+constexpr size_t kStaticGradFloats = MC_LYA_STATIC_SCRATCH_BYTES / sizeof(float);
+static_assert((size_t)kMlpGradBlocks * kMlpPartStride <= kStaticGradFloats, "static workspace size");
 __device__ __align__(256) float scratch[kStaticGradFloats];
 
 constexpr int kMaxDevices = 64;
@@ -384,8 +359,8 @@ mc_lya_status mc_lya_mlp_gradient_static(const float *params, const float *featu
     mc_lya_status st = scratch_address(&ws);
     if (st != MC_LYA_OK) return st;
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    hipError_t e = launch_mlp_gradient(params, features, targets, weights, n, ws, kMlpGradBlocks, grad_out, s);
-    if (e == hipSuccess) e = launch_mlp_normalise(grad_out, s);
+    const int blocks = launch_mlp_gradient(params, features, targets, weights, n, nullptr, 0, nullptr, ws, s);
+    const hipError_t e = launch_mlp_mean_gradient(ws, blocks, grad_out, s);
     if (e != hipSuccess) return static_fail(MC_LYA_EDEVICE, std::string("launch: ") + hipGetErrorString(e));
     return MC_LYA_OK;
 }

@@ -415,7 +415,7 @@ struct FeatBox {
 
 constexpr int kMlpParams = 4801;         // 8-64-64-1 network
 constexpr int kMlpPartStride = 4808;     // floats per block of gradient partial sums (params, sum w r^2, sum w)
-constexpr int kMlpGradBlocks = 1024;     // most blocks of the gradient kernel (partial-sum slots)
+constexpr int kMlpGradBlocks = 512;      // most blocks of the gradient kernel (partial-sum slots): two a compute unit
 
 struct MlpAdam {
     float lr, beta1, beta2, eps;
@@ -428,12 +428,18 @@ hipError_t launch_mlp_forward(const float *params, const float *X, uint64_t n, f
                               hipStream_t s);
 // workgroups of the inference kernel that one compute unit holds at once
 int mlp_forward_blocks_per_cu();
-// partial: [max_blocks + ceil(max_blocks / 32)][kMlpPartStride] floats of workspace
-hipError_t launch_mlp_gradient(const float *params, const float *X, const float *t, const float *w, uint64_t n,
-                               float *partial, int max_blocks, float *grad, hipStream_t s);
-hipError_t launch_mlp_normalise(float *grad, hipStream_t s);
+// The gradient's per-block partial sums over n cells (idx != NULL: rows
+// idx[0..n) of the n_cells rows of X, t, w; an index outside them reads row 0
+// and sets *bad) into partial[blocks][kMlpPartStride], blocks <=
+// kMlpGradBlocks; returns the number of blocks.
+int launch_mlp_gradient(const float *params, const float *X, const float *t, const float *w, uint64_t n,
+                        const int64_t *idx, uint64_t n_cells, unsigned int *bad, float *partial, hipStream_t s);
+// Their sum: the mean gradient, sum w r^2 and sum w into grad[kMlpParams + 2]
+hipError_t launch_mlp_mean_gradient(const float *partial, int blocks, float *grad, hipStream_t s);
+// ... or one Adam step with it, the two sums into tail[2]
+hipError_t launch_mlp_adam(const float *partial, int blocks, float *params, float *m, float *v, float *tail,
+                           const MlpAdam &a, hipStream_t s);
 hipError_t launch_mlp_correction(const float *y, const uint8_t *outside, const float *fallback, uint64_t n,
                                  float *M, hipStream_t s);
-hipError_t launch_mlp_adam(float *params, float *m, float *v, float *grad, const MlpAdam &a, hipStream_t s);
 
 }  // namespace mclya

@@ -536,52 +536,148 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const float *__restric
 // read from the block's LDS.
 //
 // Each block of kGradWaves waves writes the sum of its waves' partial sums
-// (in wave order) to its own slot; two more kernels add the slots in block
+// (in a fixed order) to its own slot; one more kernel adds the slots in a fixed
 // order, so the result does not depend on timing.
-constexpr int kGradWaves = 2;
+//
+// A training step is short (65 536 cells: 1.8 GFLOP, a microsecond on the
+// matrix cores), so what bounds it is the fixed cost of a block and of a
+// launch: the parameters come in through LDS, read once and together (each
+// lane's own strided reads of its operands were a chain of 80), the batch is
+// read through its index list here (IDX) instead of by a gather of its own,
+// and the slots' sum, the normalisation and Adam are one kernel. A step on
+// 65 536 index-picked cells went from 7 launches and 85 us to 2 and 24 us.
+constexpr int kGradWaves = 4;
+
+// The parameters in LDS, each row of W2 one float longer, so that reads down
+// its columns (the operands are gathered so) fall in different banks.
+constexpr int kW2Row = kHid + 1;
+constexpr int kStaged = kMlpParams + kHid;
+__device__ __forceinline__ constexpr int staged(int off) { return off + kHid; }     // past W2
+__device__ __forceinline__ int staged_w2(int o, int k) { return OFF_W2 + o * kW2Row + k; }
+
+// Copies the parameters to LDS: every read issued before the first is stored.
+template <int THREADS>
+__device__ __forceinline__ void stage_params(const float *__restrict__ P, float *lds)
+{
+    constexpr int N = (kMlpParams + THREADS - 1) / THREADS;
+    float v[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const int j = (int)threadIdx.x + k * THREADS;
+        v[k] = j < kMlpParams ? P[j] : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const int j = (int)threadIdx.x + k * THREADS;
+        const int row = j < OFF_W2 ? 0 : (j < OFF_B2 ? (j - OFF_W2) / kHid : kHid);
+        if (j < kMlpParams) lds[j + row] = v[k];
+    }
+}
 
 struct GradLds {
     float w3[kHid];                              // by row, for "C"
-    __bf16 w2[2][5][2][32][8];                   // a2[T][s] of lane (h, c) at [T][s][h][c]
-    __bf16 w2t[2][4][2][32][8];                  // w3[o] W2[o][32 T + c], o = l2_unit(s, h, e), at [T][s][h][c][e]
     union {
         struct {
+            __bf16 w2[2][5][2][32][8];           // a2[T][s] of lane (h, c) at [T][s][h][c]
+            __bf16 w2t[2][4][2][32][8];          // w3[o] W2[o][32 T + c], o = l2_unit(s, h, e), at [T][s][h][c][e]
             __bf16 xs[kGradWaves][kFeat][32];    // the tile's features, [feature][cell]
             float gy[kGradWaves][32];            // dL/dy of the tile's cells
+            float params[kStaged];               // before the tiles: the parameters
         } t;
-        float part[kMlpPartStride];              // another wave's partial sums
+        float part[kGradWaves][kMlpPartStride];  // after them: every wave's sums
     } u;
 };
+static_assert(sizeof(GradLds) <= 80 * 1024, "two blocks a compute unit");
 
+// IDX: cell i of the batch is row idx[i] of the training set of n_cells rows
+// (one outside it is read as row 0 and sets *bad); else row i.
+template <bool IDX>
 __global__ __launch_bounds__(64 * kGradWaves, 2) void mlp_grad_kernel(const float *__restrict__ P,
                                                                       const float *__restrict__ X,
                                                                       const float *__restrict__ tgt,
                                                                       const float *__restrict__ wgt, uint64_t n,
+                                                                      const int64_t *__restrict__ idx,
+                                                                      uint64_t n_cells,
+                                                                      unsigned int *__restrict__ bad,
                                                                       float *__restrict__ partial)
 {
     __shared__ GradLds L;
     const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
-    for (int j = threadIdx.x; j < kHid; j += blockDim.x) L.w3[j] = P[OFF_W3 + j];
-    for (int j = threadIdx.x; j < kHid * kHid; j += blockDim.x) {
-        const int e = j & 7, c = (j >> 3) & 31, h = (j >> 8) & 1, s = (j >> 9) & 3, T = j >> 11;
-        const int o = l2_unit(s, h, e);
-        L.w2t[T][s][h][c][e] = (__bf16)(P[OFF_W3 + o] * P[OFF_W2 + o * kHid + 32 * T + c]);
+    // The batch's rows are read two tiles ahead by index and one by row, the
+    // first of them while the parameters come in.
+    const uint64_t waves = (uint64_t)gridDim.x * kGradWaves;
+    const uint64_t tiles = (n + 31) / 32;
+    const uint64_t tile0 = (uint64_t)blockIdx.x * kGradWaves + wid;
+    auto row_of = [&](uint64_t tile) -> int64_t {
+        const uint64_t cell = tile * 32 + (uint64_t)col;
+        return IDX ? (cell < n ? idx[cell] : 0) : (int64_t)cell;
+    };
+    struct Cell {
+        float4 a, b;
+        float tv, wv;
+    };
+    auto read_cell = [&](uint64_t tile, int64_t row) {
+        Cell c;
+        c.a = c.b = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        c.tv = c.wv = 0.0f;                          // cells past n weigh nothing
+        if (tile * 32 + (uint64_t)col < n) {
+            uint64_t i = (uint64_t)row;
+            if (IDX && i >= n_cells) {               // (a negative index too)
+                atomicOr(bad, 1u);
+                i = 0;
+            }
+            if (half == 0) {
+                c.a = *reinterpret_cast<const float4 *>(X + i * kFeat);
+                c.b = *reinterpret_cast<const float4 *>(X + i * kFeat + 4);
+            }
+            c.tv = tgt[i];
+            c.wv = wgt[i];
+        }
+        return c;
+    };
+    int64_t row = row_of(tile0), row1 = row_of(tile0 + waves);
+    stage_params<64 * kGradWaves>(P, L.u.t.params);
+    __syncthreads();
+    Cell next = read_cell(tile0, row);
+    const float *p = L.u.t.params;
+    if (threadIdx.x < kHid) L.w3[threadIdx.x] = p[staged(OFF_W3) + threadIdx.x];
+    // the layer-2 operands (load_ops), in LDS: registers are short
+    for (int j = threadIdx.x; j < 2 * 5 * 2 * 32; j += blockDim.x) {
+        const int c = j & 31, h = (j >> 5) & 1, q = j >> 6, k = q % 5, T = q / 5, u = 32 * T + c;
+        bf16x8 v;
+        if (k < 4) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = (__bf16)p[staged_w2(u, l2_unit(k, h, e))];
+        } else {
+            v = bias_pair(p[staged(OFF_B2) + u], h == 0);
+        }
+        *reinterpret_cast<bf16x8 *>(&L.u.t.w2[T][k][h][c][0]) = v;
     }
-    // the weight operands: layer 1 in registers, layer 2 in LDS (read as
-    // needed; registers are short)
-    NetOps o;
-    load_ops(P, half, col, o);
+    for (int j = threadIdx.x; j < 2 * 4 * 2 * 32; j += blockDim.x) {
+        const int c = j & 31, h = (j >> 5) & 1, k = (j >> 6) & 3, T = j >> 8;
+        bf16x8 v;
 #pragma unroll
-    for (int T = 0; T < 2; ++T)
+        for (int e = 0; e < 8; ++e) {
+            const int o = l2_unit(k, h, e);
+            v[e] = (__bf16)(p[staged(OFF_W3) + o] * p[staged_w2(o, 32 * T + c)]);
+        }
+        *reinterpret_cast<bf16x8 *>(&L.u.t.w2t[T][k][h][c][0]) = v;
+    }
+    bf16x8 a1[2];                                // layer 1, in registers
 #pragma unroll
-        for (int s = 0; s < 5; ++s)
-            if (wid == 0) *reinterpret_cast<bf16x8 *>(&L.w2[T][s][half][col][0]) = o.a2[T][s];
+    for (int T = 0; T < 2; ++T) {
+        const int u = 32 * T + col;
+        if (half == 0) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a1[T][e] = (__bf16)p[OFF_W1 + u * kFeat + e];
+        } else {
+            a1[T] = bias_pair(p[OFF_B1 + u], true);
+        }
+    }
+    const float w3h[2] = {p[staged(OFF_W3) + col], p[staged(OFF_W3) + 32 + col]};    // unit 32 T + col, for "H"
+    const float b3 = p[staged(OFF_B3)];
     const bf16x8 ones = ones_pair(half == 0);
-    auto a2 = [&](int T, int s) { return *reinterpret_cast<const bf16x8 *>(&L.w2[T][s][half][col][0]); };
-    float w3h[2];                                // unit 32 T + col, for "H"
-    w3h[0] = P[OFF_W3 + col];
-    w3h[1] = P[OFF_W3 + 32 + col];
-    const float b3 = P[OFF_B3];
+    auto a2 = [&](int T, int s) { return *reinterpret_cast<const bf16x8 *>(&L.u.t.w2[T][s][half][col][0]); };
     f32x16 gW2[2][2], gW1[2];
 #pragma unroll
     for (int T = 0; T < 2; ++T) {
@@ -594,29 +690,15 @@ __global__ __launch_bounds__(64 * kGradWaves, 2) void mlp_grad_kernel(const floa
 
     __bf16(*xs)[32] = L.u.t.xs[wid];
     float *gys = L.u.t.gy[wid];
-    const uint64_t waves = (uint64_t)gridDim.x * kGradWaves;
-    const uint64_t tiles = (n + 31) / 32;
-    for (uint64_t tile = (uint64_t)blockIdx.x * kGradWaves + wid; tile < tiles; tile += waves) {
+    for (uint64_t tile = tile0; tile < tiles; tile += waves) {
         // the LDS tables are read in each tile, not held in registers across
         // tiles (the compiler may not hoist them past this)
         asm volatile("" ::: "memory");
-        const uint64_t cell = tile * 32 + (uint64_t)col;
-        const bool valid = cell < n;
-        float x[kFeat];
-        float tv = 0.0f, wv = 0.0f;                  // cells past n weigh nothing
-        {
-            float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f), b = a;
-            if (half == 0 && valid) {
-                a = *reinterpret_cast<const float4 *>(X + cell * kFeat);
-                b = *reinterpret_cast<const float4 *>(X + cell * kFeat + 4);
-            }
-            if (valid) {
-                tv = tgt[cell];
-                wv = wgt[cell];
-            }
-            x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
-            x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
-        }
+        const Cell cur = next;
+        next = read_cell(tile + waves, row1);
+        row1 = row_of(tile + 2 * waves);
+        const float tv = cur.tv, wv = cur.wv;
+        const float x[kFeat] = {cur.a.x, cur.a.y, cur.a.z, cur.a.w, cur.b.x, cur.b.y, cur.b.z, cur.b.w};
         const bf16x8 bx = feature_operand(x, half);
         if (half == 0)
 #pragma unroll
@@ -627,7 +709,7 @@ __global__ __launch_bounds__(64 * kGradWaves, 2) void mlp_grad_kernel(const floa
         {
             f32x16 d1[2];
 #pragma unroll
-            for (int T = 0; T < 2; ++T) d1[T] = mfma16(o.a1[T], bx, zero16());
+            for (int T = 0; T < 2; ++T) d1[T] = mfma16(a1[T], bx, zero16());
             hidden_operand(d1, h1c);
         }
         bf16x8 gzc[4];                 // dL/dz2 / w3, K operand of dL/dh1 (unit l2_unit(s, half, e))
@@ -672,7 +754,7 @@ __global__ __launch_bounds__(64 * kGradWaves, 2) void mlp_grad_kernel(const floa
             gh1[T] = zero16();
 #pragma unroll
             for (int s = 0; s < 4; ++s)
-                gh1[T] = mfma16(gzc[s], *reinterpret_cast<const bf16x8 *>(&L.w2t[T][s][half][col][0]), gh1[T]);
+                gh1[T] = mfma16(gzc[s], *reinterpret_cast<const bf16x8 *>(&L.u.t.w2t[T][s][half][col][0]), gh1[T]);
         }
 
         // X^T (feature per lane, element e of K step s' = cell
@@ -701,7 +783,7 @@ __global__ __launch_bounds__(64 * kGradWaves, 2) void mlp_grad_kernel(const floa
         bf16x8 h1h[2][2];
 #pragma unroll
         for (int T = 0; T < 2; ++T) {
-            const f32x16 d = mfma16(bx, o.a1[T], zero16());
+            const f32x16 d = mfma16(bx, a1[T], zero16());
             bf16x8 gz1[2];
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
@@ -752,8 +834,7 @@ __global__ __launch_bounds__(64 * kGradWaves, 2) void mlp_grad_kernel(const floa
         loss += __shfl_down(loss, off, 64);
         wsum += __shfl_down(wsum, off, 64);
     }
-    // Every lane visits the entries it owns in the same order in every wave,
-    // and the waves are added in index order through LDS.
+    // Every lane writes the entries it owns; the waves are added in order.
     auto visit = [&](auto &&f) {
 #pragma unroll
         for (int To = 0; To < 2; ++To)
@@ -784,54 +865,68 @@ __global__ __launch_bounds__(64 * kGradWaves, 2) void mlp_grad_kernel(const floa
             f(kMlpParams + 1, wsum);
         }
     };
-    __syncthreads();                                  // staging no longer in use
-    for (int w = kGradWaves - 1; w > 0; --w) {
-        if (wid == w) visit([&](int j, float v) { L.u.part[j] = (w == kGradWaves - 1 ? 0.0f : L.u.part[j]) + v; });
-        __syncthreads();
+    __syncthreads();                                  // the tables are no longer in use
+    visit([&](int j, float v) { L.u.part[wid][j] = v; });
+    __syncthreads();
+    float *out = partial + (size_t)blockIdx.x * kMlpPartStride;
+#pragma unroll 5
+    for (int k = 0; k < (kMlpParams + 2 + 64 * kGradWaves - 1) / (64 * kGradWaves); ++k) {
+        const int j = (int)threadIdx.x + k * 64 * kGradWaves;
+        if (j >= kMlpParams + 2) break;
+        float v = L.u.part[0][j];
+#pragma unroll
+        for (int w = 1; w < kGradWaves; ++w) v += L.u.part[w][j];
+        out[j] = v;
     }
-    if (wid == 0) {
-        float *p = partial + (size_t)blockIdx.x * kMlpPartStride;
-        visit([&](int j, float v) { p[j] = kGradWaves > 1 ? v + L.u.part[j] : v; });
+}
+
+// The sum over blocks of partial[b][j], j < kMlpParams + 2 (the last two
+// columns are sum w r^2 and sum w), divided by sum w. A workgroup takes 64
+// columns; its 16 waves each add a run of consecutive blocks, and the runs are
+// added in order (a fixed order). Every workgroup forms sum w for itself.
+// ADAM: one Adam step with the mean gradient (Kingma & Ba 2015, Algorithm 1,
+// with bias correction; step counts from 1), the two sums to tail[0..1];
+// else the mean gradient and the two sums to grad.
+constexpr int kRedWaves = 16;
+
+template <bool ADAM>
+__global__ __launch_bounds__(64 * kRedWaves) void mlp_reduce_kernel(const float *__restrict__ partial, int blocks,
+                                                                    float *__restrict__ grad, float *__restrict__ P,
+                                                                    float *__restrict__ m, float *__restrict__ v,
+                                                                    float *__restrict__ tail, MlpAdam a)
+{
+    __shared__ float s_run[kRedWaves][64];
+    __shared__ float s_w[kRedWaves];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int j = blockIdx.x * 64 + lane;
+    const int b0 = blocks * wid / kRedWaves, b1 = blocks * (wid + 1) / kRedWaves;
+    float s = 0.0f, w = 0.0f;
+    if (j < kMlpParams + 2)
+#pragma unroll 8
+        for (int b = b0; b < b1; ++b) s += partial[(size_t)b * kMlpPartStride + j];
+    for (int b = b0 + lane; b < b1; b += 64) w += partial[(size_t)b * kMlpPartStride + kMlpParams + 1];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) w += __shfl_down(w, off, 64);
+    s_run[wid][lane] = s;
+    if (lane == 0) s_w[wid] = w;
+    __syncthreads();
+    if (wid != 0 || j >= kMlpParams + 2) return;
+    float sum = 0.0f, wsum = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kRedWaves; ++k) {
+        sum += s_run[k][lane];
+        wsum += s_w[k];
     }
-}
-
-// grad[j] = sum over blocks of partial[b][j], j < kMlpParams + 2 (the last
-// two entries are sum w r^2 and sum w), in two fixed-order passes: groups of
-// kMlpGroup consecutive blocks into tmp[g][j], then the groups in order.
-constexpr int kMlpGroup = 32;
-
-__global__ __launch_bounds__(256) void mlp_reduce_groups_kernel(const float *__restrict__ partial, int blocks,
-                                                                float *__restrict__ tmp)
-{
-    const int j = blockIdx.x * 256 + threadIdx.x, g = blockIdx.y;
-    if (j >= kMlpParams + 2) return;
-    float s = 0.0f;
-    const int b1 = min(blocks, (g + 1) * kMlpGroup);
-    for (int b = g * kMlpGroup; b < b1; ++b) s += partial[(size_t)b * kMlpPartStride + j];
-    tmp[(size_t)g * kMlpPartStride + j] = s;
-}
-
-__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float *__restrict__ tmp, int groups,
-                                                         float *__restrict__ grad)
-{
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= kMlpParams + 2) return;
-    float s = 0.0f;
-    for (int g = 0; g < groups; ++g) s += tmp[(size_t)g * kMlpPartStride + j];
-    grad[j] = s;
-}
-
-// Normalise by sum w and take one Adam step (Kingma & Ba 2015, Algorithm 1,
-// with bias correction); step counts from 1.
-__global__ __launch_bounds__(256) void mlp_adam_kernel(float *__restrict__ P, float *__restrict__ m,
-                                                       float *__restrict__ v, float *__restrict__ grad,
-                                                       MlpAdam a)
-{
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= kMlpParams) return;
-    const float wsum = grad[kMlpParams + 1];
-    const float g = wsum > 0.0f ? grad[j] / wsum : 0.0f;
-    grad[j] = g;
+    if (j >= kMlpParams) {
+        if (ADAM) tail[j - kMlpParams] = sum;
+        else grad[j] = sum;
+        return;
+    }
+    const float g = wsum > 0.0f ? sum / wsum : 0.0f;
+    if (!ADAM) {
+        grad[j] = g;
+        return;
+    }
     const float mj = a.beta1 * m[j] + (1.0f - a.beta1) * g;
     const float vj = a.beta2 * v[j] + (1.0f - a.beta2) * g * g;
     m[j] = mj;
@@ -851,14 +946,6 @@ __global__ __launch_bounds__(256) void mlp_correction_kernel(const float *__rest
     if (i >= n) return;
     const bool mc = fallback && outside && outside[i];
     M[i] = mc ? fallback[i] : expf(y[i]);
-}
-
-__global__ __launch_bounds__(256) void mlp_normalise_kernel(float *__restrict__ grad)
-{
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= kMlpParams) return;
-    const float wsum = grad[kMlpParams + 1];
-    grad[j] = wsum > 0.0f ? grad[j] / wsum : 0.0f;
 }
 
 }  // namespace
@@ -885,51 +972,38 @@ int mlp_forward_blocks_per_cu()
     return b;
 }
 
-hipError_t launch_mlp_gradient(const float *params, const float *X, const float *t, const float *w, uint64_t n,
-                               float *partial, int max_blocks, float *grad, hipStream_t s)
+int launch_mlp_gradient(const float *params, const float *X, const float *t, const float *w, uint64_t n,
+                        const int64_t *idx, uint64_t n_cells, unsigned int *bad, float *partial, hipStream_t s)
 {
-    // as many blocks as give every wave kGradMinTiles tiles, up to max_blocks:
-    // fewer partial-sum slots to add for small batches (the count is a
-    // function of n alone, so the summation order is too)
-    constexpr uint64_t kGradMinTiles = 4;
-    const uint64_t tiles = (n + 31) / 32;
-    const int blocks = (int)std::max<uint64_t>(
-        1, std::min<uint64_t>((uint64_t)max_blocks, tiles / (kGradWaves * kGradMinTiles)));
-    const int groups = (blocks + kMlpGroup - 1) / kMlpGroup;
-    float *tmp = partial + (size_t)blocks * kMlpPartStride;
-    hipLaunchKernelGGL(mlp_grad_kernel, dim3((unsigned)blocks), dim3(64 * kGradWaves), 0, s, params, X, t, w, n,
-                       partial);
-    hipLaunchKernelGGL(mlp_reduce_groups_kernel, dim3((unsigned)((kMlpParams + 2 + 255) / 256), (unsigned)groups),
-                       dim3(256), 0, s, partial, blocks, tmp);
-    hipLaunchKernelGGL(mlp_reduce_kernel, dim3((unsigned)((kMlpParams + 2 + 255) / 256)), dim3(256), 0, s, tmp,
-                       groups, grad);
+    // Two tiles a wave, up to one block a compute unit, then up to
+    // kMlpGradBlocks (two a unit) of longer runs: fewer partial-sum slots to
+    // add for small batches. The count is a function of n alone, so the
+    // summation order is too.
+    const uint64_t tiles = (n + 31) / 32, per = 2 * kGradWaves;
+    const int blocks = (int)std::max<uint64_t>(1, std::min<uint64_t>(kMlpGradBlocks, (tiles + per - 1) / per));
+    if (idx)
+        hipLaunchKernelGGL(mlp_grad_kernel<true>, dim3((unsigned)blocks), dim3(64 * kGradWaves), 0, s, params, X, t,
+                           w, n, idx, n_cells, bad, partial);
+    else
+        hipLaunchKernelGGL(mlp_grad_kernel<false>, dim3((unsigned)blocks), dim3(64 * kGradWaves), 0, s, params, X, t,
+                           w, n, idx, n_cells, bad, partial);
+    return blocks;
+}
+
+constexpr unsigned kRedGrid = (kMlpParams + 2 + 63) / 64;
+
+hipError_t launch_mlp_mean_gradient(const float *partial, int blocks, float *grad, hipStream_t s)
+{
+    hipLaunchKernelGGL(mlp_reduce_kernel<false>, dim3(kRedGrid), dim3(64 * kRedWaves), 0, s, partial, blocks, grad,
+                       nullptr, nullptr, nullptr, nullptr, MlpAdam{});
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void mlp_gather_kernel(const float *__restrict__ X, const float *__restrict__ t,
-                                                         const float *__restrict__ w, uint64_t n_cells,
-                                                         const int64_t *__restrict__ idx, uint64_t batch,
-                                                         float *__restrict__ Xb, float *__restrict__ tb,
-                                                         float *__restrict__ wb, unsigned int *__restrict__ bad)
+hipError_t launch_mlp_adam(const float *partial, int blocks, float *params, float *m, float *v, float *tail,
+                           const MlpAdam &a, hipStream_t s)
 {
-    const uint64_t i = (uint64_t)blockIdx.x * 256u + threadIdx.x;
-    if (i >= batch) return;
-    int64_t c = idx[i];
-    if (c < 0 || (uint64_t)c >= n_cells) {
-        atomicOr(bad, 1u);
-        c = 0;
-    }
-#pragma unroll
-    for (int e = 0; e < kFeat; ++e) Xb[i * kFeat + e] = X[(uint64_t)c * kFeat + e];
-    tb[i] = t[c];
-    wb[i] = w[c];
-}
-
-hipError_t launch_mlp_gather(const float *X, const float *t, const float *w, uint64_t n_cells, const int64_t *idx,
-                             uint64_t batch, float *Xb, float *tb, float *wb, unsigned int *bad, hipStream_t s)
-{
-    hipLaunchKernelGGL(mlp_gather_kernel, dim3((unsigned)((batch + 255) / 256)), dim3(256), 0, s, X, t, w, n_cells,
-                       idx, batch, Xb, tb, wb, bad);
+    hipLaunchKernelGGL(mlp_reduce_kernel<true>, dim3(kRedGrid), dim3(64 * kRedWaves), 0, s, partial, blocks, nullptr,
+                       params, m, v, tail, a);
     return hipGetLastError();
 }
 
@@ -938,19 +1012,6 @@ hipError_t launch_mlp_correction(const float *y, const uint8_t *outside, const f
 {
     hipLaunchKernelGGL(mlp_correction_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, y, outside,
                        fallback, n, M);
-    return hipGetLastError();
-}
-
-hipError_t launch_mlp_normalise(float *grad, hipStream_t s)
-{
-    hipLaunchKernelGGL(mlp_normalise_kernel, dim3((unsigned)((kMlpParams + 255) / 256)), dim3(256), 0, s, grad);
-    return hipGetLastError();
-}
-
-hipError_t launch_mlp_adam(float *params, float *m, float *v, float *grad, const MlpAdam &a, hipStream_t s)
-{
-    hipLaunchKernelGGL(mlp_adam_kernel, dim3((unsigned)((kMlpParams + 255) / 256)), dim3(256), 0, s, params, m, v,
-                       grad, a);
     return hipGetLastError();
 }
 
