@@ -317,6 +317,12 @@ def _check_mlp(status, mlp=None):
     return status
 
 
+def _floats(arr):
+    """A ctypes float array as a list of floats (a buffer's tolist: a third of
+    the time of list(arr) for the network's 4801)."""
+    return memoryview(arr).cast("B").cast("f").tolist()
+
+
 def mc_lya_mlp_create(params, stream=None):
     """params: sequence of MC_LYA_MLP_PARAMS floats; returns the handle."""
     L = load()
@@ -331,7 +337,7 @@ def mc_lya_mlp_create(params, stream=None):
 def mc_lya_mlp_get_params(mlp):
     arr = (C.c_float * MC_LYA_MLP_PARAMS)()
     _check_mlp(load().mc_lya_mlp_get_params(mlp, arr), mlp)
-    return list(arr)
+    return _floats(arr)
 
 
 def mc_lya_mlp_set_envelope(mlp, lo, hi):
@@ -358,7 +364,7 @@ def mc_lya_mlp_gradient(mlp, feat_ptr, t_ptr, w_ptr, n):
     g = (C.c_float * MC_LYA_MLP_PARAMS)()
     loss = C.c_float()
     _check_mlp(load().mc_lya_mlp_gradient(mlp, feat_ptr, t_ptr, w_ptr, int(n), g, C.byref(loss)), mlp)
-    return list(g), loss.value
+    return _floats(g), loss.value
 
 
 def mc_lya_mlp_train_step(mlp, feat_ptr, t_ptr, w_ptr, n, lr, beta1=0.9, beta2=0.999, eps=1e-8, want_loss=False):

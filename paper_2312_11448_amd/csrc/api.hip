@@ -112,6 +112,21 @@ struct mc_lya_ctx {
     bool voigt = false;                      // some box has the Voigt profile
     int num_cu = 256;
 
+    // Every device buffer but the tiled walk's packet states is a part of one
+    // allocation, d_all. Tables that travel together lie together: d_walk and
+    // d_redbox up, d_tot, d_boxabs and d_fsum down.
+    void *d_all = nullptr;
+    // Pinned host memory behind the copies: `up` holds what emit, feed and the
+    // history upload (rewritten only when nothing reads it any more), `down`
+    // what is read back.
+    char *pin = nullptr;
+    WalkBox *up_walk = nullptr;              // then the RedBox table
+    FeedBox *up_feed = nullptr;
+    double *up_coef = nullptr;
+    PackBox *up_pack = nullptr;
+    char *down = nullptr;
+    bool up_busy = false;                    // emit's upload may still be in flight
+
     PackBox *d_pack = nullptr;
     WalkBox *d_walk = nullptr;
     BoxRed *d_red = nullptr;
@@ -133,6 +148,7 @@ struct mc_lya_ctx {
     double *d_fsum = nullptr;
     FeedBox *d_feed = nullptr;
     uint32_t *d_cop = nullptr;               // [max_packets] cell of each packet
+    bool queue_clear = false;    // the persistent walk's work counters are zero
     bool cop_valid = false;      // d_cop holds the cells of the current emission
     uint64_t *d_pfirst = nullptr;
 
@@ -211,6 +227,21 @@ mc_lya_status hip_fail(mc_lya_ctx *c, hipError_t e, const char *what)
     return e == hipErrorOutOfMemory ? MC_LYA_ENOMEM : MC_LYA_EDEVICE;
 }
 
+// Waits for the context's stream.
+hipError_t wait(mc_lya_ctx *c)
+{
+    const hipError_t e = hipStreamSynchronize(c->stream);
+    if (e == hipSuccess) c->up_busy = false;
+    return e;
+}
+
+// Reads n bytes at `from` into c->down and waits for them.
+hipError_t read_back(mc_lya_ctx *c, const void *from, size_t n)
+{
+    const hipError_t e = hipMemcpyAsync(c->down, from, n, hipMemcpyDeviceToHost, c->stream);
+    return e == hipSuccess ? wait(c) : e;
+}
+
 #define HIP_TRY(ctx, expr)                                           \
     do {                                                             \
         hipError_t e_ = (expr);                                      \
@@ -230,12 +261,8 @@ void free_all(mc_lya_ctx *c)
     if (c->join) (void)hipEventDestroy(c->join);
     c->side = nullptr;
     c->fork = c->join = nullptr;
-    void *ptrs[] = {c->d_pack, c->d_walk, c->d_red, c->d_tot, c->d_redbox, c->d_share, c->d_rec, c->d_wgt, c->d_part, c->d_q,
-                    c->d_bsum, c->d_npk, c->d_A, c->d_queue, c->d_boxabs, c->d_fsum, c->d_feed,
-                    c->d_cop, c->d_pfirst, c->d_seg, c->d_featbox, c->d_tail_prefix, c->d_tiles, c->d_texits[0], c->d_texits[1], c->d_sbox, c->d_ev, c->d_ev_coef,
-                    c->d_gen};
-    for (void *p : ptrs)
-        if (p) (void)hipFree(p);
+    if (c->d_all) (void)hipFree(c->d_all);
+    if (c->pin) (void)hipHostFree(c->pin);
     free_tile_buffers(c);
     for (auto &ev : c->events) {
         (void)hipEventDestroy(ev.first);
@@ -340,15 +367,13 @@ double crossings_per_packet(double kappa, double delta, double x_eff, double w0)
 mc_lya_status do_refresh(mc_lya_ctx *c)
 {
     const int nb = c->n_boxes;
-    HIP_TRY(c, hipMemsetAsync(c->d_red, 0, sizeof(BoxRed) * nb, c->stream));
-    HIP_TRY(c, launch_pack(c->d_pack, nb, c->max_blk, c->vel, c->d_rec, c->d_wgt, c->d_part, c->d_red,
-                           c->stream));
+    HIP_TRY(c, launch_pack(c->d_pack, nb, c->max_blk, c->vel, c->d_rec, c->d_wgt, c->d_part, c->stream));
     HIP_TRY(c, launch_box_reduce(c->d_pack, nb, c->max_blk, c->d_part, c->d_red, c->stream));
     if (c->vel)
         HIP_TRY(c, launch_margin(c->d_pack, nb, c->max_blk, static_cast<const float4 *>(c->d_rec), c->d_red,
                                  c->d_part, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(c->red.data(), c->d_red, sizeof(BoxRed) * nb, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    HIP_TRY(c, read_back(c, c->d_red, sizeof(BoxRed) * nb));
+    std::memcpy(c->red.data(), c->down, sizeof(BoxRed) * nb);
     c->featbox_stale = true;                 // the box clumping comes from these sums
     for (int b = 0; b < nb; ++b) {
         const uint32_t f = c->red[b].flags;
@@ -730,12 +755,12 @@ mc_lya_status enqueue_red_list(mc_lya_ctx *c, uint64_t n, int gen, bool timed)
     return MC_LYA_OK;
 }
 
-// Packets still crossing tiles after generation gen - 1 (synchronises).
+// Packets still crossing tiles after generation gen - 1 (synchronises); the
+// counters of every generation before are left in c->down.
 mc_lya_status exits_after(mc_lya_ctx *c, int gen, unsigned long long *exits)
 {
-    HIP_TRY(c, hipMemcpyAsync(exits, c->d_gen + 2 * (gen - 1) + 1, sizeof *exits, hipMemcpyDeviceToHost,
-                              c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    HIP_TRY(c, read_back(c, c->d_gen, sizeof(unsigned long long) * 2 * (size_t)gen));
+    *exits = reinterpret_cast<const unsigned long long *>(c->down)[2 * (gen - 1) + 1];
     return MC_LYA_OK;
 }
 
@@ -787,18 +812,16 @@ mc_lya_status walk_tiled(mc_lya_ctx *c, uint64_t first, uint64_t count)
         if (st == MC_LYA_OK && end > g1) st = enqueue_tail(c, n, true);
         if (st == MC_LYA_OK && end > g1) st = enqueue_red_list(c, n, end, true);
         if (st != MC_LYA_OK) return st;
-        // the last generation that still handed packets on
-        std::vector<unsigned long long> cnt(2 * (size_t)end);
-        HIP_TRY(c, hipMemcpyAsync(cnt.data(), c->d_gen, sizeof(unsigned long long) * cnt.size(),
-                                  hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        // the last generation that still handed packets on (the counters that
+        // the last check read)
+        const unsigned long long *cnt = reinterpret_cast<const unsigned long long *>(c->down);
         int last = 0;
         for (int g = 0; g < end; ++g)
             if (cnt[2 * g + 1]) last = g;
         needed = std::max(needed, last + 2);
         done += n;
     }
-    c->eager_gens = needed + 4;
+    c->eager_gens = needed + 2;
     return MC_LYA_OK;
 }
 
@@ -809,8 +832,11 @@ mc_lya_status ensure_cell_of_packet(mc_lya_ctx *c)
 {
     if (c->cop_valid) return MC_LYA_OK;
     const uint64_t ntot = c->total_packets;
-    if (ntot) HIP_TRY(c, launch_cell_of_packet(c->d_pack, c->n_boxes, c->max_blk, c->d_npk, c->d_pfirst, c->d_cop,
-                                               c->stream));
+    if (ntot) {
+        HIP_TRY(c, launch_cell_of_packet(c->d_pack, c->n_boxes, c->max_blk, c->d_npk, c->d_pfirst, c->d_cop,
+                                         c->d_queue, c->stream));
+        c->queue_clear = true;
+    }
     c->cop_valid = true;
     return MC_LYA_OK;
 }
@@ -1065,6 +1091,7 @@ mc_lya_status launch_walk(mc_lya_ctx *c, uint64_t first, uint64_t count)
         if (w.tiled) st = walk_tiled(c, first, count);
         if (st == MC_LYA_OK && w.global) st = launch_global_walk(c, w.p, true);
     }
+    if (w.global) c->queue_clear = false;    // (a replayed graph's walk too)
     if (st == MC_LYA_OK && coarse_end) st = timed_end(c, coarse_end);
     if (st != MC_LYA_OK) return st;
     account_walked(c, first, count, c->kernel == 2);
@@ -1090,7 +1117,8 @@ mc_lya_status launch_global_walk(mc_lya_ctx *c, const WalkParams &p, bool timed,
         const int grid = (int)std::min<uint64_t>((uint64_t)c->num_cu, (waves + per - 1) / per);
         q.chunk = 64;
         q.nqueues = 1;
-        HIP_TRY(c, launch_walk_box(q, c->total_cells, 64 * per, grid, c->stream));
+        HIP_TRY(c, launch_walk_box(q, c->total_cells, 64 * per, grid, !c->queue_clear || !timed, c->stream));
+        c->queue_clear = false;
     } else {
         const int waves_per_block = c->block / 64;
         // never more workgroups than can be resident at once
@@ -1105,7 +1133,8 @@ mc_lya_status launch_global_walk(mc_lya_ctx *c, const WalkParams &p, bool timed,
         WalkParams q = p;
         const uint64_t each = count / ((uint64_t)grid * waves_per_block);
         q.chunk = (int32_t)std::min<uint64_t>((uint64_t)p.chunk, std::max<uint64_t>(64, each));
-        HIP_TRY(c, launch_walk_persistent(q, c->block, grid, c->stream));
+        HIP_TRY(c, launch_walk_persistent(q, c->block, grid, !c->queue_clear || !timed, c->stream));
+        c->queue_clear = false;
     }
     if (timed) return timed_end(c, e1);
     return MC_LYA_OK;
@@ -1213,24 +1242,6 @@ mc_lya_status mc_lya_init(mc_lya_ctx **out, const mc_lya_box_desc *boxes, int32_
         return s;
     };
     const size_t nbk = (size_t)n_boxes * max_blk;
-    hipError_t e = hipSuccess;
-    if ((e = dalloc(&c->d_pack, n_boxes)) != hipSuccess || (e = dalloc(&c->d_walk, n_boxes)) != hipSuccess ||
-        (e = dalloc(&c->d_red, n_boxes)) != hipSuccess || (e = dalloc(&c->d_tot, n_boxes)) != hipSuccess ||
-        (e = dalloc(&c->d_redbox, n_boxes)) != hipSuccess ||
-        (e = hipMalloc(&c->d_rec, cells * (c->vel ? sizeof(float4) : sizeof(float)))) != hipSuccess ||
-        (e = dalloc(&c->d_wgt, cells)) != hipSuccess || (e = dalloc(&c->d_part, nbk * kPartStride)) != hipSuccess ||
-        (e = dalloc(&c->d_q, cells)) != hipSuccess || (e = dalloc(&c->d_bsum, nbk)) != hipSuccess ||
-        (e = dalloc(&c->d_npk, cells)) != hipSuccess || (e = dalloc(&c->d_A, cells)) != hipSuccess ||
-        (e = dalloc(&c->d_queue, kMaxQueues)) != hipSuccess || (e = dalloc(&c->d_boxabs, n_boxes)) != hipSuccess ||
-        (e = dalloc(&c->d_fsum, (size_t)4 * n_boxes)) != hipSuccess ||
-        (e = dalloc(&c->d_feed, n_boxes)) != hipSuccess || (e = dalloc(&c->d_pfirst, cells)) != hipSuccess ||
-        (e = dalloc(&c->d_seg, 2 * ((size_t)n_boxes + 1))) != hipSuccess ||
-        (e = dalloc(&c->d_featbox, n_boxes)) != hipSuccess || (e = dalloc(&c->d_sbox, n_boxes)) != hipSuccess ||
-        (e = dalloc(&c->d_cop, lim.max_packets)) != hipSuccess ||
-        (lim.evolve && ((e = dalloc(&c->d_ev, 6 * cells)) != hipSuccess ||
-                        (e = dalloc(&c->d_ev_coef, (size_t)n_boxes)) != hipSuccess)) ||
-        (e = alloc_tile_buffers(c, lim.batch_packets)) != hipSuccess)
-        return cleanup(e == hipErrorOutOfMemory ? MC_LYA_ENOMEM : MC_LYA_EDEVICE);
     c->cpp.assign(n_boxes, 1.0);
     c->tiled.assign(n_boxes, 1);         // the tile table starts with every box; emit narrows it
     build_tiles(c);
@@ -1238,16 +1249,76 @@ mc_lya_status mc_lya_init(mc_lya_ctx **out, const mc_lya_box_desc *boxes, int32_
     // (a lone box with few tiles: room for its tiles shared among the chip's workgroups)
     const size_t nt = n_boxes == 1 ? std::max<size_t>(nt0, (size_t)c->num_cu) : nt0;
     c->share_cells = (nt - nt0) * (size_t)kTileCells;
-    if (c->share_cells) {
-        if ((e = dalloc(&c->d_share, c->share_cells)) != hipSuccess)
-            return cleanup(e == hipErrorOutOfMemory ? MC_LYA_ENOMEM : MC_LYA_EDEVICE);
-        if (hipMemsetAsync(c->d_share, 0, sizeof(unsigned long long) * c->share_cells, c->stream) != hipSuccess)
-            return cleanup(MC_LYA_EDEVICE);
-    }
-    if ((e = dalloc(&c->d_tiles, nt)) != hipSuccess || (e = dalloc(&c->d_texits[0], nt)) != hipSuccess ||
-        (e = dalloc(&c->d_texits[1], nt)) != hipSuccess || (e = dalloc(&c->d_gen, kGenCounters)) != hipSuccess ||
-        (e = dalloc(&c->d_tail_prefix, nt)) != hipSuccess)
+    // the buffers' places in d_all (and, second time round, their addresses)
+    const size_t nb = (size_t)n_boxes;
+    size_t bytes = 0;
+    auto place = [&](auto **q, size_t n) {
+        if (c->d_all) *q = reinterpret_cast<std::remove_reference_t<decltype(*q)>>(static_cast<char *>(c->d_all) + bytes);
+        bytes += (std::max<size_t>(1, n) * sizeof(**q) + 255) / 256 * 256;
+    };
+    auto place_all = [&] {
+        bytes = 0;
+        char *rec = nullptr, *walk = nullptr, *tot = nullptr;
+        place(&c->d_pack, nb);
+        place(&walk, nb * (sizeof(WalkBox) + sizeof(RedBox)));
+        c->d_walk = reinterpret_cast<WalkBox *>(walk);
+        c->d_redbox = reinterpret_cast<RedBox *>(c->d_walk + nb);
+        place(&tot, nb * (sizeof(BoxTot) + sizeof(unsigned long long) + 4 * sizeof(double)));
+        c->d_tot = reinterpret_cast<BoxTot *>(tot);
+        c->d_boxabs = reinterpret_cast<unsigned long long *>(c->d_tot + nb);
+        c->d_fsum = reinterpret_cast<double *>(c->d_boxabs + nb);
+        place(&c->d_red, nb);
+        place(&c->d_queue, (size_t)kMaxQueues);
+        place(&c->d_feed, nb);
+        place(&c->d_seg, 2 * (nb + 1));
+        place(&c->d_featbox, nb);
+        place(&c->d_sbox, nb);
+        place(&c->d_gen, (size_t)kGenCounters);
+        place(&c->d_tiles, nt);
+        place(&c->d_texits[0], nt);
+        place(&c->d_texits[1], nt);
+        place(&c->d_tail_prefix, nt);
+        place(&c->d_part, nbk * kPartStride);
+        place(&c->d_bsum, nbk);
+        place(&rec, cells * (c->vel ? sizeof(float4) : sizeof(float)));
+        c->d_rec = rec;
+        place(&c->d_wgt, cells);
+        place(&c->d_q, cells);
+        place(&c->d_npk, cells);
+        place(&c->d_A, cells);
+        place(&c->d_pfirst, cells);
+        place(&c->d_cop, lim.max_packets);
+        if (c->share_cells) place(&c->d_share, c->share_cells);
+        if (lim.evolve) {
+            place(&c->d_ev, 6 * cells);
+            place(&c->d_ev_coef, nb);
+        }
+    };
+    place_all();
+    hipError_t e = hipMalloc(&c->d_all, bytes);
+    if (e != hipSuccess) {
+        c->d_all = nullptr;
         return cleanup(e == hipErrorOutOfMemory ? MC_LYA_ENOMEM : MC_LYA_EDEVICE);
+    }
+    place_all();
+    if ((e = alloc_tile_buffers(c, lim.batch_packets)) != hipSuccess)
+        return cleanup(e == hipErrorOutOfMemory ? MC_LYA_ENOMEM : MC_LYA_EDEVICE);
+    {
+        const size_t up = nb * (sizeof(WalkBox) + sizeof(RedBox) + sizeof(FeedBox) + sizeof(double) + sizeof(PackBox));
+        const size_t down = std::max(nb * std::max(sizeof(BoxRed), sizeof(BoxTot) + 8 + 32),
+                                     sizeof(unsigned long long) * 2 * (size_t)kMaxGenerations);
+        void *pin = nullptr;
+        if (hipHostMalloc(&pin, up + down + 4096, hipHostMallocDefault) != hipSuccess) return cleanup(MC_LYA_ENOMEM);
+        c->pin = static_cast<char *>(pin);
+        c->up_walk = reinterpret_cast<WalkBox *>(c->pin);
+        c->up_feed = reinterpret_cast<FeedBox *>(c->pin + nb * (sizeof(WalkBox) + sizeof(RedBox)));
+        c->up_pack = reinterpret_cast<PackBox *>(c->up_feed + nb);
+        c->up_coef = reinterpret_cast<double *>(c->up_pack + nb);
+        c->down = c->pin + (up + 255) / 256 * 256;
+    }
+    if (c->share_cells &&
+        hipMemsetAsync(c->d_share, 0, sizeof(unsigned long long) * c->share_cells, c->stream) != hipSuccess)
+        return cleanup(MC_LYA_EDEVICE);
     // (default stream priority)
     if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&c->fork, hipEventDisableTiming) != hipSuccess ||
@@ -1303,15 +1374,18 @@ mc_lya_status mc_lya_emit(mc_lya_ctx *c, const uint64_t *seeds, const uint64_t *
     }
     c->total_packets = ntot;
     const int nb = c->n_boxes;
-    HIP_TRY(c, hipMemcpyAsync(c->d_walk, c->walk.data(), sizeof(WalkBox) * nb, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(c->d_redbox, c->redbox.data(), sizeof(RedBox) * nb, hipMemcpyHostToDevice, c->stream));
+    if (c->up_busy) HIP_TRY(c, wait(c));
+    std::memcpy(c->up_walk, c->walk.data(), sizeof(WalkBox) * nb);
+    std::memcpy(c->up_walk + nb, c->redbox.data(), sizeof(RedBox) * nb);
+    c->up_busy = true;
+    HIP_TRY(c, hipMemcpyAsync(c->d_walk, c->up_walk, (sizeof(WalkBox) + sizeof(RedBox)) * nb, hipMemcpyHostToDevice,
+                              c->stream));
     HIP_TRY(c, launch_quantize(c->d_pack, nb, c->max_blk, c->d_wgt, c->d_red, c->d_q, c->d_bsum, c->stream));
-    HIP_TRY(c, launch_scan_blocks(c->d_pack, nb, c->max_blk, c->d_bsum, c->d_red, c->stream));
+    HIP_TRY(c, launch_scan_blocks(c->d_pack, nb, c->max_blk, c->d_bsum, c->d_red, c->d_tot, c->stream));
     HIP_TRY(c, launch_allocate(c->d_pack, c->d_walk, nb, c->max_blk, c->d_q, c->d_bsum, c->d_red, c->d_npk,
-                               c->d_pfirst, c->stream));
+                               c->d_pfirst, c->d_A, c->stream));
     c->cop_valid = false;
-    HIP_TRY(c, hipMemsetAsync(c->d_A, 0, sizeof(unsigned long long) * c->total_cells, c->stream));
-    HIP_TRY(c, hipMemsetAsync(c->d_tot, 0, sizeof(BoxTot) * nb, c->stream));
+    c->queue_clear = false;
     c->state = 1;
     return MC_LYA_OK;
 }
@@ -1339,12 +1413,9 @@ mc_lya_status mc_lya_tally(mc_lya_ctx *c, int64_t *absorbed, int64_t *emitted, m
     const int nb = c->n_boxes;
     HIP_TRY(c, launch_tally(c->d_walk, nb, c->max_blk, c->d_A, c->d_npk, absorbed, emitted, c->d_part,
                             c->d_boxabs, c->stream));
-    std::vector<BoxTot> tot(nb);
-    std::vector<unsigned long long> abs(nb);
-    HIP_TRY(c, hipMemcpyAsync(tot.data(), c->d_tot, sizeof(BoxTot) * nb, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(abs.data(), c->d_boxabs, sizeof(unsigned long long) * nb, hipMemcpyDeviceToHost,
-                              c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    HIP_TRY(c, read_back(c, c->d_tot, (sizeof(BoxTot) + sizeof(unsigned long long)) * nb));
+    const BoxTot *tot = reinterpret_cast<const BoxTot *>(c->down);
+    const unsigned long long *abs = reinterpret_cast<const unsigned long long *>(tot + nb);
     bool capped = false, broken = false;
     for (int b = 0; b < nb; ++b) {
         const uint64_t w0 = c->desc[b].w0;
@@ -1437,19 +1508,13 @@ mc_lya_status mc_lya_features(mc_lya_ctx *c, float *out)
 static mc_lya_status feed_prepare(mc_lya_ctx *c, mc_lya_feed_stats *stats)
 {
     const int nb = c->n_boxes;
-    HIP_TRY(c, launch_tally(c->d_walk, nb, c->max_blk, c->d_A, c->d_npk, nullptr, nullptr, c->d_part,
-                            c->d_boxabs, c->stream));
-    HIP_TRY(c, launch_feed_sums(c->d_pack, nb, c->max_blk, c->d_wgt, c->d_part, c->stream));
-    HIP_TRY(c, launch_feed_reduce(nb, c->max_blk, c->d_pack, c->d_part, c->d_fsum, c->stream));
-    std::vector<BoxTot> tot(nb);
-    std::vector<unsigned long long> abs(nb);
-    std::vector<double> sums((size_t)4 * nb);
-    HIP_TRY(c, hipMemcpyAsync(tot.data(), c->d_tot, sizeof(BoxTot) * nb, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(abs.data(), c->d_boxabs, sizeof(unsigned long long) * nb, hipMemcpyDeviceToHost,
-                              c->stream));
-    HIP_TRY(c, hipMemcpyAsync(sums.data(), c->d_fsum, sizeof(double) * 4 * nb, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    std::vector<FeedBox> fb(nb);
+    HIP_TRY(c, launch_feed_sums(c->d_pack, nb, c->max_blk, c->d_wgt, c->d_A, c->d_part, c->d_fsum, c->d_boxabs,
+                                c->stream));
+    HIP_TRY(c, read_back(c, c->d_tot, (sizeof(BoxTot) + sizeof(unsigned long long) + 4 * sizeof(double)) * nb));
+    const BoxTot *tot = reinterpret_cast<const BoxTot *>(c->down);
+    const unsigned long long *abs = reinterpret_cast<const unsigned long long *>(tot + nb);
+    const double *sums = reinterpret_cast<const double *>(abs + nb);
+    FeedBox *fb = c->up_feed;                // (the last feed's copy of it has been waited for above)
     for (int b = 0; b < nb; ++b) {
         const phys::Box &ph = c->ph[b];
         const mc_lya_box_desc &d = c->desc[b];
@@ -1488,9 +1553,7 @@ static mc_lya_status feed_prepare(mc_lya_ctx *c, mc_lya_feed_stats *stats)
             s.ndot_e_mean = (-sum_s + reion * sum_A * fb[b].a_norm + fb[b].thermal * sum_n1s) / ncell;
         }
     }
-    // (fb is host memory the copy reads: synchronise before it goes)
-    HIP_TRY(c, hipMemcpyAsync(c->d_feed, fb.data(), sizeof(FeedBox) * nb, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    HIP_TRY(c, hipMemcpyAsync(c->d_feed, fb, sizeof(FeedBox) * nb, hipMemcpyHostToDevice, c->stream));
     return MC_LYA_OK;
 }
 
@@ -1503,8 +1566,8 @@ mc_lya_status mc_lya_feed(mc_lya_ctx *c, double *ndot_e, float *mix_corr, mc_lya
     if (ndot_e || mix_corr) {
         HIP_TRY(c, launch_feed(c->d_pack, c->d_feed, c->n_boxes, c->max_blk, c->d_wgt, c->d_A, ndot_e, mix_corr,
                                c->stream));
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
     }
+    HIP_TRY(c, wait(c));
     return MC_LYA_OK;
 }
 
@@ -1608,6 +1671,7 @@ mc_lya_status mc_lya_scatter(mc_lya_ctx *c, uint64_t first, uint64_t count, cons
     hipEvent_t e1 = nullptr;
     st = timed_begin(c, &e1);
     if (st != MC_LYA_OK) return st;
+    c->queue_clear = false;
     HIP_TRY(c, launch_scatter(p, 256, grid, c->stream));
     st = timed_end(c, e1);
     if (st != MC_LYA_OK) return st;
@@ -1627,8 +1691,9 @@ mc_lya_status set_epoch(mc_lya_ctx *c, double z)
         c->ph[b] = phys::scalars(d);
         c->pack[b].kappa_unit = c->ph[b].kappa_unit;
     }
-    HIP_TRY(c, hipMemcpyAsync(c->d_pack, c->pack.data(), sizeof(PackBox) * c->n_boxes, hipMemcpyHostToDevice,
-                              c->stream));
+    // (every caller has waited since the last epoch's copy was queued)
+    std::memcpy(c->up_pack, c->pack.data(), sizeof(PackBox) * c->n_boxes);
+    HIP_TRY(c, hipMemcpyAsync(c->d_pack, c->up_pack, sizeof(PackBox) * c->n_boxes, hipMemcpyHostToDevice, c->stream));
     drop_graph(c);
     ++c->epoch;
     return MC_LYA_OK;
@@ -1638,11 +1703,10 @@ mc_lya_status set_epoch(mc_lya_ctx *c, double z)
 mc_lya_status global_xe(mc_lya_ctx *c, double *X)
 {
     const int nb = c->n_boxes;
-    HIP_TRY(c, launch_feed_sums(c->d_pack, nb, c->max_blk, c->d_wgt, c->d_part, c->stream));
-    HIP_TRY(c, launch_feed_reduce(nb, c->max_blk, c->d_pack, c->d_part, c->d_fsum, c->stream));
-    std::vector<double> sums((size_t)4 * nb);
-    HIP_TRY(c, hipMemcpyAsync(sums.data(), c->d_fsum, sizeof(double) * 4 * nb, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    HIP_TRY(c, launch_feed_sums(c->d_pack, nb, c->max_blk, c->d_wgt, nullptr, c->d_part, c->d_fsum, c->d_boxabs,
+                                c->stream));
+    HIP_TRY(c, read_back(c, c->d_fsum, sizeof(double) * 4 * nb));
+    const double *sums = reinterpret_cast<const double *>(c->down);
     for (int b = 0; b < nb; ++b) X[b] = sums[4 * b + 3] > 0.0 ? sums[4 * b + 2] / sums[4 * b + 3] : 0.0;
     return MC_LYA_OK;
 }
@@ -1672,7 +1736,6 @@ mc_lya_status mc_lya_evolve(mc_lya_ctx *c, double z0, double z1, int32_t n_steps
     const double h = (z1 - z0) / n_steps;
     const double cz[4] = {0.0, 0.5, 0.5, 1.0};            // stage redshift offsets
     std::vector<uint64_t> seeds(nb);
-    std::vector<double> coef(nb);
     for (int32_t i = 0; i < n_steps; ++i) {
         const double z = z0 + i * h;
         for (int s = 0; s < 4; ++s) {
@@ -1689,11 +1752,11 @@ mc_lya_status mc_lya_evolve(mc_lya_ctx *c, double z0, double z1, int32_t n_steps
             if (st == MC_LYA_OK) st = launch_walk(c, 0, c->total_packets);
             if (st == MC_LYA_OK) st = mc_lya_feed(c, ndot, nullptr, nullptr);
             if (st != MC_LYA_OK) return st;
-            for (int b = 0; b < nb; ++b) coef[b] = -1.0 / (c->ph[b].nH * (1.0 + zs) * c->ph[b].H);
-            HIP_TRY(c, hipMemcpyAsync(c->d_ev_coef, coef.data(), sizeof(double) * nb, hipMemcpyHostToDevice,
+            // (the next stage waits in its refresh before it rewrites up_coef)
+            for (int b = 0; b < nb; ++b) c->up_coef[b] = -1.0 / (c->ph[b].nH * (1.0 + zs) * c->ph[b].H);
+            HIP_TRY(c, hipMemcpyAsync(c->d_ev_coef, c->up_coef, sizeof(double) * nb, hipMemcpyHostToDevice,
                                       c->stream));
             HIP_TRY(c, launch_xe_rate(c->d_pack, nb, c->max_blk, c->d_ev_coef, ndot, k[s], c->stream));
-            HIP_TRY(c, hipStreamSynchronize(c->stream));   // coef is reused by the next stage
         }
         const double w[4] = {h / 6.0, h / 3.0, h / 3.0, h / 6.0};
         const double *kk[4] = {k[0], k[1], k[2], k[3]};

@@ -19,6 +19,7 @@ struct mc_lya_mlp {
     float *d_part = nullptr;                 // [kMlpGradBlocks][kMlpPartStride]
     float *d_env = nullptr;                  // [16]: lower then upper feature bounds
     unsigned long long *d_count = nullptr;
+    float *pin = nullptr;                    // [kMlpParams + 2] pinned host memory behind the read-backs
     bool envelope = false;
     int64_t step = 0;
     int forward_grid = 0;
@@ -54,10 +55,11 @@ mc_lya_status mlp_hip(mc_lya_mlp *m, hipError_t e, const char *what)
 
 void mlp_free(mc_lya_mlp *m)
 {
-    void *ptrs[] = {m->d_params, m->d_m, m->d_v, m->d_grad, m->d_part, m->d_env, m->d_count, m->d_bad,
-                    m->d_tails};
-    for (void *p : ptrs)
-        if (p) (void)hipFree(p);
+    // (one allocation: parameters, moments, gradient, envelope, count, partial sums)
+    if (m->d_params) (void)hipFree(m->d_params);
+    if (m->d_bad) (void)hipFree(m->d_bad);
+    if (m->d_tails) (void)hipFree(m->d_tails);
+    if (m->pin) (void)hipHostFree(m->pin);
 }
 
 mc_lya_status check_batch(mc_lya_mlp *m, const float *features, uint64_t n)
@@ -96,21 +98,21 @@ mc_lya_status mc_lya_mlp_create(mc_lya_mlp **out, const float *params, void *str
     };
     hipError_t e;
     const size_t pb = sizeof(float) * kMlpParams;
-    if ((e = hipMalloc(reinterpret_cast<void **>(&m->d_params), pb)) != hipSuccess) return bail(e, "allocation");
-    if ((e = hipMalloc(reinterpret_cast<void **>(&m->d_m), pb)) != hipSuccess) return bail(e, "allocation");
-    if ((e = hipMalloc(reinterpret_cast<void **>(&m->d_v), pb)) != hipSuccess) return bail(e, "allocation");
-    if ((e = hipMalloc(reinterpret_cast<void **>(&m->d_grad), sizeof(float) * (kMlpParams + 2))) != hipSuccess)
+    constexpr size_t kVec = (kMlpParams + 2 + 63) / 64 * 64;     // a vector's room (256-byte multiples)
+    if ((e = hipMalloc(reinterpret_cast<void **>(&m->d_params),
+                       sizeof(float) * (4 * kVec + 64 + 64 + (size_t)kMlpGradBlocks * kMlpPartStride))) != hipSuccess)
         return bail(e, "allocation");
-    if ((e = hipMalloc(reinterpret_cast<void **>(&m->d_part),
-                       sizeof(float) * (size_t)kMlpGradBlocks * kMlpPartStride)) != hipSuccess)
-        return bail(e, "allocation");
-    if ((e = hipMalloc(reinterpret_cast<void **>(&m->d_env), sizeof(float) * 16)) != hipSuccess)
-        return bail(e, "allocation");
-    if ((e = hipMalloc(reinterpret_cast<void **>(&m->d_count), sizeof(unsigned long long))) != hipSuccess)
-        return bail(e, "allocation");
+    m->d_m = m->d_params + kVec;
+    m->d_v = m->d_m + kVec;
+    m->d_grad = m->d_v + kVec;
+    m->d_env = m->d_grad + kVec;
+    m->d_count = reinterpret_cast<unsigned long long *>(m->d_env + 64);
+    m->d_part = m->d_env + 128;
+    if ((e = hipHostMalloc(reinterpret_cast<void **>(&m->pin), sizeof(float) * (kMlpParams + 2), hipHostMallocDefault)) !=
+        hipSuccess)
+        return bail(e, "host allocation");
     if ((e = hipMemcpyAsync(m->d_params, params, pb, hipMemcpyHostToDevice, m->stream)) != hipSuccess ||
-        (e = hipMemsetAsync(m->d_m, 0, pb, m->stream)) != hipSuccess ||
-        (e = hipMemsetAsync(m->d_v, 0, pb, m->stream)) != hipSuccess ||
+        (e = hipMemsetAsync(m->d_m, 0, sizeof(float) * 2 * kVec, m->stream)) != hipSuccess ||
         (e = hipStreamSynchronize(m->stream)) != hipSuccess)
         return bail(e, "upload");
     int dev = 0, cu = 256;
@@ -130,8 +132,9 @@ mc_lya_status mc_lya_mlp_get_params(mc_lya_mlp *m, float *params)
 {
     if (!m) return MC_LYA_EINVAL;
     if (!params) return mlp_fail(m, MC_LYA_EINVAL, "params is NULL");
-    MLP_TRY(m, hipMemcpyAsync(params, m->d_params, sizeof(float) * kMlpParams, hipMemcpyDeviceToHost, m->stream));
+    MLP_TRY(m, hipMemcpyAsync(m->pin, m->d_params, sizeof(float) * kMlpParams, hipMemcpyDeviceToHost, m->stream));
     MLP_TRY(m, hipStreamSynchronize(m->stream));
+    std::memcpy(params, m->pin, sizeof(float) * kMlpParams);
     return MC_LYA_OK;
 }
 
@@ -172,8 +175,9 @@ mc_lya_status mc_lya_mlp_forward(mc_lya_mlp *m, const float *features, uint64_t 
                                   m->stream));
     if (n_outside) {
         unsigned long long c = 0;
-        MLP_TRY(m, hipMemcpyAsync(&c, m->d_count, sizeof c, hipMemcpyDeviceToHost, m->stream));
+        MLP_TRY(m, hipMemcpyAsync(m->pin, m->d_count, sizeof c, hipMemcpyDeviceToHost, m->stream));
         MLP_TRY(m, hipStreamSynchronize(m->stream));
+        std::memcpy(&c, m->pin, sizeof c);
         *n_outside = c;
     }
     return MC_LYA_OK;
@@ -201,10 +205,10 @@ mc_lya_status mc_lya_mlp_gradient(mc_lya_mlp *m, const float *features, const fl
     const int blocks = launch_mlp_gradient(m->d_params, features, targets, weights, n, nullptr, 0, nullptr, m->d_part,
                                            m->stream);
     MLP_TRY(m, launch_mlp_mean_gradient(m->d_part, blocks, m->d_grad, m->stream));
-    float tail[2];
-    MLP_TRY(m, hipMemcpyAsync(tail, m->d_grad + kMlpParams, sizeof tail, hipMemcpyDeviceToHost, m->stream));
-    if (grad) MLP_TRY(m, hipMemcpyAsync(grad, m->d_grad, sizeof(float) * kMlpParams, hipMemcpyDeviceToHost, m->stream));
+    MLP_TRY(m, hipMemcpyAsync(m->pin, m->d_grad, sizeof(float) * (kMlpParams + 2), hipMemcpyDeviceToHost, m->stream));
     MLP_TRY(m, hipStreamSynchronize(m->stream));
+    const float *tail = m->pin + kMlpParams;
+    if (grad) std::memcpy(grad, m->pin, sizeof(float) * kMlpParams);
     if (!(tail[1] > 0.0f)) return mlp_fail(m, MC_LYA_EINVAL, "the weights sum to zero");
     if (loss) *loss = tail[0] / tail[1];
     return MC_LYA_OK;

@@ -123,13 +123,14 @@ constexpr int kSetupBlock = 256;
 // Per-block partial results of the setup and tally kernels, kPartStride
 // doubles per (box, block): [0..3] sums (pack, then feed), [4] the block's
 // largest emission weight, [5] its largest |U - <U>|, [6] its absorbed-weight
-// sum (uint64 bits), [7] sum of Delta and [8] of Delta^2 (pack). Reduced per
+// sum (uint64 bits), [7] sum of Delta and [8] of Delta^2 (pack), [9] its
+// largest kappa, [10] its validation failures (a small integer). Reduced per
 // box by one-block kernels; no same-address atomics, which serialise at the
 // cache.
-constexpr int kPartStride = 10;   // ([9]: the block's largest kappa)
+constexpr int kPartStride = 12;
 
 hipError_t launch_pack(const PackBox *pb_dev, int n_boxes, int max_blk, bool vel_rec, void *rec,
-                       double *wgt, double *partials, BoxRed *red, hipStream_t s);
+                       double *wgt, double *partials, hipStream_t s);
 hipError_t launch_box_reduce(const PackBox *pb_dev, int n_boxes, int max_blk, const double *partials,
                              BoxRed *red, hipStream_t s);
 hipError_t launch_margin(const PackBox *pb_dev, int n_boxes, int max_blk, const float4 *rec, BoxRed *red,
@@ -138,12 +139,14 @@ hipError_t launch_margin(const PackBox *pb_dev, int n_boxes, int max_blk, const 
 hipError_t launch_quantize(const PackBox *pb_dev, int n_boxes, int max_blk, const double *wgt,
                            const BoxRed *red, uint64_t *q, uint64_t *bsum, hipStream_t s);
 hipError_t launch_scan_blocks(const PackBox *pb_dev, int n_boxes, int max_blk, uint64_t *bsum,
-                              BoxRed *red, hipStream_t s);
+                              BoxRed *red, BoxTot *tot, hipStream_t s);
 hipError_t launch_allocate(const PackBox *pb_dev, const WalkBox *wb_dev, int n_boxes, int max_blk,
                            const uint64_t *q, const uint64_t *bsum, const BoxRed *red,
-                           uint32_t *npk, uint64_t *pfirst, hipStream_t s);
+                           uint32_t *npk, uint64_t *pfirst, unsigned long long *A, hipStream_t s);
 hipError_t launch_cell_of_packet(const PackBox *pb_dev, int n_boxes, int max_blk, const uint32_t *npk,
-                                 const uint64_t *pfirst, uint32_t *cell_of_packet, hipStream_t s);
+                                 const uint64_t *pfirst, uint32_t *cell_of_packet, unsigned long long *queue,
+                                 hipStream_t s);
+constexpr int kMaxQueues = 64;       // work counters of the persistent walk
 
 struct WalkParams {
     const WalkBox *boxes;
@@ -168,7 +171,6 @@ struct WalkParams {
     const uint64_t *seg_start;
     const uint64_t *seg_id;
 };
-constexpr int kMaxQueues = 64;
 
 // ---- resonant scattering ----------------------------------------------------
 // Per-box constants of the scattering Monte Carlo.
@@ -361,11 +363,12 @@ hipError_t launch_red_mark(unsigned long long *counters, hipStream_t s);
 hipError_t launch_zero_counters(unsigned long long *c, int n, hipStream_t s);
 
 hipError_t launch_walk_simple(const WalkParams &p, int block, hipStream_t s);
-hipError_t launch_walk_persistent(const WalkParams &p, int block, int grid, hipStream_t s);
+// (reset: the work counters are not zero yet)
+hipError_t launch_walk_persistent(const WalkParams &p, int block, int grid, bool reset, hipStream_t s);
 // The persistent walk of a lone box with its records in LDS (box_fits_lds),
 // one workgroup of up to 1024 threads per compute unit.
 bool box_fits_lds(uint64_t cells, bool vel);
-hipError_t launch_walk_box(const WalkParams &p, uint64_t cells, int block, int grid, hipStream_t s);
+hipError_t launch_walk_box(const WalkParams &p, uint64_t cells, int block, int grid, bool reset, hipStream_t s);
 int persistent_blocks_per_cu(bool vel, bool voigt, int block);   // resident workgroups per CU
 hipError_t launch_trace(const WalkParams &p, mc_lya_packet_trace *out, hipStream_t s);
 hipError_t launch_philox(const uint32_t *ctr, const uint32_t *key, uint32_t *out, uint64_t n,
@@ -385,10 +388,11 @@ struct FeedBox {
     double wing_n1s;         // wing / sum(n_1s): the far damping wing's absorption per unit n_1s
     double w_inv;            // 1 / sum(weight): a cell's share of the box's emission is weight * w_inv
 };
+// Per box: the sums of weights, (1 - x_e) Delta, x_e Delta and Delta into
+// sums[4 b], and (A given) of the absorbed weight into box_abs[b].
 hipError_t launch_feed_sums(const PackBox *pb_dev, int n_boxes, int max_blk, const double *wgt,
-                            double *partials, hipStream_t s);
-hipError_t launch_feed_reduce(int n_boxes, int max_blk, const PackBox *pb_dev, const double *partials,
-                              double *sums, hipStream_t s);
+                            const unsigned long long *A, double *partials, double *sums,
+                            unsigned long long *box_abs, hipStream_t s);
 // The surrogate's regression data per cell: y = ln M_c and the cell's share
 // of its box's emission (both 0 where M_c = 0).
 hipError_t launch_targets(const PackBox *pb_dev, const FeedBox *fb_dev, int n_boxes, int max_blk,

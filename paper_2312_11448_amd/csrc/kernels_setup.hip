@@ -67,6 +67,41 @@ __device__ __forceinline__ double block_max(double v, double *lds)
     return t;
 }
 
+// N block sums and M block maxima (each formed as block_sum and block_max
+// form one) with two barriers in all; `lds` holds kWaves x (N + M) doubles. Results in
+// thread 0.
+template <int N, int M>
+__device__ __forceinline__ void block_reduce(double (&sum)[N], double (&top)[M], double *lds)
+{
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+    for (int j = 0; j < N; ++j) sum[j] = wave_sum(sum[j]);
+#pragma unroll
+    for (int j = 0; j < M; ++j) top[j] = wave_max(top[j]);
+    __syncthreads();
+    if (lane == 0) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) lds[wid * (N + M) + j] = sum[j];
+#pragma unroll
+        for (int j = 0; j < M; ++j) lds[wid * (N + M) + N + j] = top[j];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            double t = 0.0;
+            for (int w = 0; w < kWaves; ++w) t += lds[w * (N + M) + j];
+            sum[j] = t;
+        }
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            double t = 0.0;
+            for (int w = 0; w < kWaves; ++w) t = fmax(t, lds[w * (N + M) + N + j]);
+            top[j] = t;
+        }
+    }
+}
+
 // Inclusive scan of a 64-bit value across the block; also returns the block
 // total through *total (all threads).
 __device__ __forceinline__ uint64_t block_inclusive_scan(uint64_t v, uint64_t *lds, uint64_t *total)
@@ -99,10 +134,10 @@ __device__ __forceinline__ bool finite_f(float v) { return __builtin_isfinite(v)
 template <bool VREC>
 __global__ __launch_bounds__(B) void pack_kernel(const PackBox *__restrict__ pbs, void *__restrict__ rec,
                                                  double *__restrict__ wgt,
-                                                 double *__restrict__ partials, BoxRed *red,
-                                                 int max_blk)
+                                                 double *__restrict__ partials, int max_blk)
 {
-    __shared__ double lds[kWaves];
+    __shared__ double lds[kWaves * 8];
+    __shared__ uint32_t s_flags[kWaves];
     const int b = blockIdx.y;
     const PackBox pb = pbs[b];
     if ((int)blockIdx.x >= pb.nblk) return;
@@ -149,27 +184,23 @@ __global__ __launch_bounds__(B) void pack_kernel(const PackBox *__restrict__ pbs
         d1 = (double)od;
         d2 = d1 * d1;
     }
-    const double sx = block_sum(ux, lds);
-    const double sy = block_sum(uy, lds);
-    const double sz = block_sum(uz, lds);
-    const double sk = block_sum(ks, lds);
-    const double sd1 = block_sum(d1, lds);
-    const double sd2 = block_sum(d2, lds);
-    const double wm = block_max(w, lds);
-    const double km = block_max(ks, lds);
-    // validation failures are rare: an atomic only where one is found
+    double sum[6] = {ux, uy, uz, ks, d1, d2}, top[2] = {w, ks};
     const uint32_t fl = wave_or(flags);
-    if ((threadIdx.x & 63) == 0 && fl) atomicOr(&red[b].flags, fl);
+    if ((threadIdx.x & 63) == 0) s_flags[threadIdx.x >> 6] = fl;
+    block_reduce(sum, top, lds);
     if (threadIdx.x == 0) {
         double *p = partials + ((size_t)b * max_blk + blockIdx.x) * kPartStride;
-        p[0] = sx;
-        p[1] = sy;
-        p[2] = sz;
-        p[3] = sk;
-        p[4] = wm;
-        p[7] = sd1;
-        p[8] = sd2;
-        p[9] = km;
+        p[0] = sum[0];
+        p[1] = sum[1];
+        p[2] = sum[2];
+        p[3] = sum[3];
+        p[4] = top[0];
+        p[7] = sum[4];
+        p[8] = sum[5];
+        p[9] = top[1];
+        uint32_t f = 0;
+        for (int k = 0; k < kWaves; ++k) f |= s_flags[k];
+        p[10] = (double)f;
     }
 }
 
@@ -178,34 +209,39 @@ __global__ __launch_bounds__(B) void box_reduce_kernel(const PackBox *__restrict
                                                        const double *__restrict__ partials,
                                                        BoxRed *red, int max_blk)
 {
-    __shared__ double lds[kWaves];
+    __shared__ double lds[kWaves * 8];
+    __shared__ uint32_t s_flags[kWaves];
     const int b = blockIdx.x;
     const int nblk = pbs[b].nblk;
-    double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    double wm = 0.0, km = 0.0;
+    double sum[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, top[2] = {0.0, 0.0};
+    uint32_t flags = 0;
+#pragma unroll 4
     for (int k = threadIdx.x; k < nblk; k += B) {
         const double *p = partials + ((size_t)b * max_blk + k) * kPartStride;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] += p[j];
-        acc[4] += p[7];
-        acc[5] += p[8];
-        wm = fmax(wm, p[4]);
-        km = fmax(km, p[9]);
+        for (int j = 0; j < 4; ++j) sum[j] += p[j];
+        sum[4] += p[7];
+        sum[5] += p[8];
+        top[0] = fmax(top[0], p[4]);
+        top[1] = fmax(top[1], p[9]);
+        flags |= (uint32_t)p[10];
     }
-    double tot[6];
-#pragma unroll
-    for (int j = 0; j < 6; ++j) tot[j] = block_sum(acc[j], lds);
-    wm = block_max(wm, lds);
-    km = block_max(km, lds);
+    flags = wave_or(flags);
+    if ((threadIdx.x & 63) == 0) s_flags[threadIdx.x >> 6] = flags;
+    block_reduce(sum, top, lds);
     if (threadIdx.x == 0) {
-        red[b].usum[0] = tot[0];
-        red[b].usum[1] = tot[1];
-        red[b].usum[2] = tot[2];
-        red[b].kappa_sum = tot[3];
-        red[b].od_sum = tot[4];
-        red[b].od2_sum = tot[5];
-        red[b].kappa_max = (float)km;
-        red[b].wmax_bits = (unsigned long long)__double_as_longlong(wm);
+        BoxRed r;
+        for (int a = 0; a < 3; ++a) r.usum[a] = sum[a];
+        r.kappa_sum = sum[3];
+        r.od_sum = sum[4];
+        r.od2_sum = sum[5];
+        r.kappa_max = (float)top[1];
+        r.wmax_bits = (unsigned long long)__double_as_longlong(top[0]);
+        r.udev_bits = 0;                 // (margin_reduce_kernel's, with a flow)
+        r.flags = 0;
+        for (int k = 0; k < kWaves; ++k) r.flags |= s_flags[k];
+        r.qtot = 0;
+        red[b] = r;
     }
 }
 
@@ -241,6 +277,7 @@ __global__ __launch_bounds__(B) void margin_reduce_kernel(const PackBox *__restr
     const int b = blockIdx.x;
     const int nblk = pbs[b].nblk;
     double m = 0.0;
+#pragma unroll 8
     for (int k = threadIdx.x; k < nblk; k += B) m = fmax(m, partials[((size_t)b * max_blk + k) * kPartStride + 5]);
     m = block_max(m, lds);
     if (threadIdx.x == 0) red[b].udev_bits = (unsigned long long)__double_as_longlong(m);
@@ -276,14 +313,15 @@ __global__ __launch_bounds__(B) void quantize_kernel(const PackBox *__restrict__
 }
 
 // One block per box: exclusive scan of the block sums (in place) and the box
-// total.
+// total; the box's walk totals start from zero.
 __global__ __launch_bounds__(B) void scan_blocks_kernel(const PackBox *__restrict__ pbs,
                                                         uint64_t *__restrict__ bsum, BoxRed *red,
-                                                        int max_blk)
+                                                        BoxTot *__restrict__ tot, int max_blk)
 {
     __shared__ uint64_t lds[kWaves];
     const int b = blockIdx.x;
     const int nblk = pbs[b].nblk;
+    if (threadIdx.x < sizeof(BoxTot) / 8) reinterpret_cast<unsigned long long *>(&tot[b])[threadIdx.x] = 0ull;
     uint64_t carry = 0;
     for (int base = 0; base < nblk; base += B) {
         const int k = base + threadIdx.x;
@@ -320,14 +358,16 @@ __device__ __forceinline__ uint64_t count_below(uint64_t Q, uint64_t qtot, uint6
     return c >> 1;
 }
 
-// Allocation: each cell learns its first packet id and its count.
+// Allocation: each cell learns its first packet id and its count, and its
+// tally starts from zero.
 __global__ __launch_bounds__(B) void allocate_kernel(const PackBox *__restrict__ pbs,
                                                      const WalkBox *__restrict__ wbs,
                                                      const uint64_t *__restrict__ q,
                                                      const uint64_t *__restrict__ bsum,
                                                      const BoxRed *__restrict__ red,
                                                      uint32_t *__restrict__ npk,
-                                                     uint64_t *__restrict__ pfirst, int max_blk)
+                                                     uint64_t *__restrict__ pfirst,
+                                                     unsigned long long *__restrict__ A, int max_blk)
 {
     __shared__ uint64_t lds[kWaves];
     const int b = blockIdx.y;
@@ -339,6 +379,7 @@ __global__ __launch_bounds__(B) void allocate_kernel(const PackBox *__restrict__
     uint64_t tot;
     const uint64_t inc = block_inclusive_scan(v, lds, &tot);
     if (i >= pb.ncells) return;
+    A[g] = 0ull;
     const uint64_t n = wbs[b].npkt;
     const uint64_t qtot = red[b].qtot;
     if (n == 0 || qtot == 0) {
@@ -359,8 +400,11 @@ __global__ __launch_bounds__(B) void allocate_kernel(const PackBox *__restrict__
 __global__ __launch_bounds__(B) void cell_of_packet_kernel(const PackBox *__restrict__ pbs,
                                                            const uint32_t *__restrict__ npk,
                                                            const uint64_t *__restrict__ pfirst,
-                                                           uint32_t *__restrict__ cop)
+                                                           uint32_t *__restrict__ cop,
+                                                           unsigned long long *__restrict__ queue)
 {
+    // (the walk that asked for the list finds its work counters at zero)
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kMaxQueues) queue[threadIdx.x] = 0ull;
     const int b = blockIdx.y;
     const PackBox pb = pbs[b];
     if ((int)blockIdx.x >= pb.nblk) return;
@@ -377,14 +421,14 @@ inline dim3 grid2(int max_blk, int n_boxes) { return dim3((unsigned)max_blk, (un
 }  // namespace
 
 hipError_t launch_pack(const PackBox *pb_dev, int n_boxes, int max_blk, bool vel_rec, void *rec,
-                       double *wgt, double *partials, BoxRed *red, hipStream_t s)
+                       double *wgt, double *partials, hipStream_t s)
 {
     if (vel_rec)
         hipLaunchKernelGGL(pack_kernel<true>, grid2(max_blk, n_boxes), dim3(B), 0, s, pb_dev, rec, wgt,
-                           partials, red, max_blk);
+                           partials, max_blk);
     else
         hipLaunchKernelGGL(pack_kernel<false>, grid2(max_blk, n_boxes), dim3(B), 0, s, pb_dev, rec, wgt,
-                           partials, red, max_blk);
+                           partials, max_blk);
     return hipGetLastError();
 }
 
@@ -415,27 +459,28 @@ hipError_t launch_quantize(const PackBox *pb_dev, int n_boxes, int max_blk, cons
 }
 
 hipError_t launch_scan_blocks(const PackBox *pb_dev, int n_boxes, int max_blk, uint64_t *bsum, BoxRed *red,
-                              hipStream_t s)
+                              BoxTot *tot, hipStream_t s)
 {
-    hipLaunchKernelGGL(scan_blocks_kernel, dim3((unsigned)n_boxes), dim3(B), 0, s, pb_dev, bsum, red,
+    hipLaunchKernelGGL(scan_blocks_kernel, dim3((unsigned)n_boxes), dim3(B), 0, s, pb_dev, bsum, red, tot,
                        max_blk);
     return hipGetLastError();
 }
 
 hipError_t launch_allocate(const PackBox *pb_dev, const WalkBox *wb_dev, int n_boxes, int max_blk,
                            const uint64_t *q, const uint64_t *bsum, const BoxRed *red, uint32_t *npk,
-                           uint64_t *pfirst, hipStream_t s)
+                           uint64_t *pfirst, unsigned long long *A, hipStream_t s)
 {
     hipLaunchKernelGGL(allocate_kernel, grid2(max_blk, n_boxes), dim3(B), 0, s, pb_dev, wb_dev, q, bsum, red,
-                       npk, pfirst, max_blk);
+                       npk, pfirst, A, max_blk);
     return hipGetLastError();
 }
 
 hipError_t launch_cell_of_packet(const PackBox *pb_dev, int n_boxes, int max_blk, const uint32_t *npk,
-                                 const uint64_t *pfirst, uint32_t *cell_of_packet, hipStream_t s)
+                                 const uint64_t *pfirst, uint32_t *cell_of_packet, unsigned long long *queue,
+                                 hipStream_t s)
 {
     hipLaunchKernelGGL(cell_of_packet_kernel, grid2(max_blk, n_boxes), dim3(B), 0, s, pb_dev, npk, pfirst,
-                       cell_of_packet);
+                       cell_of_packet, queue);
     return hipGetLastError();
 }
 

@@ -69,61 +69,95 @@ __global__ __launch_bounds__(B) void tally_reduce_kernel(const WalkBox *__restri
     const uint32_t nblk = (wbs[b].cells() + B - 1) / B;
     const unsigned long long *p = reinterpret_cast<const unsigned long long *>(partials);
     unsigned long long a = 0;
+#pragma unroll 8
     for (uint32_t k = threadIdx.x; k < nblk; k += B) a += p[((size_t)b * max_blk + k) * kPartStride + 6];
     a = block_sum(a, lds);
     if (threadIdx.x == 0) box_abs[b] = a;
 }
 
-// Per block: sum of weights, of (1 - x_e) Delta, of x_e Delta and of Delta.
+// Per block: sum of weights, of (1 - x_e) Delta, of x_e Delta and of Delta,
+// and (A given) of the absorbed weight.
 __global__ __launch_bounds__(B) void feed_sums_kernel(const PackBox *__restrict__ pbs,
                                                       const double *__restrict__ wgt,
+                                                      const unsigned long long *__restrict__ A,
                                                       double *__restrict__ partials, int max_blk)
 {
-    __shared__ double lds[kWaves];
+    __shared__ double lds[4][kWaves];
+    __shared__ unsigned long long lds_a[kWaves];
     const int b = blockIdx.y;
     const PackBox pb = pbs[b];
     if ((int)blockIdx.x >= pb.nblk) return;
     const uint32_t i = blockIdx.x * B + threadIdx.x;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    unsigned long long a = 0;
     if (i < pb.ncells) {
         const double od = (double)pb.od[i];
         const double xe = (double)(pb.xe ? pb.xe[i] : pb.xe_uniform);
-        s0 = wgt[(size_t)pb.cell_off + i];
-        s1 = (1.0 - xe) * od;
-        s2 = xe * od;
-        s3 = od;
+        s[0] = wgt[(size_t)pb.cell_off + i];
+        s[1] = (1.0 - xe) * od;
+        s[2] = xe * od;
+        s[3] = od;
+        if (A) a = A[(size_t)pb.cell_off + i];
     }
-    const double t0 = block_sum(s0, lds);
-    const double t1 = block_sum(s1, lds);
-    const double t2 = block_sum(s2, lds);
-    const double t3 = block_sum(s3, lds);
-    if (threadIdx.x == 0) {
-        double *p = partials + ((size_t)b * max_blk + blockIdx.x) * kPartStride;
-        p[0] = t0;
-        p[1] = t1;
-        p[2] = t2;
-        p[3] = t3;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s[j] = wave_sum(s[j]);
+    a = wave_sum(a);
+    if (lane == 0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) lds[j][wid] = s[j];
+        lds_a[wid] = a;
+    }
+    __syncthreads();
+    double *p = partials + ((size_t)b * max_blk + blockIdx.x) * kPartStride;
+    if (threadIdx.x < 4) {
+        double v = 0.0;
+        for (int w = 0; w < kWaves; ++w) v += lds[threadIdx.x][w];
+        p[threadIdx.x] = v;
+    } else if (threadIdx.x == 4) {
+        unsigned long long v = 0;
+        for (int w = 0; w < kWaves; ++w) v += lds_a[w];
+        reinterpret_cast<unsigned long long *>(p)[6] = v;
     }
 }
 
 // One block per box: fixed-order sum of the block partials.
-__global__ __launch_bounds__(B) void reduce4_kernel(const PackBox *__restrict__ pbs,
-                                                    const double *__restrict__ partials,
-                                                    double *__restrict__ sums, int max_blk)
+__global__ __launch_bounds__(B) void feed_reduce_kernel(const PackBox *__restrict__ pbs,
+                                                        const double *__restrict__ partials,
+                                                        double *__restrict__ sums,
+                                                        unsigned long long *__restrict__ box_abs, int max_blk)
 {
-    __shared__ double lds[kWaves];
+    __shared__ double lds[4][kWaves];
+    __shared__ unsigned long long lds_a[kWaves];
     const int b = blockIdx.x;
     const int nblk = pbs[b].nblk;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    unsigned long long a = 0;
+#pragma unroll 4
     for (int k = threadIdx.x; k < nblk; k += B) {
         const double *p = partials + ((size_t)b * max_blk + k) * kPartStride;
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] += p[j];
+        a += reinterpret_cast<const unsigned long long *>(p)[6];
     }
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const double t = block_sum(acc[j], lds);
-        if (threadIdx.x == 0) sums[4 * b + j] = t;
+    for (int j = 0; j < 4; ++j) acc[j] = wave_sum(acc[j]);
+    a = wave_sum(a);
+    if (lane == 0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) lds[j][wid] = acc[j];
+        lds_a[wid] = a;
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        double v = 0.0;
+        for (int w = 0; w < kWaves; ++w) v += lds[threadIdx.x][w];
+        sums[4 * b + threadIdx.x] = v;
+    } else if (threadIdx.x == 4) {
+        unsigned long long v = 0;
+        for (int w = 0; w < kWaves; ++w) v += lds_a[w];
+        box_abs[b] = v;
     }
 }
 
@@ -199,17 +233,11 @@ hipError_t launch_tally(const WalkBox *wb_dev, int n_boxes, int max_blk, const u
 }
 
 hipError_t launch_feed_sums(const PackBox *pb_dev, int n_boxes, int max_blk, const double *wgt,
-                            double *partials, hipStream_t s)
+                            const unsigned long long *A, double *partials, double *sums,
+                            unsigned long long *box_abs, hipStream_t s)
 {
-    hipLaunchKernelGGL(feed_sums_kernel, grid2(max_blk, n_boxes), dim3(B), 0, s, pb_dev, wgt, partials,
-                       max_blk);
-    return hipGetLastError();
-}
-
-hipError_t launch_feed_reduce(int n_boxes, int max_blk, const PackBox *pb_dev, const double *partials,
-                              double *sums, hipStream_t s)
-{
-    hipLaunchKernelGGL(reduce4_kernel, dim3((unsigned)n_boxes), dim3(B), 0, s, pb_dev, partials, sums,
+    hipLaunchKernelGGL(feed_sums_kernel, grid2(max_blk, n_boxes), dim3(B), 0, s, pb_dev, wgt, A, partials, max_blk);
+    hipLaunchKernelGGL(feed_reduce_kernel, dim3((unsigned)n_boxes), dim3(B), 0, s, pb_dev, partials, sums, box_abs,
                        max_blk);
     return hipGetLastError();
 }

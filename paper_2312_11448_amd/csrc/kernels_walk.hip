@@ -94,7 +94,8 @@ struct BoxSink {
     }
 };
 
-template <bool VEL, bool VOIGT, class Sink>
+// LONE: one box, whose constants are read once.
+template <bool VEL, bool VOIGT, bool LONE, class Sink>
 __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkBox *sbox, const Sink &sink)
 {
     const uint32_t lane = lane_id();
@@ -118,6 +119,8 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
     // each XCD's L2 mostly sees one slab.
     const uint32_t nq = (uint32_t)P.nqueues;
     uint32_t part = blockIdx.x % nq, tried = 0;
+    const RedBox lone = P.red[0];
+    auto red_of = [&](int box) { return LONE ? lone : P.red[box]; };
 
     for (;;) {
         uint64_t idle = __ballot(!alive);
@@ -125,7 +128,7 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
         const uint64_t reds = __ballot(red);
         if (reds && (fill || (uint32_t)__popcll(reds) >= kRedGather || !__ballot(alive))) {
             if (red) {
-                const RedBox R = P.red[acc.box];
+                const RedBox R = red_of(acc.box);
                 RedEnd e;
                 if (!VEL || R.mode == kRedStill) e = red_exact<false, VOIGT>(L, P.rec, max_cross, ln);
                 else e = red_count<VOIGT>(L, R, P.rec, max_cross, ln);
@@ -167,7 +170,7 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
                 int nb = acc.box;
                 if (fresh) {
                     gp = packet_id(P, cur + r);
-                    nb = P.n_boxes == 1 ? 0 : box_of(sbox, P.n_boxes, gp);
+                    nb = LONE || P.n_boxes == 1 ? 0 : box_of(sbox, P.n_boxes, gp);
                 }
                 const bool change = fresh && nb != acc.box;
                 if (__ballot(change && acc.box >= 0)) flush(acc, change, P.tot);
@@ -177,7 +180,7 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
                     init_packet<VEL, VOIGT>(L, B, gp - B.pkt_off, P.cell_of_packet[gp], P.rec);
                     if (VOIGT) ln = line_of(B);
                     alive = true;
-                    sure = P.red[nb].mode != kRedOff;
+                    sure = red_of(nb).mode != kRedOff;
                 }
                 cur += take;
                 idle = __ballot(!alive);
@@ -203,7 +206,7 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
             acc.wing += fin ? wing : 0u;
             alive = alive && fate == kAlive;
             if (++tick % kRedEvery == 0 && __ballot(alive && sure)) {
-                if (alive && sure) red = red_only(P.red[acc.box], L.x, L.ku, L.kx, L.ky, L.kz, L.w);
+                if (alive && sure) red = red_only(red_of(acc.box), L.x, L.ku, L.kx, L.ky, L.kz, L.w);
                 alive = alive && !red;
             }
         }
@@ -217,7 +220,7 @@ __global__ __launch_bounds__(256) void walk_persistent_kernel(WalkParams P)
     extern __shared__ WalkBox sbox[];
     for (int i = threadIdx.x; i < P.n_boxes; i += blockDim.x) sbox[i] = P.boxes[i];
     __syncthreads();
-    persistent_walk<VEL, VOIGT>(P, sbox, GlobalSink{P.A});
+    persistent_walk<VEL, VOIGT, false>(P, sbox, GlobalSink{P.A});
 }
 
 // A lone box whose records fit the LDS: each workgroup reads them all once.
@@ -245,7 +248,7 @@ __global__ __launch_bounds__(1024) void walk_box_kernel(WalkParams P)
     if (TALLY)
         for (uint32_t i = threadIdx.x; i < cells; i += blockDim.x) tally[i] = 0ull;
     __syncthreads();
-    persistent_walk<VEL, VOIGT>(P, sbox, BoxSink{TALLY ? tally : P.A, reinterpret_cast<const char *>(recs)});
+    persistent_walk<VEL, VOIGT, true>(P, sbox, BoxSink{TALLY ? tally : P.A, reinterpret_cast<const char *>(recs)});
     if (TALLY) {
         __syncthreads();
         for (uint32_t i = threadIdx.x; i < cells; i += blockDim.x)
@@ -348,9 +351,9 @@ int persistent_blocks_per_cu(bool vel, bool voigt, int block)
     return (e == hipSuccess && n > 0) ? n : 1;
 }
 
-hipError_t launch_walk_persistent(const WalkParams &p, int block, int grid, hipStream_t s)
+hipError_t launch_walk_persistent(const WalkParams &p, int block, int grid, bool reset, hipStream_t s)
 {
-    hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(64), 0, s, p.queue, (int)p.nqueues);
+    if (reset) hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(64), 0, s, p.queue, (int)p.nqueues);
     const size_t lds = sizeof(WalkBox) * (size_t)p.n_boxes;
     const dim3 g((unsigned)grid), b((unsigned)block);
     if (p.voigt) {
@@ -377,9 +380,9 @@ static void launch_box(const WalkParams &p, dim3 g, dim3 b, hipStream_t s)
     }
 }
 
-hipError_t launch_walk_box(const WalkParams &p, uint64_t cells, int block, int grid, hipStream_t s)
+hipError_t launch_walk_box(const WalkParams &p, uint64_t cells, int block, int grid, bool reset, hipStream_t s)
 {
-    hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(64), 0, s, p.queue, (int)p.nqueues);
+    if (reset) hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(64), 0, s, p.queue, (int)p.nqueues);
     // tallies in LDS where they fit and adding every workgroup's to the
     // device's costs less than the deposits (some 40 a packet)
     const bool tally = cells * (p.vel ? 24 : 12) <= (uint64_t)kBoxLds && cells * (uint64_t)grid <= 10 * p.count;
