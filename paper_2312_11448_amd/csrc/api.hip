@@ -414,8 +414,9 @@ mc_lya_status do_refresh(mc_lya_ctx *c)
     return MC_LYA_OK;
 }
 
-// Tiles of kTileX x kTileY x kTileZ cells per box (the last ones along an axis may be
-// thinner). For each tile, the exit lists it pulls: for each of its six faces
+// Tiles of at most kTileX x kTileY x kTileZ cells per box, an axis cut into
+// equal ones (a box of 18 cells into 9 + 9, not 16 + 2: a thin tile is left
+// after a few crossings, and every generation costs the same). For each tile, the exit lists it pulls: for each of its six faces
 // whose neighbour is another tile, that neighbour's list through the
 // opposite face (a tile that spans an axis wraps onto itself there).
 void build_tiles(mc_lya_ctx *c)
@@ -428,6 +429,7 @@ void build_tiles(mc_lya_ctx *c)
         const int nt[3] = {(d.nx + TE[0] - 1) / TE[0], (d.ny + TE[1] - 1) / TE[1], (d.nz + TE[2] - 1) / TE[2]};
         const int off = (int)c->tiles.size();
         const int n[3] = {d.nx, d.ny, d.nz};
+        const int te[3] = {(n[0] + nt[0] - 1) / nt[0], (n[1] + nt[1] - 1) / nt[1], (n[2] + nt[2] - 1) / nt[2]};
         for (int tz = 0; tz < nt[2]; ++tz)
             for (int ty = 0; ty < nt[1]; ++ty)
                 for (int tx = 0; tx < nt[0]; ++tx) {
@@ -437,8 +439,10 @@ void build_tiles(mc_lya_ctx *c)
                     const int tc[3] = {tx, ty, tz};
                     int o[3], e[3];
                     for (int a = 0; a < 3; ++a) {
-                        o[a] = tc[a] * TE[a];
-                        e[a] = std::min(TE[a], n[a] - o[a]);
+                        o[a] = tc[a] * te[a];
+                        e[a] = std::min(te[a], n[a] - o[a]);
+                        const int low = tc[a] == 0 ? n[a] - (nt[a] - 1) * te[a] : te[a];
+                        t.nsrc_low |= (uint32_t)low << (8 * (a + 1));
                     }
                     t.ox = o[0];
                     t.oy = o[1];
@@ -456,9 +460,9 @@ void build_tiles(mc_lya_ctx *c)
                             q[a] = (q[a] + dir + nt[a]) % nt[a];
                             // the neighbour on side dir sends what leaves it through the opposite face
                             const int face = 2 * a + (dir < 0 ? 1 : 0);
-                            t.src_tile[t.nsrc] = off + q[0] + nt[0] * (q[1] + nt[1] * q[2]);
-                            t.src_faces |= (uint32_t)face << (4 * t.nsrc);
-                            ++t.nsrc;
+                            t.src_tile[t.nsrc()] = off + q[0] + nt[0] * (q[1] + nt[1] * q[2]);
+                            t.src_faces |= (uint32_t)face << (4 * t.nsrc());
+                            ++t.nsrc_low;
                         }
                     }
                     t.span |= (uint32_t)c->share << 8;
@@ -472,7 +476,7 @@ void build_tiles(mc_lya_ctx *c)
         for (int i = 0; i < n; ++i) {
             TileInfo t = c->tiles[i];
             t.span |= (uint32_t)r << 20;
-            for (int k = 0; k < t.nsrc; ++k) t.src_tile[k] += r * n;
+            for (int k = 0; k < t.nsrc(); ++k) t.src_tile[k] += r * n;
             c->tiles.push_back(t);
         }
 }
@@ -491,13 +495,22 @@ constexpr int kAllTiled = 1000000;        // tile_share at or above this: every 
 constexpr uint64_t kSharePackets = 512;
 // A lone box with fewer tiles than compute units is walked by (shared) tiles
 // from this many crossings as classify_boxes estimates them (42 a packet on
-// the 128^3 workload's fields, where they walk 87). The tiles take about 20 generations of
-// 35 us however few packets there are; the persistent walk takes as long as
-// its longest packet (0.3 to 0.5 ms) and then is bound by the device's 2.4e10
-// deposits/s. Transports, us (tiles, persistent): 48^3 with 1.1e5 packets 850,
-// 560 and with 4.4e5 960, 1200; 64^3 with 2.6e5 910, 930; 32^3 with 5.2e5
-// 1060, 1180 and with 2.1e6 1420, 4050; 64^3 with 1.7e7 4900, 31500.
-constexpr double kSharedWork = 1.2e7;
+// the 128^3 workload's fields, where they walk 87). The tiles take about 20
+// generations of 35 us however few packets there are; the persistent walk
+// takes as long as its longest packet (0.3 to 0.5 ms) and then is bound by the
+// device's 2.4e10 deposits/s, or, with its tallies in LDS, by its steps.
+// Transports, us (tiles, persistent): 48^3 with 1.1e5 packets 650, 570 and
+// with 2.2e5 680, 890; 32^3 with 1.3e5 670, 490 and with 2.6e5 716, 810; 64^3
+// with 2.6e5 708, 950 and with 1.7e7 4900, 31500. Tallies in LDS: 16^3 and
+// 20^3 with 3e5 700, 490 and 800, 490, with 1e6 1030, 1270 and 1020, 1210; the
+// longest steps (Voigt in a flow), 16^3 with 6e4 630, 870 and with 1e6 1330,
+// 1550.
+constexpr double kSharedWork = 8e6, kSharedWorkTally = 1.3e7, kSharedWorkVoigtFlow = 2e6;
+double shared_work(const mc_lya_ctx *c)
+{
+    if (!box_tally_fits_lds(c->total_cells, c->vel)) return kSharedWork;
+    return c->vel && c->voigt ? kSharedWorkVoigtFlow : kSharedWorkTally;
+}
 int sharing(const mc_lya_ctx *c, int nt, uint64_t packets)
 {
     const uint64_t per = packets / ((uint64_t)nt * kSharePackets);
@@ -532,7 +545,7 @@ mc_lya_status classify_boxes(mc_lya_ctx *c)
     if (nb == 1 && c->tile_share > 0) {
         const int nt = tiles_of_box(c->desc[0]);
         share = sharing(c, nt, c->walk[0].npkt);
-        if (cost[0] >= kSharedWork) m[0] = 1;
+        if (cost[0] >= shared_work(c)) m[0] = 1;
         if (!m[0]) share = 1;
     }
     if (m == c->tiled && share == c->share) return MC_LYA_OK;

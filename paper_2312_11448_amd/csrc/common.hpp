@@ -212,8 +212,9 @@ hipError_t launch_xe_combine(const PackBox *pb_dev, int n_boxes, int max_blk, co
                              hipStream_t s);
 
 // ---- tile-decomposed walk -------------------------------------------------
-// Tile extent in cells along x, y, z (the last tiles along an axis may be
-// thinner) and the workgroup that walks one tile.
+// Largest tile extent in cells along x, y, z and the workgroup that walks one
+// tile. An axis of n cells is cut into ceil(n / 16) tiles of equal extent (the
+// last one may lack some cells).
 #ifndef MCLYA_TILE_Z
 #define MCLYA_TILE_Z 16
 #endif
@@ -228,7 +229,8 @@ struct TileInfo {
     int32_t box;
     int32_t ox, oy, oz;      // origin (cell coordinates in the box)
     int32_t sx, sy, sz;      // extent (cells)
-    int32_t nsrc;            // exit lists this tile pulls from (0..6)
+    uint32_t nsrc_low;       // bits 0-2: exit lists this tile pulls from (0..6); bits 8-12, 16-20 and
+                             // 24-28: the extent along x, y, z of the neighbour below it
     int32_t src_tile[6];     // tile whose exits through face src_face[k] enter this tile
     uint32_t src_faces;      // 4 bits per source: the face (0 -x, 1 +x, 2 -y, 3 +y, 4 -z, 5 +z)
     uint32_t span;           // bits 0-2: the tile spans the box along axis a (a packet wraps
@@ -236,6 +238,7 @@ struct TileInfo {
                              // 20-31: how many workgroups share the tile's cells, and which
                              // of them this entry is (its share of the emitted packets, its
                              // own tally)
+    __host__ __device__ int nsrc() const { return (int)(nsrc_low & 7u); }
 };
 static_assert(sizeof(TileInfo) == 64, "TileInfo layout");
 
@@ -368,6 +371,7 @@ hipError_t launch_walk_persistent(const WalkParams &p, int block, int grid, bool
 // The persistent walk of a lone box with its records in LDS (box_fits_lds),
 // one workgroup of up to 1024 threads per compute unit.
 bool box_fits_lds(uint64_t cells, bool vel);
+bool box_tally_fits_lds(uint64_t cells, bool vel);     // ... and its tallies
 hipError_t launch_walk_box(const WalkParams &p, uint64_t cells, int block, int grid, bool reset, hipStream_t s);
 int persistent_blocks_per_cu(bool vel, bool voigt, int block);   // resident workgroups per CU
 hipError_t launch_trace(const WalkParams &p, mc_lya_packet_trace *out, hipStream_t s);

@@ -68,7 +68,7 @@ struct TileCtx {
     uint32_t max_cross;
     Line ln;
     int32_t ox, oy, oz, sx, sy, sz;
-    uint32_t span;
+    uint32_t span, low;
     RedBox red;
 };
 
@@ -267,14 +267,11 @@ __device__ __forceinline__ void idle_tlane(TLane &T, int32_t rs)
     T.dqz = kSX * kSY * rs;
 }
 
-// Offsets of a cell inside its tile, packed (tile origins are multiples of
-// the tile edge, so they are the low bits of the box coordinates).
-static_assert((kTileX & (kTileX - 1)) == 0 && (kTileY & (kTileY - 1)) == 0 && (kTileZ & (kTileZ - 1)) == 0 &&
-                  kTileX <= 16 && kTileY <= 16 && kTileZ <= 16,
-              "a cell's offset in its tile takes 4 bits per axis");
-__device__ __forceinline__ uint32_t pack_pos(int32_t ix, int32_t iy, int32_t iz)
+// Offsets of a cell inside its tile, packed.
+static_assert(kTileX <= 16 && kTileY <= 16 && kTileZ <= 16, "a cell's offset in its tile takes 4 bits per axis");
+__device__ __forceinline__ uint32_t pack_pos(int32_t lx, int32_t ly, int32_t lz)
 {
-    return (uint32_t)(ix & (kTileX - 1)) | (uint32_t)(iy & (kTileY - 1)) << 4 | (uint32_t)(iz & (kTileZ - 1)) << 8;
+    return (uint32_t)lx | (uint32_t)ly << 4 | (uint32_t)lz << 8;
 }
 
 // The state with the face distances (tx, ty, tz) and the cell at offsets pos.
@@ -308,16 +305,22 @@ __device__ __forceinline__ uint32_t save_exit(PState *out, const TLane &L, const
     const Face f = next_face(L.tmx, L.tmy, L.tmz);
     int32_t lx, ly, lz;
     slot_cell((int32_t)((uint32_t)L.q / (uint32_t)RS), lx, ly, lz);
-    const int32_t ix = C.ox + lx, iy = C.oy + ly, iz = C.oz + lz;
-    const int32_t ci = (f.bx ? ix : 0) + (f.by ? iy : 0) + (f.bz ? iz : 0);
-    const int32_t ni = (f.bx ? B.nx : 0) + (f.by ? B.ny : 0) + (f.bz ? B.nz : 0);
     const bool up = (f.bx & (L.kx > 0.0f)) | (f.by & (L.ky > 0.0f)) | (f.bz & (L.kz > 0.0f));
-    int32_t mi = ci + (up ? 1 : -1);
-    mi = mi == ni ? 0 : mi;
-    mi = mi < 0 ? ni - 1 : mi;
-    const int32_t jx = f.bx ? mi : ix, jy = f.by ? mi : iy, jz = f.bz ? mi : iz;
-    const uint32_t cell = B.cell_off + (uint32_t)jx + (uint32_t)B.nx * ((uint32_t)jy + (uint32_t)B.ny * (uint32_t)jz);
-    save_state(out, L, L.tmx, L.tmy, L.tmz, red ? cell : pack_pos(jx, jy, jz));
+    uint32_t pos;
+    if (red) {
+        const int32_t ix = C.ox + lx, iy = C.oy + ly, iz = C.oz + lz;
+        const int32_t ci = (f.bx ? ix : 0) + (f.by ? iy : 0) + (f.bz ? iz : 0);
+        const int32_t ni = (f.bx ? B.nx : 0) + (f.by ? B.ny : 0) + (f.bz ? B.nz : 0);
+        const int32_t mi = moved(ci, ni, up);
+        const int32_t jx = f.bx ? mi : ix, jy = f.by ? mi : iy, jz = f.bz ? mi : iz;
+        pos = B.cell_off + (uint32_t)jx + (uint32_t)B.nx * ((uint32_t)jy + (uint32_t)B.ny * (uint32_t)jz);
+    } else {
+        // the first layer of the neighbour above, or the last of the one below
+        const int32_t low = (int32_t)(C.low >> (f.bx ? 8 : (f.by ? 16 : 24)) & 31u);
+        const int32_t l = up ? 0 : low - 1;
+        pos = pack_pos(f.bx ? l : lx, f.by ? l : ly, f.bz ? l : lz);
+    }
+    save_state(out, L, L.tmx, L.tmy, L.tmz, pos);
     return (f.bx ? 0u : (f.by ? 2u : 4u)) + (up ? 1u : 0u);
 }
 
@@ -469,7 +472,7 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
                     // list prefix, not a chain)
                     int k = 0;
 #pragma unroll
-                    for (int m = 1; m <= 6; ++m) k += (m <= ti.nsrc && pre[m] <= j) ? 1 : 0;
+                    for (int m = 1; m <= 6; ++m) k += (m <= ti.nsrc() && pre[m] <= j) ? 1 : 0;
                     const uint32_t g = P.in_idx[lst[k] + (j - pre[k])];
                     const PState o = P.in_state[g];
                     load_state(N, o, B);
@@ -477,7 +480,7 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
                     ly = (int32_t)(o.pos >> 4 & 15u);
                     lz = (int32_t)(o.pos >> 8);
                     const Rec rc = rec_at<VEL>(recs, tile_slot(lx, ly, lz) * RS);
-                    if (k < ti.nsrc) finish_entry<VEL>(N, rc);   // entering through a face
+                    if (k < ti.nsrc()) finish_entry<VEL>(N, rc);   // entering through a face
                     else N.kap = rc.kap;                         // deferred inside its cell
                 }
                 to_tile<RS>(L, N, lx, ly, lz);
@@ -655,10 +658,10 @@ __global__ __launch_bounds__(BLK) void tile_walk_kernel(TileParams P)
         // the neighbours' face lists, then this tile's deferred list: one
         // thread per list reads its extent (independent reads), while every
         // thread loads the tile's records
-        if (tid <= ti.nsrc) {
+        if (tid <= ti.nsrc()) {
             const int k = tid;
-            const int f = k < ti.nsrc ? (int)((ti.src_faces >> (4 * k)) & 15u) : kDeferred;
-            const TileExits &e = P.in_exits[k < ti.nsrc ? P.tiles[T].src_tile[k] : T];
+            const int f = k < ti.nsrc() ? (int)((ti.src_faces >> (4 * k)) & 15u) : kDeferred;
+            const TileExits &e = P.in_exits[k < ti.nsrc() ? P.tiles[T].src_tile[k] : T];
             lst[k] = e.base + e.off[f];
             s_tsum[k] = e.off[f + 1] - e.off[f];
         }
@@ -666,11 +669,11 @@ __global__ __launch_bounds__(BLK) void tile_walk_kernel(TileParams P)
         __syncthreads();
         if (tid == 0) {
             uint32_t run = 0;
-            for (int k = 0; k <= ti.nsrc; ++k) {
+            for (int k = 0; k <= ti.nsrc(); ++k) {
                 pre[k] = run;
                 run += s_tsum[k];
             }
-            pre[ti.nsrc + 1] = run;
+            pre[ti.nsrc() + 1] = run;
             s_total = run;
         }
         __syncthreads();
@@ -716,6 +719,7 @@ __global__ __launch_bounds__(BLK) void tile_walk_kernel(TileParams P)
     C.sy = ti.sy;
     C.sz = ti.sz;
     C.span = ti.span & 7u;
+    C.low = ti.nsrc_low;
     C.red = P.red[ti.box];
     const char *recs = VEL ? reinterpret_cast<const char *>(srec4) : reinterpret_cast<const char *>(sreck);
     TileAcc acc{0};
@@ -879,7 +883,7 @@ __global__ __launch_bounds__(256) void tail_walk_kernel(TailParams P)
         // this tile pulls from through the opposite face)
         const uint32_t face = P.face[q][k];
         int to = lo;
-        for (int m = 0; m < src.nsrc; ++m)
+        for (int m = 0; m < src.nsrc(); ++m)
             if ((src.src_faces >> (4 * m) & 15u) == (face ^ 1u)) to = src.src_tile[m];
         const TileInfo &dst = P.tiles[to];
         Lane L;

@@ -367,6 +367,7 @@ hipError_t launch_walk_persistent(const WalkParams &p, int block, int grid, bool
 }
 
 bool box_fits_lds(uint64_t cells, bool vel) { return cells * (vel ? 16 : 4) <= (uint64_t)kBoxLds; }
+bool box_tally_fits_lds(uint64_t cells, bool vel) { return cells * (vel ? 24 : 12) <= (uint64_t)kBoxLds; }
 
 template <bool TALLY>
 static void launch_box(const WalkParams &p, dim3 g, dim3 b, hipStream_t s)
@@ -385,7 +386,7 @@ hipError_t launch_walk_box(const WalkParams &p, uint64_t cells, int block, int g
     if (reset) hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(64), 0, s, p.queue, (int)p.nqueues);
     // tallies in LDS where they fit and adding every workgroup's to the
     // device's costs less than the deposits (some 40 a packet)
-    const bool tally = cells * (p.vel ? 24 : 12) <= (uint64_t)kBoxLds && cells * (uint64_t)grid <= 10 * p.count;
+    const bool tally = box_tally_fits_lds(cells, p.vel) && cells * (uint64_t)grid <= 10 * p.count;
     if (tally) launch_box<true>(p, dim3((unsigned)grid), dim3((unsigned)block), s);
     else launch_box<false>(p, dim3((unsigned)grid), dim3((unsigned)block), s);
     return hipGetLastError();
