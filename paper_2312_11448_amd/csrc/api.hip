@@ -1671,15 +1671,17 @@ mc_lya_status mc_lya_scatter(mc_lya_ctx *c, uint64_t first, uint64_t count, cons
     p.first = first;
     p.count = count;
     p.max_events = o.max_events;
-    p.chunk = 64;
-    p.refill = 16;
+    // Photons a wave holds: two resident waves per SIMD (the issue rate needs
+    // two; three take 10 % longer at 131 072 photons) share a small call's
+    // photons, so that each has as many lanes as there are.
+    const uint64_t waves = (uint64_t)c->num_cu * 8;
+    p.fill = (int32_t)std::min<uint64_t>(64, (count + waves - 1) / waves);
     p.nqueues = (int32_t)std::min<uint64_t>(8, std::max<uint64_t>(1, count / 64));
     p.fixed_x0 = o.fixed_x0;
     p.x0 = o.x0;
     p.x_return = (float)o.x_return;
     p.records = records;
-    // resident waves: 8 workgroups of 256 per compute unit, capped by the work
-    const uint64_t want = (count + 255) / 256;
+    const uint64_t want = (count + 4 * (uint64_t)p.fill - 1) / (4 * (uint64_t)p.fill);
     const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)c->num_cu * 8, want));
     hipEvent_t e1 = nullptr;
     st = timed_begin(c, &e1);

@@ -195,7 +195,7 @@ struct ScatterParams {
     unsigned long long *queue;
     uint64_t first, count;
     uint64_t max_events;
-    int32_t chunk, refill, nqueues;
+    int32_t fill, nqueues;   // photons a wave holds at once (1..64); work queues
     int32_t fixed_x0;        // test hook: inject every photon at x0
     float x0;
     float x_return;          // test hook: > 0 stops a photon scattered back inside |x| < x_return
