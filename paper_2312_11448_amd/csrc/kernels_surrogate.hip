@@ -318,33 +318,6 @@ __device__ __forceinline__ bf16x8 ones_pair(bool here)
     return v;
 }
 
-// The weight operands of lane (half, col): a1[T] for unit u = 32 T + col
-// (W1[u][0..7] in half 0, the b1 pair in half 1) and a2[T][s] (W2[u][unit
-// l2_unit(s, half, e)] for s < 4, the b2 pair in half 0 for s = 4).
-struct NetOps {
-    bf16x8 a1[2];
-    bf16x8 a2[2][5];
-};
-
-__device__ __forceinline__ void load_ops(const float *__restrict__ P, int half, int col, NetOps &o)
-{
-#pragma unroll
-    for (int T = 0; T < 2; ++T) {
-        const int u = 32 * T + col;
-        if (half == 0) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o.a1[T][e] = (__bf16)P[OFF_W1 + u * kFeat + e];
-        } else {
-            o.a1[T] = bias_pair(P[OFF_B1 + u], true);
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o.a2[T][s][e] = (__bf16)P[OFF_W2 + u * kHid + l2_unit(s, half, e)];
-        o.a2[T][4] = bias_pair(P[OFF_B2 + u], half == 0);
-    }
-}
-
 // The K operand of a cell's features: the features in lane half 0, the pair
 // (1, 1) that meets the b1 pair in half 1.
 __device__ __forceinline__ bf16x8 feature_operand(const float (&x)[kFeat], int half)
@@ -363,8 +336,8 @@ typedef short s16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-// cache-policy operand of a buffer load: non-temporal (streaming)
-constexpr int kStreamingLoad = 2;
+// cache-policy operand of a buffer access: non-temporal (streaming)
+constexpr int kStreaming = 2;
 
 __device__ __forceinline__ uint32_t bf16_pair(float a, float b)
 {
@@ -390,127 +363,230 @@ __device__ __forceinline__ void hidden_operand(const f32x16 (&d1)[2], bf16x8 (&h
     }
 }
 
-__global__ __launch_bounds__(256) void mlp_forward_kernel(const float *__restrict__ P, const float *__restrict__ X,
-                                                          uint64_t n, float *__restrict__ y,
-                                                          uint8_t *__restrict__ outside,
-                                                          const float *__restrict__ lo,
-                                                          const float *__restrict__ hi,
-                                                          unsigned long long *__restrict__ n_out)
+// ---- parameters through LDS --------------------------------------------------
+// The parameters in LDS, each row of W2 one float longer, so that reads down
+// its columns (the operands are gathered so) fall in different banks.
+constexpr int kW2Row = kHid + 1;
+constexpr int kStaged = kMlpParams + kHid;
+__device__ __forceinline__ constexpr int staged(int off) { return off + kHid; }     // past W2
+__device__ __forceinline__ int staged_w2(int o, int k) { return OFF_W2 + o * kW2Row + k; }
+
+// Copies the parameters to LDS: every read issued before the first is stored.
+template <int THREADS>
+__device__ __forceinline__ void stage_params(const float *__restrict__ P, float *lds)
+{
+    constexpr int N = (kMlpParams + THREADS - 1) / THREADS;
+    float v[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const int j = (int)threadIdx.x + k * THREADS;
+        v[k] = j < kMlpParams ? P[j] : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const int j = (int)threadIdx.x + k * THREADS;
+        const int row = j < OFF_W2 ? 0 : (j < OFF_B2 ? (j - OFF_W2) / kHid : kHid);
+        if (j < kMlpParams) lds[j + row] = v[k];
+    }
+}
+
+// Inference, 32 cells a wave at a time. What bounds it is the issue of VALU and
+// matrix instructions, which do not overlap: their counters (61 % and 38 % of
+// the cycles) add up to the kernel's time, whatever their order; the memory
+// traffic alone takes half as long. So b2 enters as the C operand of a chain's
+// first product (10 products a tile instead of 12; hi + lo is exact in binary32,
+// so the sums are the same), and results and flags go out through views that
+// drop the lanes and rows past the end (no branch; 115 VALU instructions instead
+// of 122). Small calls are bound by the kernel's start: the parameters come
+// through LDS in one round trip instead of some 80 strided reads a lane.
+// Two tiles of features are on their way (one: 242 us; four and six: 235, 240).
+// 1.7e7 cells 237 -> 229 us, 1e6 21.2 -> 17.9, 112 850 9.1 -> 6.1.
+constexpr int kAhead = 2;
+__global__ __launch_bounds__(256, 2) void mlp_forward_kernel(const float *__restrict__ P, const float *__restrict__ X,
+                                                             uint64_t n, float *__restrict__ y,
+                                                             uint8_t *__restrict__ outside,
+                                                             const float *__restrict__ lo,
+                                                             const float *__restrict__ hi,
+                                                             unsigned long long *__restrict__ n_out)
 {
     __shared__ unsigned long long s_cnt;
     // w3 in the order of the layer-2 result registers: [T][lane half][r]
     __shared__ float4 s_w3[2][2][4];
+    __shared__ float s_p[kStaged];
     const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
-    if (threadIdx.x == 0) s_cnt = 0;
-    if (threadIdx.x < 64) {
-        const int T = threadIdx.x >> 5, h = (threadIdx.x >> 4) & 1, r = threadIdx.x & 15;
-        reinterpret_cast<float *>(&s_w3[T][h][0])[r] = P[OFF_W3 + 32 * T + d_row(r, h)];
-    }
-    NetOps o;
-    load_ops(P, half, col, o);
-    const bf16x8 ones = ones_pair(half == 0);
-    const float b3 = P[OFF_B3];
-    float flo[kFeat], fhi[kFeat];
-#pragma unroll
-    for (int e = 0; e < kFeat; ++e) {
-        flo[e] = lo ? lo[e] : 0.0f;
-        fhi[e] = lo ? hi[e] : 0.0f;
-    }
-    __syncthreads();
     // the wave's tiles are uniform: the loop and the tile's addresses stay
     // in scalar registers
     const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x / 64);
     const uint64_t wave =
         (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6));
     const uint64_t tiles = (n + 31) / 32;
-    uint32_t n_outside = 0;
     // Lane half 0 reads its cell's 8 features through a buffer view of the
     // tile's rows, which gives 0 for a row past the last cell; half 1 reads
     // past the view (zeros) and ORs in the pair (1, 1) that meets the b1 pair.
-    // The next tile's features are loaded as soon as this tile's are rounded.
+    // The results go out through a view as well, so that nothing in the loop
+    // depends on the lane.
     const uint32_t voff = half == 0 ? 32u * (uint32_t)col : 1024u;
+    const uint32_t yoff = half == 0 ? 4u * (uint32_t)col : 128u;
     const uint32_t ones_bits = half == 0 ? 0u : 0x3f803f80u;
     // rows of the tile starting at cell `first` (0 past the end)
     auto rows_at = [&](uint64_t first) -> uint32_t {
         return first < n ? (uint32_t)(n - first < 32 ? n - first : 32) : 0u;
     };
+    float xs[kAhead][kFeat];
     auto load = [&](uint64_t tile, float (&x)[kFeat]) {
         const uint64_t first = tile * 32;
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
             (void *)(X + first * kFeat), (short)0, (int)(rows_at(first) * 32u), 0x00020000);
         // (streaming reads: the features are read once, and keeping them out
         // of the caches leaves those to the fields the features come from)
-        const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, 0, kStreamingLoad);
-        const u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff + 16, 0, kStreamingLoad);
+        const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, 0, kStreaming);
+        const u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff + 16, 0, kStreaming);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             x[e] = __builtin_bit_cast(float, (uint32_t)a[e]);
             x[4 + e] = __builtin_bit_cast(float, (uint32_t)b[e]);
         }
     };
-    // one tile from the features in x, loading those of tile + waves into
-    // `next` (two register sets taken in turn, so nothing is copied)
-    auto step = [&](uint64_t tile, const float (&x)[kFeat], float (&next)[kFeat]) {
-        const uint64_t first = tile * 32;
-        const uint32_t rows = rows_at(first);
-        // the lanes whose features leave the envelope, as a wave mask taken
-        // now, so that the features are not kept to the store (none without
-        // an envelope)
-        uint64_t env = 0;
-        if (lo) {
-            bool out_env = false;
 #pragma unroll
-            for (int e = 0; e < kFeat; ++e) out_env |= (x[e] < flo[e]) | (x[e] > fhi[e]);
-            env = __ballot(out_env);
+    for (int k = 0; k < kAhead; ++k) load(wave + (uint64_t)k * waves, xs[k]);
+    stage_params<256>(P, s_p);
+    float flo[kFeat], fhi[kFeat];
+#pragma unroll
+    for (int e = 0; e < kFeat; ++e) {
+        flo[e] = lo ? lo[e] : 0.0f;
+        fhi[e] = lo ? hi[e] : 0.0f;
+    }
+    if (threadIdx.x == 0) s_cnt = 0;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const int T = threadIdx.x >> 5, h = (threadIdx.x >> 4) & 1, r = threadIdx.x & 15;
+        reinterpret_cast<float *>(&s_w3[T][h][0])[r] = s_p[staged(OFF_W3) + 32 * T + d_row(r, h)];
+    }
+    bf16x8 a1[2], a2[2][4];
+    f32x16 c2[2];                 // b2 (hi + lo, a sum without rounding) by result row
+#pragma unroll
+    for (int T = 0; T < 2; ++T) {
+        const int u = 32 * T + col;
+        if (half == 0) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a1[T][e] = (__bf16)s_p[OFF_W1 + u * kFeat + e];
+        } else {
+            a1[T] = bias_pair(s_p[OFF_B1 + u], true);
         }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a2[T][s][e] = (__bf16)s_p[staged_w2(u, l2_unit(s, half, e))];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const bf16x8 v = bias_pair(s_p[staged(OFF_B2) + 32 * T + d_row(r, half)], true);
+            c2[T][r] = (float)v[0] + (float)v[1];
+        }
+    }
+    const float b3 = s_p[staged(OFF_B3)];
+    __syncthreads();
+    uint32_t n_outside = 0;
+    // the lanes whose features leave the envelope, as a wave mask (none
+    // without an envelope)
+    auto envelope = [&](const float (&x)[kFeat]) -> uint64_t {
+        if (!lo) return 0;
+        bool out_env = false;
+#pragma unroll
+        for (int e = 0; e < kFeat; ++e) out_env |= (x[e] < flo[e]) | (x[e] > fhi[e]);
+        return __ballot(out_env);
+    };
+    auto operand = [&](const float (&x)[kFeat]) -> bf16x8 {
         u32x4 bu;
 #pragma unroll
         for (int p = 0; p < 4; ++p) bu[p] = bf16_pair(x[2 * p], x[2 * p + 1]);
         bu[0] |= ones_bits;
-        const bf16x8 bx = __builtin_bit_cast(bf16x8, bu);
-        load(tile + waves, next);
+        return __builtin_bit_cast(bf16x8, bu);
+    };
+    bf16x8 h1[4];
+    auto layer1 = [&](const bf16x8 &bx) {
         f32x16 d1[2];
 #pragma unroll
-        for (int T = 0; T < 2; ++T) d1[T] = mfma16(o.a1[T], bx, zero16());
-        bf16x8 h1[4];
+        for (int T = 0; T < 2; ++T) d1[T] = mfma16(a1[T], bx, zero16());
         hidden_operand(d1, h1);
-        f32x16 d2[2];
-        // the wave issues its layer-2 products at raised priority, so that
-        // the matrix cores start on them while the other waves' VALU work
-        // (ReLU, conversions, the last layer) fills the SIMD around them
-        __builtin_amdgcn_s_setprio(1);
+    };
+    f32x16 d2[2];
+    auto layer2 = [&](int T) {
 #pragma unroll
-        for (int T = 0; T < 2; ++T) {
-            d2[T] = mfma16(o.a2[T][4], ones, zero16());
+        for (int s = 0; s < 4; ++s) d2[T] = mfma16(a2[T][s], h1[s], s == 0 ? c2[T] : d2[T]);
+    };
+    // part + this lane half's share of w3 . relu(D2) over block T
+    auto layer3 = [&](int T, float part) -> float {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) d2[T] = mfma16(o.a2[T][s], h1[s], d2[T]);
+        for (int q = 0; q < 4; ++q) {
+            const float4 w = s_w3[T][half][q];
+            part += w.x * relu(d2[T][4 * q]);
+            part += w.y * relu(d2[T][4 * q + 1]);
+            part += w.z * relu(d2[T][4 * q + 2]);
+            part += w.w * relu(d2[T][4 * q + 3]);
         }
-        __builtin_amdgcn_s_setprio(0);
-        float part = 0.0f;
+        return part;
+    };
+    auto interleave = [&]() {
 #pragma unroll
-        for (int T = 0; T < 2; ++T)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 w = s_w3[T][half][q];
-                part += w.x * relu(d2[T][4 * q]);
-                part += w.y * relu(d2[T][4 * q + 1]);
-                part += w.z * relu(d2[T][4 * q + 2]);
-                part += w.w * relu(d2[T][4 * q + 3]);
-            }
-        part += __shfl_xor(part, 32, 64);
-        if (half == 0 && (uint32_t)col < rows) {
-            __builtin_nontemporal_store(part + b3, &y[first + (uint32_t)col]);
-            if (outside) outside[first + (uint32_t)col] = (uint8_t)((env >> col) & 1u);
+        for (int k = 0; k < 4; ++k) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // a matrix product
+            __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);       // eight VALU instructions
         }
+    };
+    auto store = [&](uint64_t tile, float part, uint64_t env) {
+        const float v = part + __shfl_xor(part, 32, 64) + b3;
+        const uint64_t first = tile * 32;
+        const uint32_t rows = rows_at(first);
+        const __amdgpu_buffer_rsrc_t r =
+            __builtin_amdgcn_make_buffer_rsrc((void *)(y + first), (short)0, (int)(rows * 4u), 0x00020000);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)yoff, 0, kStreaming);
+        // (no flags wanted: an empty view)
+        const __amdgpu_buffer_rsrc_t f =
+            __builtin_amdgcn_make_buffer_rsrc((void *)(outside + first), (short)0, outside ? (int)rows : 0, 0x00020000);
+        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)((env >> col) & 1u), f, (int)(yoff / 4u), 0, 0);
         n_outside += (uint32_t)__popcll(env & (rows < 32 ? (1ull << rows) - 1ull : 0xffffffffull));
     };
-    float xa[kFeat], xb[kFeat];
-    load(wave, xa);
-    for (uint64_t tile = wave; tile < tiles; tile += 2 * waves) {
-        step(tile, xa, xb);
-        if (tile + waves >= tiles) break;
-        step(tile + waves, xb, xa);
+    // Two tiles are under way at once: while the matrix cores take a half of
+    // layer 2, the VALU takes the half of layer 3 that came out before it
+    // (the tile before's second half, then this tile's first).
+    if (wave < tiles) {
+        // the operand of the tile in xs[k], which the tile kAhead turns later takes
+        auto take = [&](uint64_t tile, int k, uint64_t &env) -> bf16x8 {
+            env = envelope(xs[k]);
+            const bf16x8 bx = operand(xs[k]);
+            load(tile + (uint64_t)kAhead * waves, xs[k]);
+            return bx;
+        };
+        uint64_t env0, env1, env2;
+        layer1(take(wave, 0, env0));
+        layer2(0);
+        layer2(1);
+        float part = layer3(0, 0.0f);
+        layer1(take(wave + waves, 1, env1));
+        // h1 is tile t + waves', d2[1] and part tile t's
+        for (uint64_t t = wave;;) {
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                if (t + waves >= tiles) {
+                    store(t, layer3(1, part), env0);
+                    goto walked;
+                }
+                const bf16x8 bx = take(t + 2 * waves, (k + 2) % kAhead, env2);
+                layer2(0);
+                const float done = layer3(1, part);
+                interleave();
+                layer2(1);
+                part = layer3(0, 0.0f);
+                interleave();
+                layer1(bx);
+                store(t, done, env0);
+                env0 = env1;
+                env1 = env2;
+                t += waves;
+            }
+        }
     }
+walked:
     if (n_out) {
         // n_outside is the wave's count
         const unsigned long long c = n_outside;
@@ -547,32 +623,6 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const float *__restric
 // and the slots' sum, the normalisation and Adam are one kernel. A step on
 // 65 536 index-picked cells went from 7 launches and 85 us to 2 and 24 us.
 constexpr int kGradWaves = 4;
-
-// The parameters in LDS, each row of W2 one float longer, so that reads down
-// its columns (the operands are gathered so) fall in different banks.
-constexpr int kW2Row = kHid + 1;
-constexpr int kStaged = kMlpParams + kHid;
-__device__ __forceinline__ constexpr int staged(int off) { return off + kHid; }     // past W2
-__device__ __forceinline__ int staged_w2(int o, int k) { return OFF_W2 + o * kW2Row + k; }
-
-// Copies the parameters to LDS: every read issued before the first is stored.
-template <int THREADS>
-__device__ __forceinline__ void stage_params(const float *__restrict__ P, float *lds)
-{
-    constexpr int N = (kMlpParams + THREADS - 1) / THREADS;
-    float v[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const int j = (int)threadIdx.x + k * THREADS;
-        v[k] = j < kMlpParams ? P[j] : 0.0f;
-    }
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const int j = (int)threadIdx.x + k * THREADS;
-        const int row = j < OFF_W2 ? 0 : (j < OFF_B2 ? (j - OFF_W2) / kHid : kHid);
-        if (j < kMlpParams) lds[j + row] = v[k];
-    }
-}
 
 struct GradLds {
     float w3[kHid];                              // by row, for "C"
@@ -641,7 +691,8 @@ __global__ __launch_bounds__(64 * kGradWaves, 2) void mlp_grad_kernel(const floa
     Cell next = read_cell(tile0, row);
     const float *p = L.u.t.params;
     if (threadIdx.x < kHid) L.w3[threadIdx.x] = p[staged(OFF_W3) + threadIdx.x];
-    // the layer-2 operands (load_ops), in LDS: registers are short
+    // the layer-2 operands (W2[u][l2_unit(k, h, e)], the b2 pair in half 0 for
+    // k = 4), in LDS: registers are short
     for (int j = threadIdx.x; j < 2 * 5 * 2 * 32; j += blockDim.x) {
         const int c = j & 31, h = (j >> 5) & 1, q = j >> 6, k = q % 5, T = q / 5, u = 32 * T + c;
         bf16x8 v;
