@@ -203,10 +203,10 @@ enum {
     MC_LYA_OPT_TILE_REFILL = 14,  /* tiled walk: refill a wave once this many lanes are idle
                                      (1..64, default 32) */
     MC_LYA_OPT_TAIL = 15,         /* tiled walk: once fewer packets than this many millionths
-                                     of a batch are in flight (0..1000000, default 20000 =
-                                     2 %; 0 = never), one kernel walks them to the end with
-                                     device-wide deposits instead of further, thinning tile
-                                     generations */
+                                     of a batch are in flight (0..1000000; 0 = never), one
+                                     kernel walks them to the end with device-wide deposits
+                                     instead of further, thinning tile generations. Not set:
+                                     60 000 packets and 3 % of the batch, at most a fifth */
     MC_LYA_OPT_BESIDE = 16        /* kernel 2 with both parts: the persistent walk of the
                                      untiled boxes runs beside the tile generations on a
                                      stream of its own, with at most this many waves per

@@ -192,7 +192,7 @@ struct mc_lya_ctx {
     std::vector<uint64_t> graph_key;
     int graph_gens = 64;                     // tile generations inside the graph
     int eager_gens = kEagerGens;             // tile generations in the first eager round
-    int tail = 20000;                        // MC_LYA_OPT_TAIL (millionths of a batch)
+    int tail = -1;                           // MC_LYA_OPT_TAIL (millionths of a batch; -1: not set)
     uint32_t *d_tail_prefix = nullptr;       // [tiles] first tail packet of each tile
     uint64_t epoch = 0;                      // bumped whenever a buffer a graph reads is reallocated
 
@@ -494,22 +494,26 @@ constexpr int kAllTiled = 1000000;        // tile_share at or above this: every 
 // while each has kSharePackets packets to walk (128 to 1024 time alike).
 constexpr uint64_t kSharePackets = 512;
 // A lone box with fewer tiles than compute units is walked by (shared) tiles
-// from this many crossings as classify_boxes estimates them (42 a packet on
-// the 128^3 workload's fields, where they walk 87). The tiles take about 20
-// generations of 35 us however few packets there are; the persistent walk
-// takes as long as its longest packet (0.3 to 0.5 ms) and then is bound by the
-// device's 2.4e10 deposits/s, or, with its tallies in LDS, by its steps.
-// Transports, us (tiles, persistent): 48^3 with 1.1e5 packets 650, 570 and
-// with 2.2e5 680, 890; 32^3 with 1.3e5 670, 490 and with 2.6e5 716, 810; 64^3
-// with 2.6e5 708, 950 and with 1.7e7 4900, 31500. Tallies in LDS: 16^3 and
-// 20^3 with 3e5 700, 490 and 800, 490, with 1e6 1030, 1270 and 1020, 1210; the
-// longest steps (Voigt in a flow), 16^3 with 6e4 630, 870 and with 1e6 1330,
-// 1550.
-constexpr double kSharedWork = 8e6, kSharedWorkTally = 1.3e7, kSharedWorkVoigtFlow = 2e6;
-double shared_work(const mc_lya_ctx *c)
+// from this many packets; both ways' times grow alike with the length of the
+// walks. The tiles take some ten generations of 25 to 35 us and a tail however
+// few packets there are; the persistent walk takes as long as its longest
+// packet, a step of it longer with the records in L2 (a flow's, or more than
+// 39 936 cells) and with Voigt profiles, and then is bound by the device's
+// 2.4e10 deposits/s. Transports, us (tiles, persistent):
+//   records in L2: 48^3 with 4e4 packets 404, 382 and with 7e4 413, 491; in a
+//     flow 1e4 461, 456 and 4e4 482, 546; Voigt in a flow 5e3 705, 896;
+//   records in LDS: 32^3 with 7e4 409, 402 and with 1e5 410, 446;
+//   tallies in LDS, or one tile, which has no neighbours to hand packets to
+//     and keeps them to the end: 16^3 with 3e5 717, 493 and with 1e6 950, 1270;
+//     Voigt in a flow 6e4 630, 880.
+uint64_t shared_from(const mc_lya_ctx *c, int nt)
 {
-    if (!box_tally_fits_lds(c->total_cells, c->vel)) return kSharedWork;
-    return c->vel && c->voigt ? kSharedWorkVoigtFlow : kSharedWorkTally;
+    const uint64_t cells = c->total_cells, n = c->walk[0].npkt;
+    const bool lds = box_fits_lds(cells, c->vel), hard = c->vel && c->voigt;
+    const bool tally = box_tally_fits_lds(cells, c->vel) && cells * (uint64_t)c->num_cu <= 10 * n;
+    if (nt == 1 || tally) return hard ? 40000 : 400000;
+    if (hard) return 5000;
+    return lds ? 80000 : (c->vel ? 10000 : 45000);
 }
 int sharing(const mc_lya_ctx *c, int nt, uint64_t packets)
 {
@@ -545,7 +549,7 @@ mc_lya_status classify_boxes(mc_lya_ctx *c)
     if (nb == 1 && c->tile_share > 0) {
         const int nt = tiles_of_box(c->desc[0]);
         share = sharing(c, nt, c->walk[0].npkt);
-        if (cost[0] >= shared_work(c)) m[0] = 1;
+        if (c->walk[0].npkt >= shared_from(c, nt)) m[0] = 1;
         if (!m[0]) share = 1;
     }
     if (m == c->tiled && share == c->share) return MC_LYA_OK;
@@ -635,9 +639,17 @@ mc_lya_status timed_end(mc_lya_ctx *c, hipEvent_t e1)
 }
 
 // The tail walk takes over once fewer than this many of a batch's n packets
-// are in flight (MC_LYA_OPT_TAIL, in millionths of the batch).
+// are in flight (MC_LYA_OPT_TAIL, in millionths of the batch). Where it is not
+// set: 3 % and 60 000 more, at most a fifth. Each generation of tiles costs 30
+// to 150 us however few packets it walks, the tail walk as much in all plus
+// its deposits in device memory, so the best share falls with the batch:
+// transports at 2 %, here and at twice as much, us: 3.0e5 packets (64^3) 738,
+// 520, 546; 4.4e5 (48^3) 909, 725, 743; 1.65e6 (90 x 75 x 61) 1303, 1220, 1270;
+// 8e6 (150^3) 4800, 4690, 4568; 1.7e7 (128^3) 4187, 4165, 4300, with Voigt
+// 6328, 6323, 7500; 2.7e8 (256^3) 86900, 86500, 87500.
 uint64_t tail_packets(const mc_lya_ctx *c, uint64_t n)
 {
+    if (c->tail < 0) return std::min(n / 2, 60000u + n * 3 / 100);
     return (uint64_t)((unsigned __int128)n * (uint64_t)c->tail / 1000000u);
 }
 
