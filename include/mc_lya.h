@@ -228,7 +228,9 @@ enum {
  *               0): 4 N + 202 B bytes; if the states cannot be allocated,
  *               init halves B down to 2^25 packets; the tiled walk walks
  *               emissions larger than B in batches of B;
- *   per tile    its table entry and exit lists (about 140 bytes);
+ *   per tile    its table entry and exit lists (about 140 bytes); with fewer
+ *               tiles than compute units, as many entries as those, the ones
+ *               past T with a tally of 32 KB each (at most 8 MB);
  *   per box     a few hundred bytes of tables and per-block partial sums. */
 typedef struct mc_lya_limits {
     uint64_t max_packets;         /* most packets one mc_lya_emit may emit over all boxes,

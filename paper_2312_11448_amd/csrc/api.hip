@@ -163,7 +163,7 @@ struct mc_lya_ctx {
     PState *d_redlist = nullptr;             // [state_cap] packets with no deposit left to make
     uint64_t state_cap = 0;
     int64_t generations = 0;                 // generations launched by the last tiled transport
-    // a box alone in its context with fewer tiles than compute units: `share`
+    // a context with fewer tiles than compute units: `share`
     // workgroups walk each tile, each a share of its packets into a tally of its own
     int share = 1;
     unsigned long long *d_share = nullptr;   // their tallies, zero between walks
@@ -489,7 +489,7 @@ int tiles_of_box(const mc_lya_box_desc &d)
 constexpr int kMinTiles = 8;              // fewer tiles than this never pays
 constexpr int kAllTiled = 1000000;        // tile_share at or above this: every box is tiled
 
-// How many workgroups walk each of a lone box's nt tiles (1 with as many tiles
+// How many workgroups walk each of a context's nt tiles (1 with as many tiles
 // as compute units): as many as the chip holds at once, one per compute unit,
 // while each has kSharePackets packets to walk (128 to 1024 time alike).
 constexpr uint64_t kSharePackets = 512;
@@ -515,6 +515,16 @@ uint64_t shared_from(const mc_lya_ctx *c, int nt)
     if (hard) return 5000;
     return lds ? 80000 : (c->vel ? 10000 : 45000);
 }
+// A batch with fewer tiles than compute units takes (shared) tiles from this
+// many packets a tile, if all its boxes are of one tile or else; a box whose
+// tiles would have more than four times the mean work is left to the
+// persistent walk, which is bound by the deposits in device memory. Boxes of
+// several tiles and very different walks take as many generations as the
+// longest. Transports, us (tiles, persistent): 24 boxes of up to 14^3, 1300
+// packets a tile 774, 692 and 8000 941, 2516; 8 of up to 24^3, 331 776 packets
+// 3573, 4442 and 55 296 1753, 966; 6 of up to 40^3, 2.7e5 3382, 2854, 5.8e5
+// 4071, 5655 and 1.2e6 5809, 10598.
+constexpr uint64_t kBatchLone = 2500, kBatchTile = 30000;
 int sharing(const mc_lya_ctx *c, int nt, uint64_t packets)
 {
     const uint64_t per = packets / ((uint64_t)nt * kSharePackets);
@@ -551,6 +561,27 @@ mc_lya_status classify_boxes(mc_lya_ctx *c)
         share = sharing(c, nt, c->walk[0].npkt);
         if (c->walk[0].npkt >= shared_from(c, nt)) m[0] = 1;
         if (!m[0]) share = 1;
+    } else if (c->tile_share > 0) {
+        int all = 0;
+        bool lone_tiles = true;
+        uint64_t packets = 0;
+        for (int b = 0; b < nb; ++b) {
+            const int t = tiles_of_box(c->desc[b]);
+            all += t;
+            lone_tiles = lone_tiles && t == 1;
+            packets += c->walk[b].npkt;
+        }
+        if (all < c->num_cu && packets >= (uint64_t)all * (lone_tiles ? kBatchLone : kBatchTile)) {
+            int nt = 0;
+            packets = 0;
+            for (int b = 0; b < nb; ++b) {
+                const int t = tiles_of_box(c->desc[b]);
+                if (cost[b] / t <= 0.04 * c->tile_share * total / all) m[b] = 1;
+                nt += m[b] ? t : 0;
+                packets += m[b] ? c->walk[b].npkt : 0;
+            }
+            if (nt) share = sharing(c, nt, packets);
+        }
     }
     if (m == c->tiled && share == c->share) return MC_LYA_OK;
     HIP_TRY(c, hipStreamSynchronize(c->stream));      // the previous table may still be in flight
@@ -1271,8 +1302,8 @@ mc_lya_status mc_lya_init(mc_lya_ctx **out, const mc_lya_box_desc *boxes, int32_
     c->tiled.assign(n_boxes, 1);         // the tile table starts with every box; emit narrows it
     build_tiles(c);
     const size_t nt0 = c->tiles.size();
-    // (a lone box with few tiles: room for its tiles shared among the chip's workgroups)
-    const size_t nt = n_boxes == 1 ? std::max<size_t>(nt0, (size_t)c->num_cu) : nt0;
+    // (few tiles: room for them shared among the chip's workgroups)
+    const size_t nt = std::max<size_t>(nt0, (size_t)c->num_cu);
     c->share_cells = (nt - nt0) * (size_t)kTileCells;
     // the buffers' places in d_all (and, second time round, their addresses)
     const size_t nb = (size_t)n_boxes;
