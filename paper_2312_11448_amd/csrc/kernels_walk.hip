@@ -103,6 +103,7 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
     Lane L;
     idle_lane(L);
     Line ln{0.0f, 0.0f, 0.0f};
+    if (LONE) ln = line_of(P.boxes[0]);   // (uniform: no per-lane branch for the length of a segment)
     Acc acc{-1, 0, 0, 0, 0, 0};
     bool alive = false;
     bool red = false;                 // holds a packet with no deposit left, to be counted to its end
@@ -178,7 +179,7 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
                     acc.box = nb;
                     const WalkBox &B = sbox[nb];
                     init_packet<VEL, VOIGT>(L, B, gp - B.pkt_off, P.cell_of_packet[gp], P.rec);
-                    if (VOIGT) ln = line_of(B);
+                    if (VOIGT && !LONE) ln = line_of(B);
                     alive = true;
                     sure = red_of(nb).mode != kRedOff;
                 }
