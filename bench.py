@@ -10,8 +10,10 @@ largest single-box workload; --config c2 runs the 128^3 box with 1e7 packets).
 
 Prints one JSON line (rank 0). The dominant kernel's roofline uses the walk
 kernel's duration measured with HIP events on the library's stream and the
-algorithmic bytes per crossing (one 16-byte cell record read, one 8-byte
-tally update). The CPU baseline is the FP64 oracle on a bounded sample.
+algorithmic bytes per stepped crossing (one 16-byte cell record read, one
+8-byte tally update); the crossings of a packet that can make no further
+deposit are counted without steps and carry no bytes there. The CPU baseline
+is the FP64 oracle on a bounded sample.
 """
 import argparse
 import csv
@@ -32,12 +34,14 @@ HBM_PEAK_GBS = 8000.0
 # the sources of the dominant kernel (the tiled walk): stored byte counters are
 # only reported while these are unchanged
 WALK_SOURCES = ("paper_2312_11448_amd/csrc/walk_core.hpp", "paper_2312_11448_amd/csrc/kernels_tiled.hip",
+                "paper_2312_11448_amd/csrc/red_core.hpp", "paper_2312_11448_amd/csrc/kernels_red.hip",
                 "paper_2312_11448_amd/csrc/common.hpp")
 # the walk's launches: tile generations and the tail walk (its one-block
-# prefix kernel is timed with it and counted in its bytes, not as a launch)
+# prefix kernel and the counting of the packets with no deposit left are timed
+# with it and in its bytes, not as launches)
 WALK_KERNEL = "tile_walk_kernel"
 WALK_LAUNCH_KERNELS = ("tile_walk_kernel", "tail_walk_kernel")
-WALK_BYTE_KERNELS = ("tile_walk_kernel", "tail_walk_kernel", "tail_prefix_kernel")
+WALK_BYTE_KERNELS = ("tile_walk_kernel", "tail_walk_kernel", "tail_prefix_kernel", "red_list_kernel")
 
 
 _COMMENT = re.compile(r"//[^\n]*|/\*.*?\*/", re.S)
@@ -58,6 +62,21 @@ def source_hash(paths):
 
 def walk_source_hash():
     return source_hash(WALK_SOURCES)
+
+
+def stepped_share(config, profile):
+    """Share of the workload's crossings that the walk steps (the rest are
+    counted: packets past their last deposit), from a counting build; None
+    once the walk's sources have changed."""
+    try:
+        with open(os.path.join(ROOT, "profiles", "walk_stepped.json")) as fh:
+            rows = json.load(fh)
+    except OSError:
+        return None
+    for r in rows:
+        if r["config"] == config and r["profile"] == profile and r["source_sha256"] == walk_source_hash():
+            return r["stepped_share"]
+    return None
 
 
 def parse():
@@ -83,8 +102,7 @@ def parse():
                     help="replay each transport as a captured HIP graph (default 0)")
     ap.add_argument("--tail", type=int, default=None, metavar="PPM",
                     help="MC_LYA_OPT_TAIL: the tail walk takes over below this many millionths of the packets in "
-                         "flight (default: the library's 2 % for a single box, 20 % for the batch, whose last "
-                         "generations are held by a few crowded tiles of its low-redshift boxes)")
+                         "flight (default: the library's rule)")
     ap.add_argument("--autotune", action="store_true",
                     help="tune the walk options on the first emission, before the warm-up")
     ap.add_argument("--cpu-seconds", type=float, default=20.0,
@@ -522,7 +540,7 @@ def main():
     sim.set_option(M.MC_LYA_OPT_TIMING, 2)
     graph = a.graph if a.graph is not None else 0
     sim.set_option(M.MC_LYA_OPT_GRAPH, graph)
-    tail = a.tail if a.tail is not None else (200000 if a.config == "batch" else None)
+    tail = a.tail
     if tail is not None:
         sim.set_option(M.MC_LYA_OPT_TAIL, tail)
     seeds, npk = [s.seed for s in specs], [s.n_packets for s in specs]
@@ -563,7 +581,8 @@ def main():
     walk_s = kms / 1e3 / a.steps
     cross_per_step = cross / a.steps
     bpc = BYTES_PER_CROSSING_VEL if specs[0].velocity is not None else BYTES_PER_CROSSING_NOVEL
-    achieved = bpc * cross_per_step / walk_s / 1e9
+    share = stepped_share(a.config, a.profile)
+    achieved = None if share is None else bpc * share * cross_per_step / walk_s / 1e9
     traffic = None
     if os.path.exists(a.traffic):
         with open(a.traffic) as fh:
@@ -600,11 +619,12 @@ def main():
                    "walk_ms": walk_s * 1e3,
                    "walk_launches_per_step": launches / a.steps,
                    "walk_launch_avg_us": kms * 1e3 / max(1, launches),
-                   "walk_alg_bytes_per_launch": bpc * cross / max(1, launches),
+                   "walk_alg_bytes_per_launch": None if share is None else bpc * share * cross / max(1, launches),
+                   "stepped_share": share,
                    "walk_crossings_per_s": cross_per_step / walk_s,
                    "f_absorbed": f["stats"][0].f_absorbed, "c_mc": f["stats"][0].c_mc},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS,
+                     "frac": None if achieved is None else achieved / HBM_PEAK_GBS,
                      "traffic": None if traffic is None else traffic * a.steps / max(1, launches)},
         "roofline_valu": {"bound": "alu", "achieved": valu, "peak": VALU_PEAK_GINSTR,
                           "unit": "G wave-instr/s (VALU issue)",
