@@ -202,8 +202,9 @@ mc_lya_status mc_lya_mlp_gradient(mc_lya_mlp *m, const float *features, const fl
     mc_lya_status st = check_batch(m, features, n);
     if (st != MC_LYA_OK) return st;
     if (n == 0 || !targets || !weights) return mlp_fail(m, MC_LYA_EINVAL, "need cells, targets and weights");
-    const int blocks = launch_mlp_gradient(m->d_params, features, targets, weights, n, nullptr, 0, nullptr, m->d_part,
-                                           m->stream);
+    int blocks = 0;
+    MLP_TRY(m, launch_mlp_gradient(m->d_params, features, targets, weights, n, nullptr, 0, nullptr, m->d_part, &blocks,
+                                   m->stream));
     MLP_TRY(m, launch_mlp_mean_gradient(m->d_part, blocks, m->d_grad, m->stream));
     MLP_TRY(m, hipMemcpyAsync(m->pin, m->d_grad, sizeof(float) * (kMlpParams + 2), hipMemcpyDeviceToHost, m->stream));
     MLP_TRY(m, hipStreamSynchronize(m->stream));
@@ -224,8 +225,9 @@ mc_lya_status mc_lya_mlp_train_step(mc_lya_mlp *m, const float *features, const 
     if (!hp || !(hp->lr > 0.0f) || !(hp->beta1 >= 0.0f && hp->beta1 < 1.0f) ||
         !(hp->beta2 >= 0.0f && hp->beta2 < 1.0f) || !(hp->eps > 0.0f))
         return mlp_fail(m, MC_LYA_EINVAL, "Adam needs lr > 0, beta1 and beta2 in [0, 1), eps > 0");
-    const int blocks = launch_mlp_gradient(m->d_params, features, targets, weights, n, nullptr, 0, nullptr, m->d_part,
-                                           m->stream);
+    int blocks = 0;
+    MLP_TRY(m, launch_mlp_gradient(m->d_params, features, targets, weights, n, nullptr, 0, nullptr, m->d_part, &blocks,
+                                   m->stream));
     const int64_t t = m->step + 1;
     MlpAdam a;
     a.lr = hp->lr;
@@ -274,8 +276,9 @@ mc_lya_status mc_lya_mlp_train_steps(mc_lya_mlp *m, const float *features, const
     }
     MLP_TRY(m, hipMemsetAsync(m->d_bad, 0, sizeof(unsigned int), m->stream));
     for (int s = 0; s < n_steps; ++s) {
-        const int blocks = launch_mlp_gradient(m->d_params, features, targets, weights, batch, idx + (size_t)s * batch,
-                                               n_cells, m->d_bad, m->d_part, m->stream);
+        int blocks = 0;
+        MLP_TRY(m, launch_mlp_gradient(m->d_params, features, targets, weights, batch, idx + (size_t)s * batch, n_cells,
+                                       m->d_bad, m->d_part, &blocks, m->stream));
         const int64_t t = m->step + 1;
         MlpAdam a;
         a.lr = lr[s];
@@ -363,8 +366,9 @@ mc_lya_status mc_lya_mlp_gradient_static(const float *params, const float *featu
     mc_lya_status st = scratch_address(&ws);
     if (st != MC_LYA_OK) return st;
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    const int blocks = launch_mlp_gradient(params, features, targets, weights, n, nullptr, 0, nullptr, ws, s);
-    const hipError_t e = launch_mlp_mean_gradient(ws, blocks, grad_out, s);
+    int blocks = 0;
+    hipError_t e = launch_mlp_gradient(params, features, targets, weights, n, nullptr, 0, nullptr, ws, &blocks, s);
+    if (e == hipSuccess) e = launch_mlp_mean_gradient(ws, blocks, grad_out, s);
     if (e != hipSuccess) return static_fail(MC_LYA_EDEVICE, std::string("launch: ") + hipGetErrorString(e));
     return MC_LYA_OK;
 }

@@ -439,9 +439,11 @@ int mlp_forward_blocks_per_cu();
 // The gradient's per-block partial sums over n cells (idx != NULL: rows
 // idx[0..n) of the n_cells rows of X, t, w; an index outside them reads row 0
 // and sets *bad) into partial[blocks][kMlpPartStride], blocks <=
-// kMlpGradBlocks; returns the number of blocks.
-int launch_mlp_gradient(const float *params, const float *X, const float *t, const float *w, uint64_t n,
-                        const int64_t *idx, uint64_t n_cells, unsigned int *bad, float *partial, hipStream_t s);
+// kMlpGradBlocks (their number to *blocks). Whoever sums them checks the
+// status first: a failed launch leaves an earlier call's sums there.
+hipError_t launch_mlp_gradient(const float *params, const float *X, const float *t, const float *w, uint64_t n,
+                               const int64_t *idx, uint64_t n_cells, unsigned int *bad, float *partial, int *blocks,
+                               hipStream_t s);
 // Their sum: the mean gradient, sum w r^2 and sum w into grad[kMlpParams + 2]
 hipError_t launch_mlp_mean_gradient(const float *partial, int blocks, float *grad, hipStream_t s);
 // ... or one Adam step with it, the two sums into tail[2]

@@ -1023,8 +1023,9 @@ int mlp_forward_blocks_per_cu()
     return b;
 }
 
-int launch_mlp_gradient(const float *params, const float *X, const float *t, const float *w, uint64_t n,
-                        const int64_t *idx, uint64_t n_cells, unsigned int *bad, float *partial, hipStream_t s)
+hipError_t launch_mlp_gradient(const float *params, const float *X, const float *t, const float *w, uint64_t n,
+                               const int64_t *idx, uint64_t n_cells, unsigned int *bad, float *partial, int *blocks_out,
+                               hipStream_t s)
 {
     // Two tiles a wave, up to one block a compute unit, then up to
     // kMlpGradBlocks (two a unit) of longer runs: fewer partial-sum slots to
@@ -1032,13 +1033,14 @@ int launch_mlp_gradient(const float *params, const float *X, const float *t, con
     // summation order is too.
     const uint64_t tiles = (n + 31) / 32, per = 2 * kGradWaves;
     const int blocks = (int)std::max<uint64_t>(1, std::min<uint64_t>(kMlpGradBlocks, (tiles + per - 1) / per));
+    *blocks_out = blocks;
     if (idx)
         hipLaunchKernelGGL(mlp_grad_kernel<true>, dim3((unsigned)blocks), dim3(64 * kGradWaves), 0, s, params, X, t,
                            w, n, idx, n_cells, bad, partial);
     else
         hipLaunchKernelGGL(mlp_grad_kernel<false>, dim3((unsigned)blocks), dim3(64 * kGradWaves), 0, s, params, X, t,
                            w, n, idx, n_cells, bad, partial);
-    return blocks;
+    return hipGetLastError();
 }
 
 constexpr unsigned kRedGrid = (kMlpParams + 2 + 63) / 64;
