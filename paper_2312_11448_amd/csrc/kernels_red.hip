@@ -106,24 +106,25 @@ __global__ void red_mark_kernel(unsigned long long *counters)
 }
 
 template <bool VOIGT>
-void launch(const RedParams &p, dim3 g, bool vel, hipStream_t s)
+hipError_t launch(const RedParams &p, dim3 g, bool vel, hipStream_t s)
 {
     const dim3 b(kRedBlock);
-    if (vel) {
-        hipLaunchKernelGGL((red_list_kernel<true, VOIGT, false>), g, b, 0, s, p);
-        hipLaunchKernelGGL((red_list_kernel<true, VOIGT, true>), g, b, 0, s, p);
-    } else {
+    if (!vel) {
         hipLaunchKernelGGL((red_list_kernel<false, VOIGT, false>), g, b, 0, s, p);
+        return hipGetLastError();
     }
+    hipLaunchKernelGGL((red_list_kernel<true, VOIGT, false>), g, b, 0, s, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((red_list_kernel<true, VOIGT, true>), g, b, 0, s, p);
+    return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_red_list(const RedParams &p, int grid, bool vel, bool voigt, hipStream_t s)
 {
-    if (voigt) launch<true>(p, dim3((unsigned)grid), vel, s);
-    else launch<false>(p, dim3((unsigned)grid), vel, s);
-    return hipGetLastError();
+    return voigt ? launch<true>(p, dim3((unsigned)grid), vel, s) : launch<false>(p, dim3((unsigned)grid), vel, s);
 }
 
 hipError_t launch_red_mark(unsigned long long *counters, hipStream_t s)

@@ -237,6 +237,9 @@ hipError_t launch_feed_sums(const PackBox *pb_dev, int n_boxes, int max_blk, con
                             unsigned long long *box_abs, hipStream_t s)
 {
     hipLaunchKernelGGL(feed_sums_kernel, grid2(max_blk, n_boxes), dim3(B), 0, s, pb_dev, wgt, A, partials, max_blk);
+    // (checked before the reduction, which would take a failed launch's old sums)
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(feed_reduce_kernel, dim3((unsigned)n_boxes), dim3(B), 0, s, pb_dev, partials, sums, box_abs,
                        max_blk);
     return hipGetLastError();
