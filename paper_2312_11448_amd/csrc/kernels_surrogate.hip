@@ -336,6 +336,7 @@ typedef short s16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 // cache-policy operand of a buffer access: non-temporal (streaming)
 constexpr int kStreaming = 2;
 
@@ -677,8 +678,11 @@ __global__ __launch_bounds__(64 * kGradWaves, 2) void mlp_grad_kernel(const floa
                 i = 0;
             }
             if (half == 0) {
-                c.a = *reinterpret_cast<const float4 *>(X + i * kFeat);
-                c.b = *reinterpret_cast<const float4 *>(X + i * kFeat + 4);
+                // (a row starts at any float: the caller's rows are read where they lie)
+                const f32x4_any a = *reinterpret_cast<const f32x4_any *>(X + i * kFeat);
+                const f32x4_any b = *reinterpret_cast<const f32x4_any *>(X + i * kFeat + 4);
+                c.a = make_float4(a[0], a[1], a[2], a[3]);
+                c.b = make_float4(b[0], b[1], b[2], b[3]);
             }
             c.tv = tgt[i];
             c.wv = wgt[i];
