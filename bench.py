@@ -34,7 +34,8 @@ HBM_PEAK_GBS = 8000.0
 # the sources of the dominant kernel (the tiled walk): stored byte counters are
 # only reported while these are unchanged
 WALK_SOURCES = ("paper_2312_11448_amd/csrc/walk_core.hpp", "paper_2312_11448_amd/csrc/kernels_tiled.hip",
-                "paper_2312_11448_amd/csrc/red_core.hpp", "paper_2312_11448_amd/csrc/kernels_red.hip",
+                "paper_2312_11448_amd/csrc/red_core.hpp", "paper_2312_11448_amd/csrc/red_bound.hpp",
+                "paper_2312_11448_amd/csrc/kernels_red.hip",
                 "paper_2312_11448_amd/csrc/common.hpp")
 # the walk's launches: tile generations and the tail walk (its one-block
 # prefix kernel and the counting of the packets with no deposit left are timed

@@ -299,38 +299,6 @@ std::string check_desc(const mc_lya_box_desc &d, int b)
     return std::string();
 }
 
-// The constants of red_only and red_count for a box with largest kappa kmax,
-// drift delta, threshold x_eff and largest flow deviation udev from the mean
-// flow u. The bounds: a segment is at most 1.75 cells long; the thermal
-// profile at x is exp(-x^2)/sqrt(pi); the Voigt correction -(2a/pi) F'(x) is at
-// most damp 0.85 / x^2 for |x| >= 1; 2 % for the binary32 evaluation. One
-// face rounds x twice (the drift, the jump), by at most half an ulp of x_eff's
-// binade each, and the jump's difference of projections once; a segment's
-// length by 2^-24 of itself.
-// With a flow, red_count's decisions are unsure within the sum of those
-// roundings over the walk that is left, so it pays where that sum is well
-// below a cell's drift: at most a quarter of delta (at delta = 0.019, the
-// paper's cells, it is under 3 % of it, and some 2 % of the packets are
-// unsure; below delta = 0.006 most would be).
-RedBox red_constants(double kmax, double delta, double x_eff, const double u[3], double udev, bool vel, double damp)
-{
-    RedBox r;
-    std::memset(&r, 0, sizeof r);
-    r.cg = (float)(std::max(kmax, 0.0) * delta * 1.75 * 0.5641895835477563 * 1.02);
-    r.cv = (float)(std::max(kmax, 0.0) * delta * 1.75 * damp * 0.85 * 1.02);
-    for (int a = 0; a < 3; ++a) r.ub[a] = (float)u[a];
-    r.udev = (float)(udev * 1.0001 + 1e-4);
-    auto half_ulp = [](double v) { return std::ldexp(1.0, std::ilogb(std::max(v, 1e-30)) - 24); };
-    const double round = 1.02 * (2.0 * half_ulp(x_eff) + half_ulp(2.0 * udev + 1e-6) + delta * 1.75 * 0x1p-24);
-    r.round = (float)round;
-    r.binade = (float)std::ldexp(1.0, std::ilogb(std::max(x_eff, 1e-30)));
-    const bool still = !vel || (udev == 0.0 && u[0] == 0.0 && u[1] == 0.0 && u[2] == 0.0);
-    const double most = 1.7321 * 2.0 * (x_eff + udev) / delta + 4.0;
-    const bool fine = std::isfinite(r.cg) && std::isfinite(r.cv) && std::isfinite(x_eff) && delta > 0.0;
-    r.mode = !fine ? kRedOff : still ? kRedStill : round * most <= 0.25 * delta ? kRedFlow : kRedOff;
-    return r;
-}
-
 // Expected crossings per packet in a homogeneous box with opacity kappa per
 // unit Phi, drift delta per cell, escape at -x_eff and packet weight w0. A
 // packet emitted at x0 walks until its weight rounds to zero, once

@@ -6,6 +6,7 @@
 #include <cstdint>
 
 #include "mc_lya.h"
+#include "red_bound.hpp"
 
 namespace mclya {
 
@@ -54,21 +55,6 @@ struct BoxRed {
     float kappa_max;      // largest kappa_c
     uint64_t qtot;        // sum of the quantised weights
 };
-
-// Per-box constants of the deposit-free end of an escaping packet's walk
-// (red_core.hpp): a later deposit is at most w (cg exp(-xup^2) + cv / xup^2),
-// xup the largest frequency still to come.
-enum : int32_t { kRedOff = 0, kRedStill = 1, kRedFlow = 2 };   // not used, no flow, flow
-struct alignas(64) RedBox {
-    float cg, cv;
-    float ub[3];          // <U>
-    float udev;           // max |U_c - <U>|, rounded up
-    float round;          // bound on the binary32 roundings of x at one face
-    float binade;         // largest power of two <= x_eff
-    int32_t mode;
-    int32_t pad;
-};
-static_assert(sizeof(RedBox) == 64, "RedBox layout");
 
 // Per-box running totals of the walk (device, int64).
 struct BoxTot {

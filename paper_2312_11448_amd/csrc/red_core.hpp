@@ -130,13 +130,12 @@ __device__ __forceinline__ RedEnd red_count(const Lane &L, const RedBox &R, cons
     const double rd = 1.0 / (double)L.delta;
     const double t0 = L.t;
     // crossings left at most (every ray crosses at most sqrt 3 faces per unit
-    // length), and with them the sum of the walk's roundings: R.round a face,
-    // half that while |x| is below the binade of x_eff in every cell
+    // length), and with them the bound on the sum of the walk's roundings
     const double xc = X - (double)kub;
     const float far = fmaxf((float)((xc + (double)R.udev + (double)L.xeff) * rd), 0.0f);
     const float near = fmaxf((float)((xc - (double)R.udev + (double)R.binade) * rd), 0.0f);
     const float most = fmaf(1.7321f, far, 4.0f);
-    const float eps = fmaf(R.round, fmaf(1.7321f, far - 0.5f * fminf(near, far), 4.0f), 2e-6f);
+    const float eps = red_eps(R, far, near);
     const double safe = t0 + (xc - (double)R.udev + (double)L.xeff - 2.0 * (double)eps) * rd;
     double tmx = L.tmx, tmy = L.tmy, tmz = L.tmz, t = t0;
     int32_t ix = L.ix, iy = L.iy, iz = L.iz;
