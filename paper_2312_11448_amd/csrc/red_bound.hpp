@@ -25,6 +25,7 @@ struct alignas(64) RedBox {
     float udev;           // max |U_c - <U>|, rounded up
     float round_x;        // bound on the two binary32 roundings of x at one face, |x| <= x_eff
     float round_jump;     // ... on those of the jump's difference and of the segment's length
+    float slack;          // roundings of the count itself: X and k.U at the flow's size
     float binade;         // largest power of two <= x_eff
     int32_t mode;
 };
@@ -51,14 +52,18 @@ inline RedBox red_constants(double kmax, double delta, double x_eff, const doubl
     r.cg = (float)(std::max(kmax, 0.0) * delta * 1.75 * 0.5641895835477563 * 1.02);
     r.cv = (float)(std::max(kmax, 0.0) * delta * 1.75 * damp * 0.85 * 1.02);
     for (int a = 0; a < 3; ++a) r.ub[a] = (float)u[a];
-    r.udev = (float)(udev * 1.0001 + 1e-4);
     auto half_ulp = [](double v) { return std::ldexp(1.0, std::ilogb(std::max(v, 1e-30)) - 24); };
+    // X = x + k.U and the projections k.<U> and k.U are as large as the flow:
+    // a handful of roundings at that size
+    const double moving = 8.0 * half_ulp(std::fabs(u[0]) + std::fabs(u[1]) + std::fabs(u[2]) + udev + x_eff);
+    r.udev = (float)(udev * 1.0001 + std::max(1e-4, moving));
+    r.slack = (float)std::max(2e-6, moving);
     r.round_x = (float)(1.02 * 2.0 * half_ulp(x_eff));
     r.round_jump = (float)(1.02 * (half_ulp(2.0 * udev + 1e-6) + delta * 1.75 * 0x1p-24));
     r.binade = (float)std::ldexp(1.0, std::ilogb(std::max(x_eff, 1e-30)));
     const bool still = !vel || (udev == 0.0 && u[0] == 0.0 && u[1] == 0.0 && u[2] == 0.0);
     const double most = 1.7321 * 2.0 * (x_eff + udev) / delta + 4.0;
-    const double sum = ((double)r.round_x + (double)r.round_jump) * most;
+    const double sum = ((double)r.round_x + (double)r.round_jump) * most + (double)r.slack;
     const bool fine = std::isfinite(r.cg) && std::isfinite(r.cv) && std::isfinite(x_eff) && delta > 0.0;
     r.mode = !fine ? kRedOff : still ? kRedStill : sum <= 0.25 * delta ? kRedFlow : kRedOff;
     return r;
@@ -71,7 +76,7 @@ inline RedBox red_constants(double kmax, double delta, double x_eff, const doubl
 MCLYA_HOST_DEVICE float red_eps(const RedBox &R, float far, float near)
 {
     const float faces = fmaf(1.7321f, far, 4.0f);
-    return fmaf(R.round_x, fmaf(-0.86605f, fminf(near, far), faces), fmaf(R.round_jump, faces, 2e-6f));
+    return fmaf(R.round_x, fmaf(-0.86605f, fminf(near, far), faces), fmaf(R.round_jump, faces, R.slack));
 }
 
 }  // namespace mclya

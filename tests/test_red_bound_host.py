@@ -77,3 +77,41 @@ def test_bound_holds_face_by_face(red, x_esc, udev):
             assert eps >= worst_sum(delta, x_eff, udev, xc) + 2.0 * half_ulp(x_eff), (delta, xc)
             used += 1
     assert used
+
+
+@pytest.mark.parametrize("u", [(0.0, 0.0, 0.0), (20.0, -30.0, 10.0), (60.0, 0.0, -80.0), (300.0, 200.0, -100.0),
+                               (3e3, -1e3, 2e3)])
+def test_bound_holds_in_a_moving_frame(red, u):
+    """With a mean flow the comoving frequency X = x + k.U is as large as the
+    flow: its cast to binary32, the difference X - k.U and the mean flow's own
+    projection round at that size, not at x's."""
+    udev, x_esc = 0.3, 6.0
+    x_eff = float(np.float32(x_esc + 2.0 * udev))
+    size = float(np.linalg.norm(u)) + udev + x_eff
+    proj = sum(abs(a) for a in u)
+    # the projection: three roundings of the sum, one of each component
+    proj_err = (3.0 * half_ulp(proj) + sum(half_ulp(a) for a in u)) if proj else 0.0
+    used = 0
+    for delta in (0.02, 0.2, 0.6):
+        for xc in np.linspace(-2.0, -x_eff + udev + 0.05, 5):
+            far = np.float32((xc + udev + 1e-4 + x_eff) / delta)
+            near = np.float32(max((xc - udev - 1e-4 + 4.0) / delta, 0.0))
+            mode, eps, ud = red(delta, x_eff, u, udev, far, near)
+            if mode != 2:
+                continue
+            walk = worst_sum(delta, x_eff, udev, xc)
+            assert eps >= walk + half_ulp(size) + half_ulp(x_eff + 2.0 * udev), (delta, xc)
+            # the cells passed over: 2 eps and udev's margin hold the projection's error too
+            assert 2.0 * eps + ud - udev >= walk + proj_err, (delta, xc)
+            used += 1
+    assert used or proj > 1e3
+
+
+def test_end_margin_holds_in_a_moving_frame(red):
+    """The frequency that decides whether a packet is past its last deposit is
+    formed in binary32 at the flow's size: udev's margin holds its rounding."""
+    for u in ((0.0, 0.0, 0.0), (60.0, 0.0, -80.0), (3e3, -1e3, 2e3)):
+        proj = sum(abs(a) for a in u)
+        err = 2.0 * half_ulp(proj + 10.0) + 3.0 * half_ulp(proj) + sum(half_ulp(a) for a in u)
+        _, _, ud = red(0.2, 6.6, u, 0.3)
+        assert ud - 0.3 >= err
