@@ -1151,10 +1151,15 @@ mc_lya_status launch_global_walk(mc_lya_ctx *c, const WalkParams &p, bool timed,
         int grid = c->num_cu * per_cu;
         const uint64_t need = (count + 63) / 64;     // no more waves than packets
         if ((uint64_t)grid * waves_per_block > need) grid = (int)std::max<uint64_t>(1, (need + waves_per_block - 1) / waves_per_block);
-        // few packets: every wave gets some (a whole chunk each would leave
-        // most waves without)
+        // Few packets: a chunk for each of four waves a compute unit, one per
+        // SIMD (whole chunks would leave most of the chip without; one for
+        // every resident wave leaves none to refill the lanes that finish
+        // first). Transports with 256 a chunk, with one for all 3072 waves,
+        // with this, us: 28 518 packets (23^3, flow) 632, 416, 416; 62 046
+        // (Voigt, flow) 970, 785, 783; 139 172 (30^3, Voigt, flow) 683, 751,
+        // 708; 156 927 (Voigt, flow) 616, 712, 626; from 262 144 on 256.
         WalkParams q = p;
-        const uint64_t each = count / ((uint64_t)grid * waves_per_block);
+        const uint64_t each = count / (4 * (uint64_t)c->num_cu);
         q.chunk = (int32_t)std::min<uint64_t>((uint64_t)p.chunk, std::max<uint64_t>(64, each));
         HIP_TRY(c, launch_walk_persistent(q, c->block, grid, !c->queue_clear || !timed, c->stream));
         c->queue_clear = false;
