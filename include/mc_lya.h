@@ -196,7 +196,9 @@ enum {
     MC_LYA_OPT_DEFER = 12,        /* tiled walk: once a tile's input is used up, a wave with
                                      at most this many live packets (0..64, default 16) hands
                                      them to the tile's next generation instead of walking on
-                                     with idle lanes (tiles that took >= 2048 packets) */
+                                     with idle lanes (tiles that took >= 2048 packets; a tile that
+                                     spans its box along an axis, whatever it took, unless every
+                                     box is a single tile) */
     MC_LYA_OPT_TILE_CHUNK = 13,   /* tiled walk: packets a wave takes from its tile's input at
                                      once (1..1024, default 512; smaller claims near the end
                                      of the input) */

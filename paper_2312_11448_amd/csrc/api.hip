@@ -669,6 +669,9 @@ TileParams tile_params(mc_lya_ctx *c, uint64_t first, uint64_t n)
     p.refill = c->tile_refill;
     p.defer_lanes = c->defer;
     p.defer_min = 2048;
+    p.defer_any = 0;
+    for (int b = 0; b < c->n_boxes; ++b)
+        if (c->tiled[b] && tiles_of_box(c->desc[b]) > 1) p.defer_any = 1;
     p.tail_min = tail_packets(c, n);
     p.tail_gen = c->d_gen + kTailGenSlot;
     p.red = c->d_redbox;

@@ -294,6 +294,7 @@ struct TileParams {
     int32_t refill;          // refill a wave once this many lanes are idle
     int32_t defer_lanes;     // once the tile's input is used up, a wave with at most this many live lanes
     uint32_t defer_min;      // ... defers them to the next generation, if the tile took >= defer_min packets
+    int32_t defer_any;       // ... or, in a tile that spans its box along some axis, whatever it took
     int32_t gen;             // index of this generation in the batch
     uint64_t tail_min;       // fewer packets in flight than this: stop and leave them to the tail walk
     unsigned long long *tail_gen;   // where the first generation that stops records its index

@@ -1,0 +1,64 @@
+"""Tiles that span their box along an axis (thin boxes, boxes of one tile): a
+ray parallel to the axis wraps round inside the tile for its whole walk. Such
+tiles hand packets on to their next generation however few came in; the
+integers are those of the walk without tiles, for thin boxes, single tiles and
+batches of both, with deferral off and at its largest, a crossing cap inside
+the walk, weights of one unit and ranges of a few packets.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2312_11448_amd as M  # noqa: E402
+
+ALL_TILED = {M.MC_LYA_OPT_TILE_SHARE: 1_000_000}
+
+# (boxes, flow, profile, packets a box, packet weight, options)
+CASES = [
+    ([(1, 40, 40)], None, "doppler", 3_000, 1 << 31, {}),
+    ([(1, 40, 40)], 0.08, "doppler", 3_000, 1 << 31, {M.MC_LYA_OPT_DEFER: 64}),
+    ([(7, 9, 58)], 0.08, "voigt", 3_000, 1 << 31, {}),
+    ([(16, 33, 8), (12, 12, 12)], None, "voigt", 3_000, 1 << 31, {}),
+    ([(16, 33, 8), (12, 12, 12), (17, 18, 19)], 0.08, "doppler", 3_000, 1 << 31, {M.MC_LYA_OPT_DEFER: 64}),
+    ([(16, 16, 16), (9, 10, 11)], 0.08, "doppler", 3_000, 1 << 31, {}),
+    ([(16, 16, 16), (9, 10, 11)], None, "doppler", 3_000, 1 << 31, {M.MC_LYA_OPT_DEFER: 0}),
+    ([(8, 17, 15)], 0.08, "doppler", 20_000, 1 << 31, {M.MC_LYA_OPT_MAX_CROSSINGS: 300}),
+    ([(8, 16, 15)], None, "doppler", 3_000, 1 << 31, {M.MC_LYA_OPT_MAX_CROSSINGS: 300}),
+    ([(3, 50, 2)], 0.3, "doppler", 20_000, 1, {}),
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_tiles_that_span_their_box(case):
+    dims, flow, profile, packets, w0, opts = CASES[case]
+    print(f"case {case}: {CASES[case]}", flush=True)
+    specs = []
+    for i, n in enumerate(dims):
+        rng = np.random.default_rng(i + sum(n))
+        od = rng.lognormal(0.0, 0.7, size=n[::-1]).astype(np.float32)
+        vel = rng.normal(0.0, flow, size=(3,) + n[::-1]).astype(np.float32) if flow else None
+        specs.append(W.BoxSpec(n=n, overdensity=od, velocity=vel, n_packets=packets, seed=2 + i, profile=profile, w0=w0))
+    tot = packets * len(dims)
+    out = []
+    with M.Simulation(specs) as sim:
+        for extra, cuts in (({M.MC_LYA_OPT_KERNEL: 1}, [0, tot]), ({M.MC_LYA_OPT_KERNEL: 2, M.MC_LYA_OPT_TAIL: 0}, [0, tot]),
+                            ({M.MC_LYA_OPT_TAIL: 200_000}, [0, tot]), ({}, [0, 1, 50, tot // 3, tot])):
+            for k, v in {**ALL_TILED, **opts, **extra}.items():
+                sim.set_option(k, v)
+            sim.emit()
+            for a, b in zip(cuts, cuts[1:]):
+                sim.transport(a, b - a)
+            t = sim.tally(check=False)
+            out.append((t["absorbed"].cpu().numpy(), [(s.escaped, s.crossings, s.capped_weight, s.capped_packets, s.wing,
+                                                       s.conserved) for s in t["stats"]]))
+            if extra.get(M.MC_LYA_OPT_KERNEL) != 1:
+                assert all(s.tiled for s in t["stats"])
+    for got in out[1:]:
+        assert np.array_equal(got[0], out[0][0]) and got[1] == out[0][1]
