@@ -33,6 +33,7 @@ constexpr int TC = kTileCells;
 constexpr int BLK = kTileBlock;
 static_assert(TC % BLK == 0, "tile cells must be a multiple of the workgroup size");
 constexpr int kWaves = BLK / 64;
+constexpr uint32_t kDeferSteps = 32; // steps a wave takes before it defers packets of a small input
 constexpr uint32_t kMinClaim = 8;   // smallest claim on a tile's input
 
 // LDS slots: the tile's cells with a ring of one slot round them, in a
@@ -414,7 +415,10 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
     // us: 7 x 9 x 58, 7099 packets, Voigt in a flow 2049, 1350; 1 x 40 x 40,
     // 4e5 packets 1130, 775; boxes of 16 x 33 x 8 and 12^3 in one batch, 6e4
     // packets each, Voigt 1240, 860.
-    const uint32_t defer_from = WRAP && P.defer_any ? 0u : P.defer_min;
+    // (kDeferSteps: a wave that came in with so few packets is not to hand them
+    // on after every crossing.)
+    const uint32_t defer_after = WRAP && P.defer_any ? kDeferSteps : ~0u;
+    uint32_t steps = 0;          // wave-uniform: since the wave's last packets came in
     uint32_t cur = 0, end = 0;
     const uint32_t chunk = (uint32_t)P.chunk;
     // refilling stalls the whole wave on the new packets' loads: wait until
@@ -496,6 +500,7 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
                 alive = true;
             }
             fresh = true;
+            steps = 0;
             cur += take;
             idle = __ballot(!alive);
         }
@@ -511,7 +516,8 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
             if (!live) {
                 flush_exits();
                 stop = 1;
-            } else if (!fresh && n_in >= defer_from && (uint32_t)__popcll(live) <= (uint32_t)P.defer_lanes) {
+            } else if (!fresh && (n_in >= P.defer_min || steps >= defer_after) &&
+                       (uint32_t)__popcll(live) <= (uint32_t)P.defer_lanes) {
                 // (only after a step, so every deferred packet has moved in this generation)
                 flush_exits();
                 if (alive) {
@@ -527,6 +533,7 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
         }
         if (uniform_u32(stop)) break;
         fresh = false;
+        ++steps;
         // Every lane steps: an idle or parked lane's step changes nothing and
         // deposits nothing (selects, not branches, keep the lane state in the
         // same registers round the loop).

@@ -62,3 +62,25 @@ def test_tiles_that_span_their_box(case):
                 assert all(s.tiled for s in t["stats"])
     for got in out[1:]:
         assert np.array_equal(got[0], out[0][0]) and got[1] == out[0][1]
+
+
+@pytest.mark.parametrize("defer", [16, 64])
+def test_few_packets_on_long_walks(defer):
+    """A handful of packets, each with some 1e4 crossings: handed on after
+    every crossing they would take more generations than there are."""
+    n = (16, 33, 8)
+    od = np.random.default_rng(1).lognormal(0.0, 0.3, size=n[::-1]).astype(np.float32)
+    spec = W.BoxSpec(n=n, overdensity=od, n_packets=7, seed=3, cell_cm=2.0 * W.KPC_CM / 1e3)
+    out = []
+    with M.Simulation(spec) as sim:
+        for opts in ({M.MC_LYA_OPT_KERNEL: 1}, {M.MC_LYA_OPT_KERNEL: 2, **ALL_TILED, M.MC_LYA_OPT_TAIL: 0,
+                                                M.MC_LYA_OPT_DEFER: defer}):
+            for k, v in opts.items():
+                sim.set_option(k, v)
+            sim.emit()
+            sim.transport()
+            t = sim.tally()
+            s = t["stats"][0]
+            out.append((t["absorbed"].cpu().numpy(), (s.escaped, s.crossings, s.conserved)))
+    assert out[0][1][1] > 20_000
+    assert np.array_equal(out[0][0], out[1][0]) and out[0][1] == out[1][1]
