@@ -474,9 +474,9 @@ constexpr uint64_t kSharePackets = 512;
 //   tallies in LDS, or one tile, which has no neighbours to hand packets to
 //     and keeps them to the end: 16^3 with 3e5 717, 493 and with 1e6 950, 1270;
 //     Voigt in a flow 6e4 630, 880.
-uint64_t shared_from(const mc_lya_ctx *c, int nt)
+uint64_t shared_from(const mc_lya_ctx *c, int nt, uint64_t n)
 {
-    const uint64_t cells = c->total_cells, n = c->walk[0].npkt;
+    const uint64_t cells = c->total_cells;
     const bool lds = box_fits_lds(cells, c->vel), hard = c->vel && c->voigt;
     const bool tally = box_tally_fits_lds(cells, c->vel) && cells * (uint64_t)c->num_cu <= 10 * n;
     if (nt == 1 || tally) return hard ? 40000 : 400000;
@@ -506,7 +506,7 @@ int sharing(const mc_lya_ctx *c, int nt, uint64_t packets)
 // (a tile is walked by one workgroup, so a box with few tiles and many long
 // walks would hold the whole launch); the rest go to the persistent walk.
 // Rebuilds and uploads the tile table when the choice changes.
-mc_lya_status classify_boxes(mc_lya_ctx *c)
+mc_lya_status classify_boxes(mc_lya_ctx *c, uint64_t first, uint64_t count)
 {
     const int nb = c->n_boxes;
     std::vector<double> cost(nb, 0.0);
@@ -523,11 +523,18 @@ mc_lya_status classify_boxes(mc_lya_ctx *c)
         else if (c->tile_share > 0)
             m[b] = nt >= kMinTiles && cost[b] / nt <= 0.01 * c->tile_share * fair ? 1 : 0;
     }
+    // The rules for few tiles go by the packets of this walk: a short range of
+    // a large emission is a small call.
+    auto walked = [&](int b) -> uint64_t {
+        const uint64_t lo = std::max(first, c->walk[b].pkt_off);
+        const uint64_t hi = std::min(first + count, c->walk[b].pkt_off + c->walk[b].npkt);
+        return hi > lo ? hi - lo : 0;
+    };
     int share = 1;
     if (nb == 1 && c->tile_share > 0) {
         const int nt = tiles_of_box(c->desc[0]);
-        share = sharing(c, nt, c->walk[0].npkt);
-        if (c->walk[0].npkt >= shared_from(c, nt)) m[0] = 1;
+        share = sharing(c, nt, count);
+        if (count >= shared_from(c, nt, count)) m[0] = 1;
         if (!m[0]) share = 1;
     } else if (c->tile_share > 0) {
         int all = 0;
@@ -537,7 +544,7 @@ mc_lya_status classify_boxes(mc_lya_ctx *c)
             const int t = tiles_of_box(c->desc[b]);
             all += t;
             lone_tiles = lone_tiles && t == 1;
-            packets += c->walk[b].npkt;
+            packets += walked(b);
         }
         if (all < c->num_cu && packets >= (uint64_t)all * (lone_tiles ? kBatchLone : kBatchTile)) {
             int nt = 0;
@@ -546,7 +553,7 @@ mc_lya_status classify_boxes(mc_lya_ctx *c)
                 const int t = tiles_of_box(c->desc[b]);
                 if (cost[b] / t <= 0.04 * c->tile_share * total / all) m[b] = 1;
                 nt += m[b] ? t : 0;
-                packets += m[b] ? c->walk[b].npkt : 0;
+                packets += m[b] ? walked(b) : 0;
             }
             if (nt) share = sharing(c, nt, packets);
         }
@@ -930,7 +937,7 @@ mc_lya_status plan_walk(mc_lya_ctx *c, uint64_t first, uint64_t count, WalkPlan 
     if (c->kernel == 2) {
         // tiled boxes by tiles; the others, if any, by the persistent walk
         // over their packet segments inside [first, first + count)
-        mc_lya_status st = classify_boxes(c);
+        mc_lya_status st = classify_boxes(c, first, count);
         if (st != MC_LYA_OK) return st;
         w->tiled = !c->tiles.empty();
         std::vector<uint64_t> starts, ids;
