@@ -461,27 +461,48 @@ constexpr int kAllTiled = 1000000;        // tile_share at or above this: every 
 // as compute units): as many as the chip holds at once, one per compute unit,
 // while each has kSharePackets packets to walk (128 to 1024 time alike).
 constexpr uint64_t kSharePackets = 512;
+// Whether a box is cut into several tiles along every axis: a packet then
+// leaves its tile after some 11 cells whatever its direction.
+bool cut_along_all(const mc_lya_box_desc &d)
+{
+    return d.nx > kTileX && d.ny > kTileY && d.nz > kTileZ;
+}
+
 // A lone box with fewer tiles than compute units is walked by (shared) tiles
-// from this many packets; both ways' times grow alike with the length of the
-// walks. The tiles take some ten generations of 25 to 35 us and a tail however
-// few packets there are; the persistent walk takes as long as its longest
-// packet, a step of it longer with the records in L2 (a flow's, or more than
-// 39 936 cells) and with Voigt profiles, and then is bound by the device's
-// 2.4e10 deposits/s. Transports, us (tiles, persistent):
-//   records in L2: 48^3 with 4e4 packets 404, 382 and with 7e4 413, 491; in a
-//     flow 1e4 461, 456 and 4e4 482, 546; Voigt in a flow 5e3 705, 896;
-//   records in LDS: 32^3 with 7e4 409, 402 and with 1e5 410, 446;
+// from this many packets. The tiles take some ten generations of 25 to 35 us
+// and a tail however few packets there are; the persistent walk takes as long
+// as its longest packet, a step of it longer with the records in L2 (a flow's,
+// or more than 39 936 cells) and with Voigt profiles, and then is bound by the
+// device's 2.4e10 deposits/s. Transports, us (tiles, persistent):
+//   records in L2, no flow: 40 x 41 x 42 with 45 000 packets 365, 390;
+//   in a flow, cut along every axis into 8 tiles, little clumping (<Delta^2> /
+//     <Delta>^2 below 2): 24 x 25 x 26 with 10 000 456, 372, with 117 710
+//     (32^3) 472, 613; Voigt with 5000 670, 518, with 132 098 (23^3) 713, 809;
+//   in a flow otherwise each tile gets few packets a generation, or keeps its
+//     packets for long, and the line is far up: 64^3 with 12 124 (clumping
+//     9.5) 460, 357; 37^3 with 9057, Voigt 675, 499; 61^3 with 28 782, Voigt,
+//     clumping 9.5 1540, 1100; 21 x 71 x 13 with 46 713, Voigt 1576, 1266; and
+//     from 1e5 on 57^3 with 105 454, Voigt, clumping 9.5 670, 655; 41 x 55 x 52
+//     with 126 487, Voigt 921, 997; 22 x 62 x 35 with 170 785, Voigt 699, 1180;
+//   records in LDS: 32^3 with 1e5 392, 431; in a flow 18 x 20 x 22 with 8e4
+//     467, 410 and with 1.2e5 480, 500;
 //   tallies in LDS, or one tile, which has no neighbours to hand packets to
-//     and keeps them to the end: 16^3 with 3e5 717, 493 and with 1e6 950, 1270;
-//     Voigt in a flow 6e4 630, 880.
+//     and keeps them to the end: 16^3 in a flow with 5e5 695, 840; Voigt in a
+//     flow 9 x 10 x 11 with 4e4 604, 457.
+// (The lines of the first, second and last kinds were drawn against slower
+// persistent walks and are kept; what they cost at the line is beside them.)
+constexpr uint64_t kSharedFlow = 100000;
 uint64_t shared_from(const mc_lya_ctx *c, int nt, uint64_t n)
 {
     const uint64_t cells = c->total_cells;
     const bool lds = box_fits_lds(cells, c->vel), hard = c->vel && c->voigt;
     const bool tally = box_tally_fits_lds(cells, c->vel) && cells * (uint64_t)c->num_cu <= 10 * n;
     if (nt == 1 || tally) return hard ? 40000 : 400000;
-    if (hard) return 5000;
-    return lds ? 80000 : (c->vel ? 10000 : 45000);
+    const BoxRed &r = c->red[0];
+    const bool easy = cut_along_all(c->desc[0]) && nt <= 8 && r.od2_sum * (double)cells < 2.0 * r.od_sum * r.od_sum;
+    if (hard) return easy ? 5000 : kSharedFlow;
+    if (lds) return 80000;
+    return c->vel ? (easy ? 10000 : kSharedFlow) : 45000;
 }
 // A batch with fewer tiles than compute units takes (shared) tiles from this
 // many packets a tile, if all its boxes are of one tile or else; a box whose
@@ -492,7 +513,10 @@ uint64_t shared_from(const mc_lya_ctx *c, int nt, uint64_t n)
 // packets a tile 774, 692 and 8000 941, 2516; 8 of up to 24^3, 331 776 packets
 // 3573, 4442 and 55 296 1753, 966; 6 of up to 40^3, 2.7e5 3382, 2854, 5.8e5
 // 4071, 5655 and 1.2e6 5809, 10598.
-constexpr uint64_t kBatchLone = 2500, kBatchTile = 30000;
+// Voigt in a flow, with a box that is not cut along every axis: 35 boxes, 3.75e6
+// packets, 30 000 a tile 11013, 8533; two of 30 x 9 x 20 with 30 000 a tile
+// 1292, 1169 and with 60 000 1709, 1616.
+constexpr uint64_t kBatchLone = 2500, kBatchTile = 30000, kBatchHard = 120000;
 int sharing(const mc_lya_ctx *c, int nt, uint64_t packets)
 {
     const uint64_t per = packets / ((uint64_t)nt * kSharePackets);
@@ -538,15 +562,17 @@ mc_lya_status classify_boxes(mc_lya_ctx *c, uint64_t first, uint64_t count)
         if (!m[0]) share = 1;
     } else if (c->tile_share > 0) {
         int all = 0;
-        bool lone_tiles = true;
+        bool lone_tiles = true, cut = true;
         uint64_t packets = 0;
         for (int b = 0; b < nb; ++b) {
             const int t = tiles_of_box(c->desc[b]);
             all += t;
             lone_tiles = lone_tiles && t == 1;
+            cut = cut && cut_along_all(c->desc[b]);
             packets += walked(b);
         }
-        if (all < c->num_cu && packets >= (uint64_t)all * (lone_tiles ? kBatchLone : kBatchTile)) {
+        const uint64_t line = lone_tiles ? kBatchLone : (c->vel && c->voigt && !cut ? kBatchHard : kBatchTile);
+        if (all < c->num_cu && packets >= (uint64_t)all * line) {
             int nt = 0;
             packets = 0;
             for (int b = 0; b < nb; ++b) {

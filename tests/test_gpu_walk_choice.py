@@ -52,3 +52,36 @@ def test_a_short_range_is_a_small_call(boxes):
         short = _walk(sim, [0, total - 1000, total - 500, total])
         assert not short[2][-1]
         assert _same(whole, short)
+
+
+# (box, flow, profile, packets, rms of ln Delta, tiled): in a flow, boxes of
+# more than 8 tiles, not cut along every axis or strongly clumped take tiles
+# from 1e5 packets, others earlier
+LINES = [
+    ((37, 37, 37), 0.08, "voigt", 9_057, 0.5, 0), ((37, 37, 37), 0.08, "voigt", 100_000, 0.5, 1),
+    ((21, 60, 13), 0.08, "voigt", 46_713, 0.5, 0), ((21, 60, 13), 0.08, "voigt", 100_000, 0.5, 1),
+    ((25, 25, 25), 0.08, "doppler", 20_000, 1.5, 0), ((25, 25, 25), 0.08, "doppler", 20_000, 0.5, 1),
+    ((25, 25, 25), 0.08, "doppler", 100_000, 1.5, 1), ((50, 50, 50), 0.08, "doppler", 99_999, 0.5, 0),
+    ((50, 50, 50), None, "voigt", 45_000, 0.5, 1), ((7, 9, 58), 0.08, "voigt", 7_099, 0.5, 0),
+]
+
+
+@pytest.mark.parametrize("case", range(len(LINES)))
+def test_lone_box_lines(case):
+    n, flow, profile, packets, rms, tiled = LINES[case]
+    with M.Simulation(_box(n, flow, packets, profile, rms)) as sim:
+        got = _walk(sim)
+        assert got[2] == [tiled]
+        sim.set_option(M.MC_LYA_OPT_KERNEL, 1)
+        assert _same(got, _walk(sim))
+
+
+@pytest.mark.parametrize("packets,tiled", [(200_000, 0), (480_000, 1)])
+def test_batch_line_with_voigt_in_a_flow(packets, tiled):
+    specs = [_box((30, 9, 20), 0.08, packets, "voigt", seed=1), _box((20, 21, 17), 0.08, packets, "voigt", seed=2)]
+    specs = specs if not tiled else [specs[0], specs[0]]
+    with M.Simulation(specs) as sim:
+        got = _walk(sim)
+        assert got[2] == [tiled] * len(specs)
+        sim.set_option(M.MC_LYA_OPT_KERNEL, 1)
+        assert _same(got, _walk(sim))
