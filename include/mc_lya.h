@@ -189,7 +189,11 @@ enum {
                                      tiles and its estimated crossings per tile are at most
                                      this percentage of the emission's crossings per compute
                                      unit (default 100); other boxes take the persistent walk.
-                                     0 = no box tiled, 1000000 = every box tiled */
+                                     0 = no box tiled, 1000000 = every box tiled. At 100 a context
+                                     with fewer tiles than compute units goes by the packets of
+                                     the walk as well: above a number of them that depends on
+                                     flow, profile and shape, boxes of any number of tiles are
+                                     tiled, several workgroups sharing a tile */
     MC_LYA_OPT_GRAPH_GENS = 11,   /* tile generations inside a captured transport graph
                                      (16..4096, default 64); a replay that needs more
                                      continues eagerly and the next capture takes enough */

@@ -94,6 +94,8 @@ hipError_t dalloc(T **p, size_t n)
 constexpr int kEagerGens = 16;
 constexpr uint64_t kDefaultMaxPackets = 1ull << 20;   // limits == NULL
 
+constexpr int kTileShare = 100;              // MC_LYA_OPT_TILE_SHARE where the rules for few tiles apply too
+
 struct mc_lya_ctx {
     hipStream_t stream = nullptr;
     int n_boxes = 0;
@@ -177,7 +179,7 @@ struct mc_lya_ctx {
     bool featbox_stale = true;               // rebuilt and uploaded after each refresh
     int feat_blocks = 1;                     // grid width of the features launch
     uint64_t *d_seg = nullptr;               // [2 (n_boxes + 1)]
-    int tile_share = 100;
+    int tile_share = kTileShare;
     int defer = 16;                          // MC_LYA_OPT_DEFER
     // captured transport (MC_LYA_OPT_GRAPH)
     bool graph = false;
@@ -557,9 +559,8 @@ mc_lya_status classify_boxes(mc_lya_ctx *c, uint64_t first, uint64_t count)
     int share = 1;
     if (nb == 1 && c->tile_share > 0) {
         const int nt = tiles_of_box(c->desc[0]);
-        share = sharing(c, nt, count);
-        if (count >= shared_from(c, nt, count)) m[0] = 1;
-        if (!m[0]) share = 1;
+        if (c->tile_share == kTileShare && nt < c->num_cu && count >= shared_from(c, nt, count)) m[0] = 1;
+        if (m[0]) share = sharing(c, nt, count);
     } else if (c->tile_share > 0) {
         int all = 0;
         bool lone_tiles = true, cut = true;
@@ -571,13 +572,14 @@ mc_lya_status classify_boxes(mc_lya_ctx *c, uint64_t first, uint64_t count)
             cut = cut && cut_along_all(c->desc[b]);
             packets += walked(b);
         }
+        const bool few = all < c->num_cu;
         const uint64_t line = lone_tiles ? kBatchLone : (c->vel && c->voigt && !cut ? kBatchHard : kBatchTile);
-        if (all < c->num_cu && packets >= (uint64_t)all * line) {
+        if (few && packets >= (uint64_t)all * line) {
             int nt = 0;
             packets = 0;
             for (int b = 0; b < nb; ++b) {
                 const int t = tiles_of_box(c->desc[b]);
-                if (cost[b] / t <= 0.04 * c->tile_share * total / all) m[b] = 1;
+                if (c->tile_share == kTileShare && cost[b] / t <= 4.0 * total / all) m[b] = 1;
                 nt += m[b] ? t : 0;
                 packets += m[b] ? walked(b) : 0;
             }

@@ -85,3 +85,19 @@ def test_batch_line_with_voigt_in_a_flow(packets, tiled):
         assert got[2] == [tiled] * len(specs)
         sim.set_option(M.MC_LYA_OPT_KERNEL, 1)
         assert _same(got, _walk(sim))
+
+
+@pytest.mark.parametrize("boxes", [[((32, 32, 32), None, 300_000)], [((16, 16, 16), 0.08, 500_000)],
+                                   [((12, 12, 12), None, 30_000)] * 4])
+def test_tile_share_decides_where_it_is_set(boxes):
+    """A lower share than the default leaves boxes whose tiles have more than
+    that much work to the persistent walk, whatever the packets."""
+    specs = [_box(n, flow, packets, seed=3 + i) for i, (n, flow, packets) in enumerate(boxes)]
+    with M.Simulation(specs) as sim:
+        ref = _walk(sim)
+        assert all(ref[2])
+        for share, tiled in ((99, 0), (1, 0), (0, 0), (1_000_000, 1), (100, 1)):
+            sim.set_option(M.MC_LYA_OPT_TILE_SHARE, share)
+            got = _walk(sim)
+            assert all(t == tiled for t in got[2]), share
+            assert _same(ref, got)
