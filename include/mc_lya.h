@@ -167,10 +167,15 @@ enum {
                                      2 = tile-decomposed walk (default): 16^3-cell
                                      tiles, tallies in LDS, packets handed between
                                      tiles once per generation */
-    MC_LYA_OPT_BLOCK = 2,         /* threads per workgroup: 64, 128 or 256 */
-    MC_LYA_OPT_WAVES_PER_CU = 3,  /* resident waves per compute unit for the persistent grid */
+    MC_LYA_OPT_BLOCK = 2,         /* threads per workgroup: 64, 128 or 256 (default 256) */
+    MC_LYA_OPT_WAVES_PER_CU = 3,  /* resident waves per compute unit for the persistent grid
+                                     (default 32) */
     MC_LYA_OPT_CHUNK = 4,         /* persistent walk: packets a wave takes from the queue at
-                                     once (>= 1) */
+                                     once (>= 1, default 256). While this, _BLOCK, _WAVES_PER_CU
+                                     and _QUEUES are all at their defaults (256, 256, 32, 8) the
+                                     chunk shrinks with few packets, and kernel 2 walks a lone
+                                     box whose records fit a compute unit's LDS by a kernel with
+                                     a launch of its own */
     MC_LYA_OPT_REFILL = 5,        /* persistent walk: refill a wave once this many lanes are
                                      idle (1..64) */
     MC_LYA_OPT_MAX_CROSSINGS = 6, /* crossing cap per packet (>= 1, default 1e6) */

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "walk_plan.hpp"
 
 using namespace mclya;
 
@@ -1171,35 +1172,17 @@ mc_lya_status launch_global_walk(mc_lya_ctx *c, const WalkParams &p, bool timed,
     }
     if (c->kernel == 1) {
         HIP_TRY(c, launch_walk_simple(p, c->block, c->stream));
-    } else if (c->kernel == 2 && c->n_boxes == 1 && box_fits_lds(c->total_cells, c->vel)) {
-        WalkParams q = p;
-        const uint64_t waves = (count + 63) / 64;
-        const int per = (int)std::min<uint64_t>(16, (waves + c->num_cu - 1) / c->num_cu);
-        const int grid = (int)std::min<uint64_t>((uint64_t)c->num_cu, (waves + per - 1) / per);
-        q.chunk = 64;
-        q.nqueues = 1;
-        HIP_TRY(c, launch_walk_box(q, c->total_cells, 64 * per, grid, !c->queue_clear || !timed, c->stream));
-        c->queue_clear = false;
     } else {
-        const int waves_per_block = c->block / 64;
-        // never more workgroups than can be resident at once
-        const int resident = persistent_blocks_per_cu(c->vel, c->voigt, c->block);
-        const int waves = waves_cap > 0 ? std::min(c->waves_per_cu, waves_cap) : c->waves_per_cu;
-        const int per_cu = std::max(1, std::min(waves / waves_per_block, resident));
-        int grid = c->num_cu * per_cu;
-        const uint64_t need = (count + 63) / 64;     // no more waves than packets
-        if ((uint64_t)grid * waves_per_block > need) grid = (int)std::max<uint64_t>(1, (need + waves_per_block - 1) / waves_per_block);
-        // Few packets: a chunk for each of four waves a compute unit, one per
-        // SIMD (whole chunks would leave most of the chip without; one for
-        // every resident wave leaves none to refill the lanes that finish
-        // first). Transports with 256 a chunk, with one for all 3072 waves,
-        // with this, us: 28 518 packets (23^3, flow) 632, 416, 416; 62 046
-        // (Voigt, flow) 970, 785, 783; 139 172 (30^3, Voigt, flow) 683, 751,
-        // 708; 156 927 (Voigt, flow) 616, 712, 626; from 262 144 on 256.
+        const WalkOptions o{c->block, c->waves_per_cu, c->chunk, c->nqueues};
+        const WalkLaunch l = plan_persistent(o, count, c->num_cu, persistent_blocks_per_cu(c->vel, c->voigt, c->block),
+                                             waves_cap,
+                                             c->kernel == 2 && c->n_boxes == 1 && box_fits_lds(c->total_cells, c->vel));
         WalkParams q = p;
-        const uint64_t each = count / (4 * (uint64_t)c->num_cu);
-        q.chunk = (int32_t)std::min<uint64_t>((uint64_t)p.chunk, std::max<uint64_t>(64, each));
-        HIP_TRY(c, launch_walk_persistent(q, c->block, grid, !c->queue_clear || !timed, c->stream));
+        q.chunk = l.chunk;
+        q.nqueues = l.nqueues;
+        const bool reset = !c->queue_clear || !timed;
+        if (l.box) HIP_TRY(c, launch_walk_box(q, c->total_cells, l.block, l.grid, reset, c->stream));
+        else HIP_TRY(c, launch_walk_persistent(q, l.block, l.grid, reset, c->stream));
         c->queue_clear = false;
     }
     if (timed) return timed_end(c, e1);
