@@ -97,7 +97,7 @@ EXPORTS = ["mc_lya_init", "mc_lya_refresh", "mc_lya_emit", "mc_lya_transport",
            "mc_lya_mlp_last_error", "mc_lya_mlp_gradient_static", "mc_lya_mlp_static_last_error"]
 # the static workspace of mc_lya_mlp_gradient_static (mc_lya.h)
 MC_LYA_STATIC_MAX_CELLS = (1 << 40) - 1
-MC_LYA_STATIC_SCRATCH_BYTES = (1024 + 32) * 4808 * 4
+MC_LYA_STATIC_SCRATCH_BYTES = 512 * 4808 * 4
 MC_LYA_MLP_PARAMS = 4801
 MC_LYA_MLP_FEATURES = 8
 

@@ -309,13 +309,13 @@ mc_lya_status mc_lya_mlp_train_steps(mc_lya_mlp *m, const float *features, const
 
 // ---- gradient without allocation ---------------------------------------------
 // The workspace of mc_lya_mlp_gradient_static: the gradient kernel's per-block
-// partial sums, in one file-scope device array per GPU (held until the process ends). Host code
-// never uses the array's name as an address: its device address is looked up
-// once per device with hipGetSymbolAddress and kept below.
+// partial sums, in one file-scope device array per GPU (held until the process
+// ends). Host code never uses the array's name as an address: its device
+// address is looked up once per device with hipGetSymbolAddress and kept below.
 namespace {
 
-constexpr size_t kStaticGradFloats = MC_LYA_STATIC_SCRATCH_BYTES / sizeof(float);
-static_assert((size_t)kMlpGradBlocks * kMlpPartStride <= kStaticGradFloats, "static workspace size");
+constexpr size_t kStaticGradFloats = (size_t)kMlpGradBlocks * kMlpPartStride;
+static_assert(kStaticGradFloats * sizeof(float) == MC_LYA_STATIC_SCRATCH_BYTES, "static workspace size");
 __device__ __align__(256) float scratch[kStaticGradFloats];
 
 constexpr int kMaxDevices = 64;
