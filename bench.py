@@ -65,19 +65,54 @@ def walk_source_hash():
     return source_hash(WALK_SOURCES)
 
 
+# what decides how many crossings are counted instead of stepped: the walk, and
+# where it and the tail walk are taken
+STEPPED_SOURCES = WALK_SOURCES + ("paper_2312_11448_amd/csrc/api.hip",)
+STEPPED = os.path.join("profiles", "walk_stepped.json")
+
+
 def stepped_share(config, profile):
     """Share of the workload's crossings that the walk steps (the rest are
-    counted: packets past their last deposit), from a counting build; None
-    once the walk's sources have changed."""
+    counted: packets past their last deposit), as --count-ends found it; None
+    once one of its sources has changed."""
     try:
-        with open(os.path.join(ROOT, "profiles", "walk_stepped.json")) as fh:
+        with open(os.path.join(ROOT, STEPPED)) as fh:
             rows = json.load(fh)
     except OSError:
         return None
     for r in rows:
-        if r["config"] == config and r["profile"] == profile and r["source_sha256"] == walk_source_hash():
+        if (r["config"], r["profile"], r["source_sha256"]) == (config, profile, source_hash(STEPPED_SOURCES)):
             return r["stepped_share"]
     return None
+
+
+def count_ends(a, specs):
+    """One step of the workload with the counting build of the library
+    (python3 -m paper_2312_11448_amd.build --count-ends), whose tally returns
+    the counted crossings as scatterings; its row of profiles/walk_stepped.json
+    is replaced."""
+    from paper_2312_11448_amd import _abi, build
+    _abi.LIB_PATH = build.LIB_ENDS
+    import paper_2312_11448_amd as M
+    with M.Simulation(specs) as sim:
+        if a.tail is not None:
+            sim.set_option(M.MC_LYA_OPT_TAIL, a.tail)
+        sim.emit()
+        sim.transport()
+        stats = sim.tally(want_emitted=False)["stats"]
+    crossings = sum(s.crossings for s in stats)
+    counted = sum(s.scatterings for s in stats)
+    row = {"config": a.config, "profile": a.profile, "crossings_per_step": crossings, "counted_per_step": counted,
+           "stepped_share": 1.0 - counted / crossings, "source_sha256": source_hash(STEPPED_SOURCES)}
+    path = os.path.join(ROOT, STEPPED)
+    rows = []
+    if os.path.exists(path):
+        with open(path) as fh:
+            rows = [r for r in json.load(fh) if (r["config"], r["profile"]) != (a.config, a.profile)]
+    with open(path, "w") as fh:
+        json.dump(rows + [row], fh, indent=1)
+        fh.write("\n")
+    print(json.dumps(row), flush=True)
 
 
 def parse():
@@ -104,6 +139,9 @@ def parse():
     ap.add_argument("--tail", type=int, default=None, metavar="PPM",
                     help="MC_LYA_OPT_TAIL: the tail walk takes over below this many millionths of the packets in "
                          "flight (default: the library's rule)")
+    ap.add_argument("--count-ends", action="store_true",
+                    help="one step with the counting build of the library: the share of the crossings that the walk "
+                         "steps, kept in profiles/walk_stepped.json")
     ap.add_argument("--autotune", action="store_true",
                     help="tune the walk options on the first emission, before the warm-up")
     ap.add_argument("--cpu-seconds", type=float, default=20.0,
@@ -534,6 +572,8 @@ def main():
     specs = W.batch_specs() if a.config == "batch" else [W.make_box(a.config)]
     if a.profile != "doppler":
         specs = [dataclasses.replace(sp, profile=a.profile) for sp in specs]
+    if a.count_ends:
+        return count_ends(a, specs)
     dev = torch.device("cuda:0")
     sim = M.Simulation(specs, device=dev)
     # one event pair around each transport's walk, its launches counted: the

@@ -15,6 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmclya.so")
+LIB_ENDS = os.path.join(HERE, "libmclya_ends.so")   # --count-ends
 OBJ = os.path.join(ROOT, "_build", "mclya")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -26,9 +27,9 @@ FLAGS = ["-O3", f"--offload-arch={ARCH}", "-std=c++17", "-fPIC", "-ffp-contract=
          "-Wall", "-Wno-unused-function", f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}"]
 
 
-def _compile(src, verbose):
-    obj = os.path.join(OBJ, os.path.basename(src) + ".o")
-    cmd = [HIPCC] + FLAGS + ["-c", src, "-o", obj]
+def _compile(src, verbose, out, more):
+    obj = os.path.join(out, os.path.basename(src) + ".o")
+    cmd = [HIPCC] + FLAGS + more + ["-c", src, "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -41,20 +42,24 @@ def _compile(src, verbose):
     return obj
 
 
-def build(verbose=False):
-    """Compiles every csrc/*.hip for gfx950 and links libmclya.so (always)."""
-    os.makedirs(OBJ, exist_ok=True)
+def build(verbose=False, count_ends=False):
+    """Compiles every csrc/*.hip for gfx950 and links libmclya.so (always).
+    count_ends: libmclya_ends.so instead, whose tallies also hold the crossings
+    that were counted without a step (as scatterings)."""
+    lib, out = (LIB_ENDS, OBJ + "_ends") if count_ends else (LIB, OBJ)
+    more = ["-DMCLYA_COUNT_ENDS"] if count_ends else []
+    os.makedirs(out, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
-        objs = list(ex.map(lambda s: _compile(s, verbose), srcs))
-    tmp = LIB + ".tmp"
+        objs = list(ex.map(lambda s: _compile(s, verbose, out, more), srcs))
+    tmp = lib + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp] + objs
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
-    os.replace(tmp, LIB)
-    return LIB
+    os.replace(tmp, lib)
+    return lib
 
 
 if __name__ == "__main__":
-    print(build(verbose="-v" in sys.argv))
+    print(build(verbose="-v" in sys.argv, count_ends="--count-ends" in sys.argv))

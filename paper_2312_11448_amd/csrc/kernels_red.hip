@@ -77,6 +77,12 @@ __global__ __launch_bounds__(kRedBlock) void red_list_kernel(RedParams P)
             }
             if (!unsure) {
                 acc.cross += e.n;
+#ifdef MCLYA_COUNT_ENDS
+                // (build.py --count-ends, for bench.py --count-ends: the
+                // crossings counted here, in the total that tally returns as
+                // scatterings)
+                atomicAdd(&P.tot[box].pad[0], (unsigned long long)e.n);
+#endif
                 acc.esc += e.fate == kEscaped ? L.w : 0u;
                 acc.capn += e.fate == kCapped ? 1u : 0u;
                 acc.capw += e.fate == kCapped ? L.w : 0u;
