@@ -519,7 +519,12 @@ uint64_t shared_from(const mc_lya_ctx *c, int nt, uint64_t n)
 // Voigt in a flow, with a box that is not cut along every axis: 35 boxes, 3.75e6
 // packets, 30 000 a tile 11013, 8533; two of 30 x 9 x 20 with 30 000 a tile
 // 1292, 1169 and with 60 000 1709, 1616.
-constexpr uint64_t kBatchLone = 2500, kBatchTile = 30000, kBatchHard = 120000;
+// Boxes of one tile each, and few packets in all: with a flow or a Voigt profile
+// (not both) two with 5000 each 497, 353 and 617, 434; ten with 5000 540, 447
+// and 645, 497; three with 20 000 518, 489 and 566, 558. (Of the others' lines,
+// drawn against slower persistent walks and kept: three with 2600 415, 301;
+// five with 2600 in a flow with Voigt profiles 677, 501.)
+constexpr uint64_t kBatchLone = 2500, kBatchTile = 30000, kBatchHard = 120000, kBatchLeast = 60000;
 int sharing(const mc_lya_ctx *c, int nt, uint64_t packets)
 {
     const uint64_t per = packets / ((uint64_t)nt * kSharePackets);
@@ -575,7 +580,8 @@ mc_lya_status classify_boxes(mc_lya_ctx *c, uint64_t first, uint64_t count)
         }
         const bool few = all < c->num_cu;
         const uint64_t line = lone_tiles ? kBatchLone : (c->vel && c->voigt && !cut ? kBatchHard : kBatchTile);
-        if (few && packets >= (uint64_t)all * line) {
+        const uint64_t least = lone_tiles && c->vel != c->voigt ? kBatchLeast : 0;
+        if (few && packets >= std::max((uint64_t)all * line, least)) {
             int nt = 0;
             packets = 0;
             for (int b = 0; b < nb; ++b) {

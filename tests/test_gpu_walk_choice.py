@@ -76,6 +76,17 @@ def test_lone_box_lines(case):
         assert _same(got, _walk(sim))
 
 
+@pytest.mark.parametrize("flow,profile", [(0.08, "doppler"), (None, "voigt")])
+@pytest.mark.parametrize("packets,tiled", [(5_000, 0), (20_000, 1)])
+def test_batch_line_of_single_tiles(packets, tiled, flow, profile):
+    specs = [_box((9 + i, 11, 14), flow, packets, profile, seed=1 + i) for i in range(3)]
+    with M.Simulation(specs) as sim:
+        got = _walk(sim)
+        assert got[2] == [tiled] * 3
+        sim.set_option(M.MC_LYA_OPT_KERNEL, 1)
+        assert _same(got, _walk(sim))
+
+
 @pytest.mark.parametrize("packets,tiled", [(200_000, 0), (480_000, 1)])
 def test_batch_line_with_voigt_in_a_flow(packets, tiled):
     specs = [_box((30, 9, 20), 0.08, packets, "voigt", seed=1), _box((20, 21, 17), 0.08, packets, "voigt", seed=2)]
@@ -101,3 +112,28 @@ def test_tile_share_decides_where_it_is_set(boxes):
             got = _walk(sim)
             assert all(t == tiled for t in got[2]), share
             assert _same(ref, got)
+
+
+@pytest.mark.parametrize("flow,profile", [(None, "doppler"), (0.08, "voigt")])
+@pytest.mark.parametrize("kinds", ["one tile each", "several tiles each"])
+def test_shared_tiles_beside_a_box_left_out(kinds, flow, profile):
+    """A small batch by shared tiles, but for one box whose walks are so long
+    that it is left to the persistent walk beside them (or after them): ranges,
+    repeated emissions and replays from a graph included."""
+    n, packets = ((12, 13, 14), 8_000) if kinds == "one tile each" else ((20, 21, 22), 300_000)
+    specs = [_box(n, flow, packets, profile, seed=3 + i) for i in range(6)]
+    long = _box(n, flow, packets, profile, seed=9)
+    long.cell_cm = 5.0 * W.KPC_CM / 1e3
+    specs.insert(2, long)
+    total = sum(s.n_packets for s in specs)
+    with M.Simulation(specs) as sim:
+        sim.set_option(M.MC_LYA_OPT_KERNEL, 1)
+        ref = _walk(sim)
+        sim.set_option(M.MC_LYA_OPT_KERNEL, 2)
+        for beside, graph, cuts in ((4, 0, None), (0, 0, None), (4, 0, [0, total // 7, total]), (4, 1, None), (4, 1, None)):
+            sim.set_option(M.MC_LYA_OPT_BESIDE, beside)
+            sim.set_option(M.MC_LYA_OPT_GRAPH, graph)
+            got = _walk(sim, cuts)
+            # (a range holds fewer packets than the line asks for)
+            assert cuts or got[2] == [1, 1, 0, 1, 1, 1, 1], (beside, graph)
+            assert _same(ref, got), (beside, graph, cuts)
