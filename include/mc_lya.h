@@ -242,7 +242,8 @@ enum {
  *   per tile    its table entry and exit lists (about 140 bytes); with fewer
  *               tiles than compute units, as many entries as those, the ones
  *               past T with a tally of 32 KB each (at most 8 MB);
- *   per box     a few hundred bytes of tables and per-block partial sums. */
+ *   per box     a few hundred bytes of tables and per-block partial sums;
+ *   each of the some 25 buffers is rounded up to 64 KB. */
 typedef struct mc_lya_limits {
     uint64_t max_packets;         /* most packets one mc_lya_emit may emit over all boxes,
                                      1 <= max_packets < 2^40 */

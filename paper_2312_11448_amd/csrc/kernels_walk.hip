@@ -210,7 +210,7 @@ __global__ __launch_bounds__(1024) void walk_box_kernel(WalkParams P)
     const uint32_t cells = B.cells();
     unsigned long long *tally = reinterpret_cast<unsigned long long *>(recs) + (kBoxLds / 8 - cells);   // (TALLY)
     // (16 bytes a read, whole ones past the last record too: the records' place
-    // in the context's memory is a multiple of 256 bytes long. A call of a few
+    // in the context's memory is a multiple of 64 KB long. A call of a few
     // packets has one wave a workgroup for all of them: 39 000 records one
     // float at a time took 90 us.)
     const uint32_t quads = VEL ? cells : (cells + 3u) / 4u;
