@@ -426,7 +426,6 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
     // packets each, Voigt 1240, 860.
     // (kDeferSteps: a wave that came in with so few packets is not to hand them
     // on after every crossing.)
-    const uint32_t defer_after = WRAP && P.defer_any ? kDeferSteps : ~0u;
     uint32_t steps = 0;          // wave-uniform: since the wave's last packets came in
     uint32_t tick = 0;           // wave-uniform: steps taken
     uint32_t cur = 0, end = 0;
@@ -510,7 +509,7 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
                 alive = true;
             }
             fresh = true;
-            steps = 0;
+            if (WRAP) steps = 0;
             cur += take;
             idle = __ballot(!alive);
         }
@@ -526,7 +525,7 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
             if (!live) {
                 flush_exits();
                 stop = 1;
-            } else if (!fresh && (n_in >= P.defer_min || steps >= defer_after) &&
+            } else if (!fresh && (n_in >= P.defer_min || (WRAP && P.defer_any && steps >= kDeferSteps)) &&
                        (uint32_t)__popcll(live) <= (uint32_t)P.defer_lanes) {
                 // (only after a step, so every deferred packet has moved in this generation)
                 flush_exits();
@@ -543,7 +542,7 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
         }
         if (uniform_u32(stop)) break;
         fresh = false;
-        ++steps;
+        if (WRAP) ++steps;
         // Every lane steps: an idle or parked lane's step changes nothing and
         // deposits nothing (selects, not branches, keep the lane state in the
         // same registers round the loop).
@@ -947,7 +946,7 @@ __global__ __launch_bounds__(256) void tail_walk_kernel(TailParams P)
         int fate;
         do {
             fate = walk_step<VEL, VOIGT>(L, P.rec, GlobalSink{P.A}, P.max_cross, dep, ln, wing);
-            if (fate == kAlive && L.ncross % kTailRed == 0 && red_only(R, L.x, L.ku, L.kx, L.ky, L.kz, L.w)) {
+            if (fate == kAlive && (!VOIGT || L.ncross % kTailRed == 0) && red_only(R, L.x, L.ku, L.kx, L.ky, L.kz, L.w)) {
                 // no deposit left: to the red list (it has room for every packet of the batch)
                 save_here(&P.red_state[atomicAdd(&P.counters[kRedCountSlot], 1ull)], L, L.c);
                 break;
