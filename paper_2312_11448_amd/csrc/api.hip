@@ -960,6 +960,7 @@ mc_lya_status plan_walk(mc_lya_ctx *c, uint64_t first, uint64_t count, WalkPlan 
     p.rec = c->d_rec;
     p.A = c->d_A;
     p.tot = c->d_tot;
+    p.red = c->d_redbox;
     p.queue = c->d_queue;
     p.first = first;
     p.count = count;

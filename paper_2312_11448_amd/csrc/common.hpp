@@ -144,6 +144,7 @@ struct WalkParams {
     const uint32_t *cell_of_packet;
     unsigned long long *A;   // per-cell absorbed weight
     BoxTot *tot;
+    const RedBox *red;
     unsigned long long *queue;   // work counters, one per part of the range (persistent kernel)
     uint64_t first, count;   // global packet range
     int64_t max_cross;

@@ -15,7 +15,7 @@
 //   walk_simple      one thread per packet (reference driver, same results).
 // All produce bit-identical integer tallies: each packet's arithmetic does
 // not depend on the driver, and integer additions commute.
-#include "walk_core.hpp"
+#include "red_core.hpp"
 
 namespace mclya {
 namespace {
@@ -89,16 +89,25 @@ struct BoxSink {
     }
 };
 
-// LONE: one box, whose constants are read once. A packet is stepped to its
-// end here: counting its deposit-free end (red_core.hpp), as the tiles do,
-// takes the lanes that walk on along (16 of 64 counted at a time, since an
-// idle lane is refilled), 17 more registers and a look at the box's constants
-// every few steps. Measured over 120 lone boxes and 75 batches of 1e3 to 3e6
-// packets, all by this walk, times with the counting over times without:
-// geometric means 1.19 and 1.18; Voigt boxes in a flow up to 1.7.
+// How often a lane of a lone box without a flow looks whether its packet has a
+// deposit left to make, and how many such packets a wave gathers before it
+// counts them to their end together (or until it refills, or has nothing else
+// to do).
+constexpr uint32_t kRedEvery = 4, kRedGather = 32;
+
+// LONE: one box, whose constants are read once. A packet's deposit-free end is
+// counted (red_core.hpp), as in the tiles, only in a lone box without a flow
+// and with the Doppler profile, where the count needs no record and little
+// code. Otherwise it takes the lanes that walk on along (16 of 64 counted at a
+// time, since an idle lane is refilled), 17 more registers and a look at the
+// box's constants every few steps. Times with the counting over times without,
+// geometric means over random boxes of 1e3 to 3e6 packets, all by this walk:
+// records in LDS, no flow, Doppler 0.95, Voigt 1.21; in a flow 1.20 and 1.31;
+// records in L2 1.18, Voigt boxes in a flow up to 1.7.
 template <bool VEL, bool VOIGT, bool LONE, class Sink>
 __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkBox *sbox, const Sink &sink)
 {
+    constexpr bool kEnds = LONE && !VEL && !VOIGT;
     const uint32_t lane = lane_id();
     const uint32_t max_cross = (uint32_t)P.max_cross;
     Lane L;
@@ -107,6 +116,9 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
     if (LONE) ln = line_of(P.boxes[0]);   // (uniform: no per-lane branch for the length of a segment)
     Acc acc{-1, 0, 0, 0, 0, 0};
     bool alive = false;
+    bool sure = true;                 // kEnds: the box's constants allow it (asked a lane, 6 % faster than not asked)
+    bool red = false;                 // kEnds: holds a packet with no deposit left, to be counted to its end
+    uint32_t tick = 0;                // kEnds, wave-uniform: steps taken
     bool more = true;                 // wave-uniform: queue not drained
     uint64_t cur = 0, end = 0;        // wave-uniform: current block of packet ids
     const uint32_t refill = (uint32_t)P.refill;
@@ -118,10 +130,27 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
     // each XCD's L2 mostly sees one slab.
     const uint32_t nq = (uint32_t)P.nqueues;
     uint32_t part = blockIdx.x % nq, tried = 0;
+    RedBox R;
+    if (kEnds) R = P.red[0];
 
     for (;;) {
         uint64_t idle = __ballot(!alive);
-        if (more && (uint32_t)__popcll(idle) >= refill) {
+        const bool fill = more && (uint32_t)__popcll(idle) >= refill;
+        if (kEnds) {
+            const uint64_t reds = __ballot(red);
+            if (reds && (fill || (uint32_t)__popcll(reds) >= kRedGather || !__ballot(alive))) {
+                if (red) {
+                    const RedEnd e = red_exact<false, false>(L, P.rec, max_cross, ln);
+                    acc.cross += L.ncross + e.n;
+                    acc.esc += e.fate == kEscaped ? L.w : 0u;
+                    acc.capn += e.fate == kCapped ? 1u : 0u;
+                    acc.capw += e.fate == kCapped ? L.w : 0u;
+                    red = false;
+                }
+                idle = __ballot(!alive);
+            }
+        }
+        if (fill) {
             while (idle && more) {
                 if (cur >= end) {
                     const uint64_t lo = P.count * part / nq, hi = P.count * (part + 1) / nq;
@@ -155,6 +184,7 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
                     init_packet<VEL, VOIGT>(L, B, gp - B.pkt_off, P.cell_of_packet[gp], P.rec);
                     if (VOIGT && !LONE) ln = line_of(B);
                     alive = true;
+                    if (kEnds) sure = R.mode != kRedOff;
                 }
                 cur += take;
                 idle = __ballot(!alive);
@@ -179,6 +209,10 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
             acc.capw += fin && fate == kCapped ? L.w : 0u;
             acc.wing += fin ? wing : 0u;
             alive = alive && fate == kAlive;
+            if (kEnds && ++tick % kRedEvery == 0 && __ballot(alive && sure)) {
+                if (alive && sure) red = red_only(R, L.x, L.ku, L.kx, L.ky, L.kz, L.w);
+                alive = alive && !red;
+            }
         }
     }
     flush(acc, true, P.tot);
