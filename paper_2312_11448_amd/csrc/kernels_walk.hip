@@ -89,24 +89,26 @@ struct BoxSink {
     }
 };
 
-// How often a lane looks whether its packet has a deposit left to make (kEnds),
-// and how many such packets a wave gathers before it counts them to their end
-// together (or until it refills, or has nothing else to do).
+// How often a lane of a lone box without a flow looks whether its packet has a
+// deposit left to make, and how many such packets a wave gathers before it
+// counts them to their end together (or until it refills, or has nothing else
+// to do).
 constexpr uint32_t kRedEvery = 4, kRedGather = 32;
 
 // LONE: one box, whose constants are read once. A packet's deposit-free end is
-// counted (red_core.hpp), as in the tiles, only without a flow and with the
-// Doppler profile, where the count needs no record and little code. Otherwise
-// it takes the lanes that walk on along (16 of 64 counted at a time, since an
-// idle lane is refilled), 17 more registers and a look at the box's constants
-// every few steps. Times with the counting over times without, geometric means
-// over random boxes of 1e3 to 3e6 packets, all by this walk: without a flow,
-// Doppler, a lone box 0.95, a batch 0.95, Voigt 1.18 and 1.13; in a flow,
-// Doppler 1.17 and 1.11, Voigt 1.36 and 1.37.
+// counted (red_core.hpp), as in the tiles, only in a lone box without a flow
+// and with the Doppler profile, where the count needs no record and little
+// code. Otherwise it takes the lanes that walk on along (16 of 64 counted at a
+// time, since an idle lane is refilled), 17 more registers and a look at the
+// box's constants every few steps. Times with the counting over times without,
+// geometric means over random boxes of 1e3 to 3e6 packets, all by this walk:
+// records in LDS, no flow, Doppler 0.95, Voigt 1.18; in a flow 1.17 and 1.36;
+// batches without a flow, Doppler, 0.91 from 25 000 to 130 000 packets and
+// 1.10 above, Voigt 1.13, in a flow 1.11 and 1.37.
 template <bool VEL, bool VOIGT, bool LONE, class Sink>
 __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkBox *sbox, const Sink &sink)
 {
-    constexpr bool kEnds = !VEL && !VOIGT;
+    constexpr bool kEnds = LONE && !VEL && !VOIGT;
     const uint32_t lane = lane_id();
     const uint32_t max_cross = (uint32_t)P.max_cross;
     Lane L;
@@ -129,8 +131,8 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
     // each XCD's L2 mostly sees one slab.
     const uint32_t nq = (uint32_t)P.nqueues;
     uint32_t part = blockIdx.x % nq, tried = 0;
-    const RedBox lone = kEnds ? P.red[0] : RedBox{};
-    auto red_of = [&](int box) { return LONE ? lone : P.red[box]; };
+    RedBox R;
+    if (kEnds) R = P.red[0];
 
     for (;;) {
         uint64_t idle = __ballot(!alive);
@@ -183,7 +185,7 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
                     init_packet<VEL, VOIGT>(L, B, gp - B.pkt_off, P.cell_of_packet[gp], P.rec);
                     if (VOIGT && !LONE) ln = line_of(B);
                     alive = true;
-                    if (kEnds) sure = red_of(nb).mode != kRedOff;
+                    if (kEnds) sure = R.mode != kRedOff;
                 }
                 cur += take;
                 idle = __ballot(!alive);
@@ -209,7 +211,7 @@ __device__ __forceinline__ void persistent_walk(const WalkParams &P, const WalkB
             acc.wing += fin ? wing : 0u;
             alive = alive && fate == kAlive;
             if (kEnds && ++tick % kRedEvery == 0 && __ballot(alive && sure)) {
-                if (alive && sure) red = red_only(red_of(acc.box), L.x, L.ku, L.kx, L.ky, L.kz, L.w);
+                if (alive && sure) red = red_only(R, L.x, L.ku, L.kx, L.ky, L.kz, L.w);
                 alive = alive && !red;
             }
         }
