@@ -516,15 +516,15 @@ uint64_t shared_from(const mc_lya_ctx *c, int nt, uint64_t n)
 // packets a tile 774, 692 and 8000 941, 2516; 8 of up to 24^3, 331 776 packets
 // 3573, 4442 and 55 296 1753, 966; 6 of up to 40^3, 2.7e5 3382, 2854, 5.8e5
 // 4071, 5655 and 1.2e6 5809, 10598.
-// Voigt in a flow, with a box that is not cut along every axis: 35 boxes, 3.75e6
-// packets, 30 000 a tile 11013, 8533; two of 30 x 9 x 20 with 30 000 a tile
-// 1292, 1169 and with 60 000 1709, 1616.
+// Voigt in a flow, boxes not cut along every axis, 30 000 to 70 000 a tile: two of
+// about 20^3 1152, 3527; three 844, 1556; seven 1938, 3432; 22 3490, 8428; the
+// worst of 180 batches, 35 boxes of 10^3 to 24^3, 11190, 9735.
 // Boxes of one tile each, and few packets in all: with a flow or a Voigt profile
 // (not both) two with 5000 each 497, 353 and 617, 434; ten with 5000 540, 447
 // and 645, 497; three with 20 000 518, 489 and 566, 558. (Of the others' lines,
 // drawn against slower persistent walks and kept: three with 2600 415, 301;
 // five with 2600 in a flow with Voigt profiles 677, 501.)
-constexpr uint64_t kBatchLone = 2500, kBatchTile = 30000, kBatchHard = 120000, kBatchLeast = 60000;
+constexpr uint64_t kBatchLone = 2500, kBatchTile = 30000, kBatchLeast = 60000;
 int sharing(const mc_lya_ctx *c, int nt, uint64_t packets)
 {
     const uint64_t per = packets / ((uint64_t)nt * kSharePackets);
@@ -569,17 +569,16 @@ mc_lya_status classify_boxes(mc_lya_ctx *c, uint64_t first, uint64_t count)
         if (m[0]) share = sharing(c, nt, count);
     } else if (c->tile_share > 0) {
         int all = 0;
-        bool lone_tiles = true, cut = true;
+        bool lone_tiles = true;
         uint64_t packets = 0;
         for (int b = 0; b < nb; ++b) {
             const int t = tiles_of_box(c->desc[b]);
             all += t;
             lone_tiles = lone_tiles && t == 1;
-            cut = cut && cut_along_all(c->desc[b]);
             packets += walked(b);
         }
         const bool few = all < c->num_cu;
-        const uint64_t line = lone_tiles ? kBatchLone : (c->vel && c->voigt && !cut ? kBatchHard : kBatchTile);
+        const uint64_t line = lone_tiles ? kBatchLone : kBatchTile;
         const uint64_t least = lone_tiles && c->vel != c->voigt ? kBatchLeast : 0;
         if (few && packets >= std::max((uint64_t)all * line, least)) {
             int nt = 0;
