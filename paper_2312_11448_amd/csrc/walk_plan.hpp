@@ -51,12 +51,14 @@ inline WalkLaunch plan_persistent(const WalkOptions &o, uint64_t count, int num_
     // Few packets: a chunk for each of four waves a compute unit, one per
     // SIMD (whole chunks would leave most of the chip without; one for
     // every resident wave leaves none to refill the lanes that finish
-    // first). Transports with 256 a chunk, with one for all 3072 waves,
-    // with this, us: 28 518 packets (23^3, flow) 632, 416, 416; 62 046
-    // (Voigt, flow) 970, 785, 783; 139 172 (30^3, Voigt, flow) 683, 751,
-    // 708; 156 927 (Voigt, flow) 616, 712, 626; from 262 144 on 256.
-    const uint64_t each = count / (4 * (uint64_t)num_cu);
-    l.chunk = free ? (int)std::min<uint64_t>((uint64_t)o.chunk, std::max<uint64_t>(64, each)) : o.chunk;
+    // first), from 128 packets a chunk on for each of eight. Transports with
+    // 256 a chunk, with one for all 3072 waves, with this, us: 28 518 packets
+    // (23^3, flow) 632, 416, 416; 62 046 (Voigt, flow) 970, 785, 783; 139 172
+    // (30^3, Voigt, flow) 683, 751, 708; 156 927 (Voigt, flow) 616, 712, 626;
+    // 262 296 (four of 40^3) 2165, 1700, 1864; from 524 288 on 256.
+    const uint64_t per4 = count / (4 * (uint64_t)num_cu), per8 = per4 / 2;
+    const uint64_t each = std::max({(uint64_t)64, std::min<uint64_t>(per4, 128), per8});
+    l.chunk = free ? (int)std::min<uint64_t>((uint64_t)o.chunk, each) : o.chunk;
     l.nqueues = o.nqueues;
     return l;
 }

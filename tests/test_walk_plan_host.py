@@ -66,4 +66,4 @@ def test_the_defaults_follow_the_packets(plan, count, cap, lone):
     if lone:
         assert l["chunk"] == 64 and l["queues"] == 1
     else:
-        assert l["queues"] == 8 and (l["chunk"] == 256) == (count >= 262_144)
+        assert l["queues"] == 8 and (l["chunk"] == 256) == (count >= 524_288)
