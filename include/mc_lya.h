@@ -217,7 +217,9 @@ enum {
                                      of a batch are in flight (0..1000000; 0 = never), one
                                      kernel walks them to the end with device-wide deposits
                                      instead of further, thinning tile generations. Not set:
-                                     60 000 packets and 3 % of the batch, at most a fifth */
+                                     60 000 packets and 3 % of the batch, at most half of it
+                                     (no value that can be set stands for that: a context
+                                     whose option was set keeps a share) */
     MC_LYA_OPT_BESIDE = 16        /* kernel 2 with both parts: the persistent walk of the
                                      untiled boxes runs beside the tile generations on a
                                      stream of its own, with at most this many waves per

@@ -512,13 +512,15 @@ uint64_t shared_from(const mc_lya_ctx *c, int nt, uint64_t n)
 // tiles would have more than four times the mean work is left to the
 // persistent walk, which is bound by the deposits in device memory. Boxes of
 // several tiles and very different walks take as many generations as the
-// longest. Transports, us (tiles, persistent): 24 boxes of up to 14^3, 1300
-// packets a tile 774, 692 and 8000 941, 2516; 8 of up to 24^3, 331 776 packets
-// 3573, 4442 and 55 296 1753, 966; 6 of up to 40^3, 2.7e5 3382, 2854, 5.8e5
-// 4071, 5655 and 1.2e6 5809, 10598.
-// Voigt in a flow, boxes not cut along every axis, 30 000 to 70 000 a tile: two of
-// about 20^3 1152, 3527; three 844, 1556; seven 1938, 3432; 22 3490, 8428; the
-// worst of 180 batches, 35 boxes of 10^3 to 24^3, 11190, 9735.
+// longest. Transports with so many packets a tile, us (tiles, persistent):
+//   24 boxes of 14^3, a tile each, 2500 451, 415 and 8000 512, 771; Voigt in a
+//     flow 2500 741, 615 and 8000 872, 969;
+//   8 of 24^3, 64 tiles, 10 000 721, 1563 and 30 000 1142, 3437; Voigt in a flow
+//     10 000 1209, 1840 and 30 000 2076, 4492;
+//   8 of up to 24^3, 36 tiles, Voigt in a flow, 3000 754, 743 and 30 000 1915,
+//     2919; 35 of 10^3 to 24^3, Voigt in a flow, 25 000 11190, 9735.
+// (The second line was drawn against slower tiles and is kept: it could be lower
+// wherever the boxes are alike.)
 // Boxes of one tile each, and few packets in all: with a flow or a Voigt profile
 // (not both) two with 5000 each 497, 353 and 617, 434; ten with 5000 540, 447
 // and 645, 497; three with 20 000 518, 489 and 566, 558. (Of the others' lines,
@@ -680,7 +682,7 @@ mc_lya_status timed_end(mc_lya_ctx *c, hipEvent_t e1)
 
 // The tail walk takes over once fewer than this many of a batch's n packets
 // are in flight (MC_LYA_OPT_TAIL, in millionths of the batch). Where it is not
-// set: 3 % and 60 000 more, at most a fifth. Each generation of tiles costs 30
+// set: 3 % and 60 000 more, at most half. Each generation of tiles costs 30
 // to 150 us however few packets it walks, the tail walk as much in all plus
 // its deposits in device memory, so the best share falls with the batch:
 // transports at 2 %, here and at twice as much, us: 3.0e5 packets (64^3) 738,

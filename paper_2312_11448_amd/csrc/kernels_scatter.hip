@@ -44,8 +44,8 @@
 // path's end, a failed trial (one in 20) is repeated beside the other lanes'
 // next events, and the half of the searches inside r_safe that end from below
 // are not repeated over the whole flight.
-// 32^3, Voigt, zeta = 1e4: 131 072 photons at p = 1e-4 (8700 events each) 473
-// -> 235 ms, 1 048 576 at 1e-3 166 -> 92 ms; 13^3, 3000 photons at 2e-4 237 ->
+// 32^3, Voigt, zeta = 1e4: 131 072 photons at p = 1e-4 (8700 events each) 607
+// -> 264 ms, 1 048 576 at 1e-3 166 -> 92 ms; 13^3, 3000 photons at 2e-4 237 ->
 // 63 ms.
 #include "walk_core.hpp"
 
@@ -286,55 +286,55 @@ __device__ __forceinline__ int fly(Photon &P, const WalkBox &B, const ScatBox &S
         float s_max = (float)rsafe;
         if (!near) {
             // next face (ties: x, then y, then z)
-                const double tx = P.kx > 0.0 ? (1.0 - P.fx) / P.kx : (P.kx < 0.0 ? P.fx / -P.kx : 1.0e300);
-                const double ty = P.ky > 0.0 ? (1.0 - P.fy) / P.ky : (P.ky < 0.0 ? P.fy / -P.ky : 1.0e300);
-                const double tz = P.kz > 0.0 ? (1.0 - P.fz) / P.kz : (P.kz < 0.0 ? P.fz / -P.kz : 1.0e300);
-                const bool bx = tx <= ty && tx <= tz;
-                const bool by = !bx && ty <= tz;
-                const double sf = bx ? tx : (by ? ty : tz);
-                const float xf = fmaf(-B.delta, (float)sf, P.x);
-                const bool inert = xf <= -S.x_inert;
-                const float dx = inert ? P.x + S.x_inert : B.delta * (float)sf;
-                const float dtau = kap * swept(P.x, dx, S.damp);
-                if (dtau < P.tau) {
-                    if (inert) {
-                        // lost where the frequency reaches -x_inert, inside this cell
-                        const double sl = (double)((P.x + S.x_inert) / B.delta);
-                        P.fx = fmin(fmax(P.fx + P.kx * sl, 0.0), 1.0);
-                        P.fy = fmin(fmax(P.fy + P.ky * sl, 0.0), 1.0);
-                        P.fz = fmin(fmax(P.fz + P.kz * sl, 0.0), 1.0);
-                        x_stop = -S.x_inert;
-                        return kSLost;
-                    }
-                    P.tau -= dtau;
-                    // cross the face into the neighbour (periodic)
-                    const double nfx = fmin(fmax(P.fx + P.kx * sf, 0.0), 1.0);
-                    const double nfy = fmin(fmax(P.fy + P.ky * sf, 0.0), 1.0);
-                    const double nfz = fmin(fmax(P.fz + P.kz * sf, 0.0), 1.0);
-                    P.fx = nfx;
-                    P.fy = nfy;
-                    P.fz = nfz;
-                    if (bx) {
-                        if (P.kx > 0.0) { P.fx = 0.0; P.ix = P.ix + 1 == B.nx ? 0 : P.ix + 1; ++P.mx; }
-                        else { P.fx = 1.0; P.ix = P.ix == 0 ? B.nx - 1 : P.ix - 1; --P.mx; }
-                    } else if (by) {
-                        if (P.ky > 0.0) { P.fy = 0.0; P.iy = P.iy + 1 == B.ny ? 0 : P.iy + 1; ++P.my; }
-                        else { P.fy = 1.0; P.iy = P.iy == 0 ? B.ny - 1 : P.iy - 1; --P.my; }
-                    } else {
-                        if (P.kz > 0.0) { P.fz = 0.0; P.iz = P.iz + 1 == B.nz ? 0 : P.iz + 1; ++P.mz; }
-                        else { P.fz = 1.0; P.iz = P.iz == 0 ? B.nz - 1 : P.iz - 1; --P.mz; }
-                    }
-                    P.c = B.cell_off + (uint32_t)P.ix + (uint32_t)B.nx * ((uint32_t)P.iy + (uint32_t)B.ny * (uint32_t)P.iz);
-                    const Rec nr = load_rec<VEL>(rec, P.c);
-                    if (VEL)
-                        P.x = xf - ((float)P.kx * (nr.ux - P.r.ux) + (float)P.ky * (nr.uy - P.r.uy) +
-                                    (float)P.kz * (nr.uz - P.r.uz));
-                    else
-                        P.x = xf;
-                    P.r = nr;
-                    ++P.ncross;
-                    return kSAlive;
+            const double tx = P.kx > 0.0 ? (1.0 - P.fx) / P.kx : (P.kx < 0.0 ? P.fx / -P.kx : 1.0e300);
+            const double ty = P.ky > 0.0 ? (1.0 - P.fy) / P.ky : (P.ky < 0.0 ? P.fy / -P.ky : 1.0e300);
+            const double tz = P.kz > 0.0 ? (1.0 - P.fz) / P.kz : (P.kz < 0.0 ? P.fz / -P.kz : 1.0e300);
+            const bool bx = tx <= ty && tx <= tz;
+            const bool by = !bx && ty <= tz;
+            const double sf = bx ? tx : (by ? ty : tz);
+            const float xf = fmaf(-B.delta, (float)sf, P.x);
+            const bool inert = xf <= -S.x_inert;
+            const float dx = inert ? P.x + S.x_inert : B.delta * (float)sf;
+            const float dtau = kap * swept(P.x, dx, S.damp);
+            if (dtau < P.tau) {
+                if (inert) {
+                    // lost where the frequency reaches -x_inert, inside this cell
+                    const double sl = (double)((P.x + S.x_inert) / B.delta);
+                    P.fx = fmin(fmax(P.fx + P.kx * sl, 0.0), 1.0);
+                    P.fy = fmin(fmax(P.fy + P.ky * sl, 0.0), 1.0);
+                    P.fz = fmin(fmax(P.fz + P.kz * sl, 0.0), 1.0);
+                    x_stop = -S.x_inert;
+                    return kSLost;
                 }
+                P.tau -= dtau;
+                // cross the face into the neighbour (periodic)
+                const double nfx = fmin(fmax(P.fx + P.kx * sf, 0.0), 1.0);
+                const double nfy = fmin(fmax(P.fy + P.ky * sf, 0.0), 1.0);
+                const double nfz = fmin(fmax(P.fz + P.kz * sf, 0.0), 1.0);
+                P.fx = nfx;
+                P.fy = nfy;
+                P.fz = nfz;
+                if (bx) {
+                    if (P.kx > 0.0) { P.fx = 0.0; P.ix = P.ix + 1 == B.nx ? 0 : P.ix + 1; ++P.mx; }
+                    else { P.fx = 1.0; P.ix = P.ix == 0 ? B.nx - 1 : P.ix - 1; --P.mx; }
+                } else if (by) {
+                    if (P.ky > 0.0) { P.fy = 0.0; P.iy = P.iy + 1 == B.ny ? 0 : P.iy + 1; ++P.my; }
+                    else { P.fy = 1.0; P.iy = P.iy == 0 ? B.ny - 1 : P.iy - 1; --P.my; }
+                } else {
+                    if (P.kz > 0.0) { P.fz = 0.0; P.iz = P.iz + 1 == B.nz ? 0 : P.iz + 1; ++P.mz; }
+                    else { P.fz = 1.0; P.iz = P.iz == 0 ? B.nz - 1 : P.iz - 1; --P.mz; }
+                }
+                P.c = B.cell_off + (uint32_t)P.ix + (uint32_t)B.nx * ((uint32_t)P.iy + (uint32_t)B.ny * (uint32_t)P.iz);
+                const Rec nr = load_rec<VEL>(rec, P.c);
+                if (VEL)
+                    P.x = xf - ((float)P.kx * (nr.ux - P.r.ux) + (float)P.ky * (nr.uy - P.r.uy) +
+                                (float)P.kz * (nr.uz - P.r.uz));
+                else
+                    P.x = xf;
+                P.r = nr;
+                ++P.ncross;
+                return kSAlive;
+            }
             // the scattering point lies inside this cell
             s_max = inert ? (P.x + S.x_inert) / B.delta : (float)sf;
         }

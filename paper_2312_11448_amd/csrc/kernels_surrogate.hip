@@ -392,9 +392,10 @@ __device__ __forceinline__ void stage_params(const float *__restrict__ P, float 
 }
 
 // Inference, 32 cells a wave at a time. What bounds it is the issue of VALU and
-// matrix instructions, which do not overlap: their counters (61 % and 38 % of
-// the cycles) add up to the kernel's time, whatever their order; the memory
-// traffic alone takes half as long. So b2 enters as the C operand of a chain's
+// matrix instructions by the two waves a SIMD holds (179 registers): the
+// counters say 61 % and 38 % of the cycles, next to no overlap. (Three waves of
+// 154 registers overlapped some, 70 % and 46 %, with more instructions, and
+// took 237 us.) The memory traffic alone takes half as long. So b2 enters as the C operand of a chain's
 // first product (10 products a tile instead of 12; hi + lo is exact in binary32,
 // so the sums are the same), and results and flags go out through views that
 // drop the lanes and rows past the end (no branch; 115 VALU instructions instead
@@ -622,7 +623,8 @@ walked:
 // lane's own strided reads of its operands were a chain of 80), the batch is
 // read through its index list here (IDX) instead of by a gather of its own,
 // and the slots' sum, the normalisation and Adam are one kernel. A step on
-// 65 536 index-picked cells went from 7 launches and 85 us to 2 and 24 us.
+// 65 536 index-picked cells went from 7 launches to 2: 84 -> 39 us of a call's
+// time, 52 -> 20 us on the device.
 constexpr int kGradWaves = 4;
 
 struct GradLds {

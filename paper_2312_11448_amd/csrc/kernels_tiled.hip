@@ -431,10 +431,10 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
     uint32_t cur = 0, end = 0;
     const uint32_t chunk = (uint32_t)P.chunk;
     // refilling stalls the whole wave on the new packets' loads: wait until
-    // this many lanes are idle (1..64; 64 waits for all). On 256^3 a threshold
-    // of 24 / 32 / 40 / 48 walks in 107.6 / 105.8 / 108.2 / 114.4 ms: fewer
-    // lanes idle against fewer refill passes. With 112-byte states the best
-    // was 40, at 136 ms: a refill then read 2.6 sectors a lane, now 1.
+    // this many lanes are idle (1..64; 64 waits for all). A step on 256^3 with a
+    // threshold of 24 / 32 / 40 / 48 takes 91.3 / 89.7 / 90.4 / 93.9 ms, on
+    // 128^3 4.57 / 4.51 / 4.59 / 4.69: fewer lanes idle against fewer refill
+    // passes.
     const uint32_t refill = (uint32_t)min(max(P.refill, 1), 64);
     // a ring slot of this lane's own (the ring's z = -1 plane has 324 slots),
     // whose tally is never read: where a lane with nothing to deposit adds 0
@@ -444,75 +444,75 @@ __device__ __forceinline__ void walk_tile(const TileParams &P, const TileInfo &t
     for (;;) {
         uint64_t idle = __ballot(!alive);
         if (more && (uint32_t)__popcll(idle) >= refill) {
-        flush_exits();
-        while (idle && more) {
-            if (cur >= end) {
-                // near the end of the input the claims shrink, so that the
-                // last packets spread over the waves instead of leaving one
-                // wave with a whole chunk while the others are done
-                uint32_t base = 0, want = 0;
-                if (lane == 0) {
-                    const uint32_t seen = __hip_atomic_load(s_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    const uint32_t left = seen < n_in ? n_in - seen : 0u;
-                    want = left < chunk * kWaves ? max(left / kWaves, min(chunk, n_in < 64u * kWaves ? 64u : kMinClaim)) : chunk;
-                    base = atomicAdd(s_next, want);
-                }
-                base = uniform_u32(__shfl(base, 0, 64));
-                want = uniform_u32(__shfl(want, 0, 64));
-                if (base >= n_in) {
-                    more = false;
-                    break;
-                }
-                cur = base;
-                end = base + want < n_in ? base + want : n_in;
-            }
-            const uint32_t take = min((uint32_t)__popcll(idle), end - cur);
-            const uint32_t r = rank_in(idle);
-            if (!alive && r < take) {
-                const uint32_t j = (GEN0 ? j0 : 0u) + cur + r;
-                Lane N;
-                int32_t lx, ly, lz;
-                if (GEN0) {
-                    int lo = 0, hi = ncell - 1;             // largest cell with pre <= j
-                    while (lo < hi) {
-                        const int mid = (lo + hi + 1) >> 1;
-                        if (pre[mid] <= j) lo = mid; else hi = mid - 1;
+            flush_exits();
+            while (idle && more) {
+                if (cur >= end) {
+                    // near the end of the input the claims shrink, so that the
+                    // last packets spread over the waves instead of leaving one
+                    // wave with a whole chunk while the others are done
+                    uint32_t base = 0, want = 0;
+                    if (lane == 0) {
+                        const uint32_t seen = __hip_atomic_load(s_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        const uint32_t left = seen < n_in ? n_in - seen : 0u;
+                        want = left < chunk * kWaves ? max(left / kWaves, min(chunk, n_in < 64u * kWaves ? 64u : kMinClaim)) : chunk;
+                        base = atomicAdd(s_next, want);
                     }
-                    lx = lo % ti.sx;
-                    ly = (lo / ti.sx) % ti.sy;
-                    lz = lo / (ti.sx * ti.sy);
-                    const uint32_t gc = B.cell_off + (uint32_t)(ti.ox + lx) +
-                                        (uint32_t)B.nx * ((uint32_t)(ti.oy + ly) + (uint32_t)B.ny * (uint32_t)(ti.oz + lz));
-                    const uint64_t pf = P.pfirst[gc];
-                    const uint64_t gp = (pf > r_lo ? pf : r_lo) + (j - pre[lo]);
-                    emit_packet<VOIGT>(N, B, gp - B.pkt_off, gc);
-                    const Rec rc = rec_at<VEL>(recs, tile_slot(lx, ly, lz) * RS);   // the emission cell's record
-                    N.kap = rc.kap;
-                    N.ku = VEL ? ray_velocity(N.kx, N.ky, N.kz, rc) : 0.0f;
-                } else {
-                    // the list holding position j (independent reads of the
-                    // list prefix, not a chain)
-                    int k = 0;
-#pragma unroll
-                    for (int m = 1; m <= 6; ++m) k += (m <= ti.nsrc() && pre[m] <= j) ? 1 : 0;
-                    const uint32_t g = P.in_idx[lst[k] + (j - pre[k])];
-                    const PState o = P.in_state[g];
-                    load_state(N, o, B);
-                    lx = (int32_t)(o.pos & 15u);
-                    ly = (int32_t)(o.pos >> 4 & 15u);
-                    lz = (int32_t)(o.pos >> 8);
-                    const Rec rc = rec_at<VEL>(recs, tile_slot(lx, ly, lz) * RS);
-                    if (k < ti.nsrc()) finish_entry<VEL>(N, rc);   // entering through a face
-                    else N.kap = rc.kap;                         // deferred inside its cell
+                    base = uniform_u32(__shfl(base, 0, 64));
+                    want = uniform_u32(__shfl(want, 0, 64));
+                    if (base >= n_in) {
+                        more = false;
+                        break;
+                    }
+                    cur = base;
+                    end = base + want < n_in ? base + want : n_in;
                 }
-                to_tile<RS>(L, N, lx, ly, lz);
-                alive = true;
+                const uint32_t take = min((uint32_t)__popcll(idle), end - cur);
+                const uint32_t r = rank_in(idle);
+                if (!alive && r < take) {
+                    const uint32_t j = (GEN0 ? j0 : 0u) + cur + r;
+                    Lane N;
+                    int32_t lx, ly, lz;
+                    if (GEN0) {
+                        int lo = 0, hi = ncell - 1;             // largest cell with pre <= j
+                        while (lo < hi) {
+                            const int mid = (lo + hi + 1) >> 1;
+                            if (pre[mid] <= j) lo = mid; else hi = mid - 1;
+                        }
+                        lx = lo % ti.sx;
+                        ly = (lo / ti.sx) % ti.sy;
+                        lz = lo / (ti.sx * ti.sy);
+                        const uint32_t gc = B.cell_off + (uint32_t)(ti.ox + lx) +
+                                            (uint32_t)B.nx * ((uint32_t)(ti.oy + ly) + (uint32_t)B.ny * (uint32_t)(ti.oz + lz));
+                        const uint64_t pf = P.pfirst[gc];
+                        const uint64_t gp = (pf > r_lo ? pf : r_lo) + (j - pre[lo]);
+                        emit_packet<VOIGT>(N, B, gp - B.pkt_off, gc);
+                        const Rec rc = rec_at<VEL>(recs, tile_slot(lx, ly, lz) * RS);   // the emission cell's record
+                        N.kap = rc.kap;
+                        N.ku = VEL ? ray_velocity(N.kx, N.ky, N.kz, rc) : 0.0f;
+                    } else {
+                        // the list holding position j (independent reads of the
+                        // list prefix, not a chain)
+                        int k = 0;
+#pragma unroll
+                        for (int m = 1; m <= 6; ++m) k += (m <= ti.nsrc() && pre[m] <= j) ? 1 : 0;
+                        const uint32_t g = P.in_idx[lst[k] + (j - pre[k])];
+                        const PState o = P.in_state[g];
+                        load_state(N, o, B);
+                        lx = (int32_t)(o.pos & 15u);
+                        ly = (int32_t)(o.pos >> 4 & 15u);
+                        lz = (int32_t)(o.pos >> 8);
+                        const Rec rc = rec_at<VEL>(recs, tile_slot(lx, ly, lz) * RS);
+                        if (k < ti.nsrc()) finish_entry<VEL>(N, rc);   // entering through a face
+                        else N.kap = rc.kap;                         // deferred inside its cell
+                    }
+                    to_tile<RS>(L, N, lx, ly, lz);
+                    alive = true;
+                }
+                fresh = true;
+                if (WRAP) steps = 0;
+                cur += take;
+                idle = __ballot(!alive);
             }
-            fresh = true;
-            if (WRAP) steps = 0;
-            cur += take;
-            idle = __ballot(!alive);
-        }
         }
         // The wave stops once the input is used up and no lane is live (while
         // there is input, a wave with every lane idle refills), or, once the

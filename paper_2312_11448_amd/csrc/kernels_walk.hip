@@ -70,9 +70,10 @@ __device__ __forceinline__ uint64_t packet_id(const WalkParams &P, uint64_t i)
 
 // ---- persistent driver ---------------------------------------------------
 // The records of a lone box in LDS (walk_box_kernel), its tallies there too
-// (a small box) or in device memory. No global load is then in a step, so a
-// step never waits for an earlier step's deposit (loads and atomics return in
-// order).
+// (a small box) or in device memory. No load of the walk's data goes to device
+// memory in a step then, so a step does not wait for an earlier step's deposit
+// (loads and atomics return in order); Voigt variants spill 16 or 24 bytes a
+// lane.
 struct BoxSink {
     static constexpr bool kCell = true;
     unsigned long long *A;        // in LDS or device memory
