@@ -44,8 +44,8 @@
 // path's end, a failed trial (one in 20) is repeated beside the other lanes'
 // next events, and the half of the searches inside r_safe that end from below
 // are not repeated over the whole flight.
-// 32^3, Voigt, zeta = 1e4: 131 072 photons at p = 1e-4 (8700 events each) 607
-// -> 264 ms, 1 048 576 at 1e-3 166 -> 92 ms; 13^3, 3000 photons at 2e-4 237 ->
+// 32^3, Voigt, zeta = 1e4: 131 072 photons at p = 1e-4 (8700 events each) 549
+// -> 257 ms, 1 048 576 at 1e-3 166 -> 92 ms; 13^3, 3000 photons at 2e-4 237 ->
 // 63 ms.
 #include "walk_core.hpp"
 
